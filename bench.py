@@ -48,10 +48,11 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def algorithmic_ops(work, mode):
+def algorithmic_ops(work, mode, packets=0):
+    """``packets``: the sampled form's packet shape (0: it walks fans of instants)."""
     box, prism, edges, inserts = (int(work[i]) for i in range(4))
     if mode == "sampled":
-        return box * COST["ray_box"] + prism * COST["ray_prism"] + edges * COST["ray_edge"]
+        return box * COST["ray_box" if packets else "fan_box"] + prism * COST["ray_prism"] + edges * COST["ray_edge"]
     return box * COST["fan_box"] + prism * COST["fan_prism"] + edges * COST["fan_edge"] + \
         inserts * COST["insert"]
 
@@ -691,7 +692,7 @@ def main():
             sa.sa_accumulate(ctx, scene, pts, path, sa.SA_SAMPLED, counts_s, mins_s, work=work)
             ctx.sync()
             ws = work.cpu().numpy()
-            sops = algorithmic_ops(ws, "sampled")
+            sops = algorithmic_ops(ws, "sampled", ctx.get_launch()["sampled_instants_per_packet"])
             result["sampled"]["roofline_frac"] = (sops / (result["sampled"]["ms_per_pass"] / 1e3)) / LANE_OP_PEAK
             result["sampled"]["work_per_pass"] = {"box_tests": int(ws[0]), "prism_tests": int(ws[1]),
                                                   "prism_edges": int(ws[2]),

@@ -94,8 +94,11 @@ typedef struct {
     int32_t accrual_waves_per_simd;      /* accrual form: occupancy variant of its kernel, 6, 7 or 8
                                             waves per SIMD (registers per lane shrink as it grows);
                                             0 = 8 */
-    int32_t sampled_instants_per_packet; /* sampled form: instants a wave's packet takes per point,
-                                            1, 2, 4, 8 or 16 (so 64 down to 4 points); 0 = 8 */
+    int32_t sampled_instants_per_packet; /* sampled form: 0 = by fans of instants (sa_accumulate; packets
+                                            of 8 where no scratch may be used: under stream capture, in
+                                            sa_accumulate_noalloc, out of memory); 1, 2, 4, 8 or 16 =
+                                            packets of that many instants per point (so 64 down to 4
+                                            points) in any case */
     int32_t reserved[2];                 /* 0 */
 } sa_launch;
 /* Errors: INVALID_ARG (negative or out-of-range values). */
@@ -318,7 +321,10 @@ typedef struct {
  * run as several launches, the continuous shadow one day at least) in
  * memory the context owns: grown on first need with the stream
  * synchronised, kept until sa_destroy.  Under stream capture make one
- * eager call of the same (or a larger) size first.
+ * eager call of the same (or a larger) size first.  The sampled form keeps
+ * the same views per 16 instants and a 16-bit mask per point and 16
+ * instants, likewise at most 256 MiB each per launch; it needs neither, nor
+ * an eager call, under stream capture.
  * Errors: INVALID_ARG, CAPACITY (reported by sa_sync if the accrual spill
  * queue overflows), OOM, DEVICE. */
 sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts,

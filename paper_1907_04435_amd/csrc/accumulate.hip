@@ -53,18 +53,6 @@ __device__ __forceinline__ void put_bin(const BinOut &O, int64_t o, bool fresh, 
 }
 
 // ------------------------------------------------------------------ sampled
-// Sum a per-lane counter over the wave and add it to a global total.
-__device__ __forceinline__ void flush_work(const Work &w, uint64_t *work)
-{
-    uint32_t v[8] = {w.box, w.prism, w.edges, w.inserts, w.nodes, w.units, w.spills, w.leaves};
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        uint64_t s = v[c];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-        if ((tid() & 63) == 0 && s) atomicAdd((unsigned long long *)&work[c], (unsigned long long)s);
-    }
-}
-
 // Outputs of the sampled form (parked in LDS by the kernel).
 struct SampOut {
     int32_t *counts;
@@ -557,24 +545,6 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
     ov = lane_in(ovm);
 }
 
-// The view of node `nd` for segment g, with child references r0 (left)
-// and r1 (right) already in view form (byte offsets, or leaf / absent).
-__device__ __forceinline__ SegNode make_view(const Node &nd, int r0, int r1, const SegConst &g)
-{
-    const FanGeom f = fan_geom(g);
-    const bool lfirst = seg_key(nd.lx0, nd.ly0, nd.lx1, nd.ly1, g.mdx, g.mdy) <=
-                        seg_key(nd.rx0, nd.ry0, nd.rx1, nd.ry1, g.mdx, g.mdy);
-    SegNode v;
-    const int a = lfirst ? 0 : 1;
-    seg_child(f, nd.lx0, nd.ly0, nd.lx1, nd.ly1, nd.lz1, nd.left != kNone, v.c[a]);
-    seg_child(f, nd.rx0, nd.ry0, nd.rx1, nd.ry1, nd.rz1, nd.right != kNone, v.c[1 - a]);
-    v.ref[a] = r0;
-    v.ref[1 - a] = r1;
-    return v;
-}
-
-__device__ __forceinline__ int view_ref(int r) { return r >= 0 ? r * (int)sizeof(SegNode) : r; }
-
 // The per-segment node views of segments [j0, j1): one thread per
 // (segment, node), written to out[(j - j0) * stride + node].
 __global__ void k_seg_nodes(const Node *__restrict__ nodes, int n_nodes, const SegConst *__restrict__ segs, int j0,
@@ -585,7 +555,8 @@ __global__ void k_seg_nodes(const Node *__restrict__ nodes, int n_nodes, const S
     const int jj = (int)(t / n_nodes);
     const int node = (int)(t - (int64_t)jj * n_nodes);
     const Node nd = nodes[node];
-    out[jj * stride + node] = make_view(nd, view_ref(nd.left), view_ref(nd.right), segs[j0 + jj]);
+    const SegConst &g = segs[j0 + jj];
+    out[jj * stride + node] = make_view(nd, view_ref(nd.left), view_ref(nd.right), fan_geom(g), g.mdx, g.mdy);
 }
 
 // Roof-covered: inside a footprint (other than the point's own building)
@@ -1141,7 +1112,8 @@ __global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__
     if (c >= vcount[v]) return;
     const Node nd = vnodes[(int64_t)v * n_nodes + vlist[vc]];
     const int2 r = vref[vc];
-    out[jj * stride + n_nodes + vc] = make_view(nd, r.x, r.y, segs[j0 + jj]);
+    const SegConst &g = segs[j0 + jj];
+    out[jj * stride + n_nodes + vc] = make_view(nd, r.x, r.y, fan_geom(g), g.mdx, g.mdy);
 }
 
 // tile_off[v] = first tile of variant v, 64 points per tile

@@ -27,6 +27,9 @@ struct sa_ctx {
     sa::Scratch scratch_grad;     // FP64 height-gradient accumulator
     sa::Scratch scratch_w;        // per-bin weights of a region score
     sa::Scratch scratch_piece;    // per-piece sums of accrual launches on few tiles
+    sa::Scratch scratch_fan;      // node views of the sampled form's fans (their own: a graph captured
+                                  // over accrual calls keeps scratch_seg)
+    sa::Scratch scratch_mask;     // and their mask words
     uint32_t sam_stamp = 0;       // the last segment stamp written into it
     sa_launch launch = {0, 0, 1, 0, 0, 0, {0, 0}};  // tuning choices (sa_set_launch)
     int32_t n_cu = 256;           // compute units of the device
@@ -206,6 +209,8 @@ void sa_destroy(sa_ctx *ctx)
     (void)hipFree(ctx->scratch_grad.ptr);
     (void)hipFree(ctx->scratch_w.ptr);
     (void)hipFree(ctx->scratch_piece.ptr);
+    (void)hipFree(ctx->scratch_fan.ptr);
+    (void)hipFree(ctx->scratch_mask.ptr);
     delete ctx;
 }
 
@@ -543,6 +548,92 @@ void merge_segments(std::vector<sa::SegConst> &segs, const std::vector<std::arra
     segs = std::move(out);
 }
 
+// The sampled form's chunks: consecutive instants of one day, aligned to
+// kFanInstants, while the sun stays within kFanArc of the chunk's first
+// direction.  At 1-minute instants 16 span 4 degrees.  At 5, 10, 30 and 60
+// minutes (20,000 prisms, 0.4M, 0.4M, 1M and 1M points, June) arcs of 6, 12,
+// 24 and 45 degrees took 369/312/255/255, 364/278/263/229, 557/420/347/386 and
+// 384/384/316/345 us: shorter ones walk the hierarchy more often, longer ones
+// test rays against prisms that only others of the fan meet.
+constexpr double kFanArc = 30.0 * M_PI / 180.0;
+
+void fan_chunks(const std::vector<sa::SampleConst> &samples, std::vector<sa::FanChunk> &chunks,
+                std::vector<sa::FanDirs> &dirs)
+{
+    for (size_t k0 = 0; k0 < samples.size();) {
+        const sa::SampleConst &a = samples[k0];
+        size_t k1 = k0 + 1;
+        while (k1 < samples.size() && (k1 & (sa::kFanInstants - 1)) != 0 && !(samples[k1].tag & sa::kDayStart) &&
+               (double)a.dx * samples[k1].dx + (double)a.dy * samples[k1].dy + (double)a.dz * samples[k1].dz >=
+                   std::cos(kFanArc))
+            ++k1;
+        sa::FanChunk ch;
+        std::memset(&ch, 0, sizeof(ch));
+        sa::FanDirs dd;
+        // horizontal offsets per metre of rise, and their mean direction;
+        // offsets beyond 1e30 stand for a sun on the horizon
+        double lo[2] = {0, 0}, hi[2] = {0, 0}, mean[2] = {0, 0};
+        bool edges = true;
+        for (size_t k = k0; k < k1; ++k) {
+            const double d[2] = {samples[k].dx, samples[k].dy};
+            const double l = std::hypot(d[0], d[1]);
+            edges = edges && l > 1e-6;  // at the zenith: no direction to bound
+            for (int i = 0; i < 2; ++i) {
+                const double u = std::max(-1e30, std::min(1e30, d[i] / std::max((double)samples[k].dz, 1e-37)));
+                lo[i] = std::min(lo[i], u);
+                hi[i] = std::max(hi[i], u);
+                if (l > 0.0) mean[i] += d[i] / l;
+            }
+        }
+        const double lm = std::hypot(mean[0], mean[1]);
+        edges = edges && lm > 0.0;
+        // the extreme directions on either side of the mean one, if all are
+        // within 80 degrees of it
+        double right[2] = {0, 0}, left[2] = {0, 0}, amin = 10, amax = -10;
+        for (size_t k = k0; k < k1 && edges; ++k) {
+            const double d[2] = {samples[k].dx, samples[k].dy};
+            const double l = std::hypot(d[0], d[1]);
+            const double ang = std::atan2(mean[0] * d[1] - mean[1] * d[0], mean[0] * d[0] + mean[1] * d[1]);
+            edges = std::fabs(ang) < 80.0 * M_PI / 180.0;
+            for (int i = 0; i < 2; ++i) {
+                if (ang < amin) right[i] = d[i] / l;
+                if (ang > amax) left[i] = d[i] / l;
+            }
+            amin = std::min(amin, ang);
+            amax = std::max(amax, ang);
+        }
+        for (int i = 0; i < 2; ++i) {  // rounded outward
+            ch.f[2 * i] = (float)(lo[i] - std::fabs(lo[i]) * 0x1p-22);
+            ch.f[2 * i + 1] = (float)(hi[i] + std::fabs(hi[i]) * 0x1p-22);
+        }
+        if (edges) {
+            ch.f[4] = (float)-right[1];
+            ch.f[5] = (float)right[0];
+            ch.f[6] = (float)left[1];
+            ch.f[7] = (float)-left[0];
+        }
+        const sa::SampleConst &mid = samples[(k0 + k1) / 2];
+        ch.mdx = mid.dx;
+        ch.mdy = mid.dy;
+        ch.first = (int32_t)k0;
+        ch.n = (int32_t)(k1 - k0);
+        ch.bin = a.tag & sa::kBinMask;
+        ch.day_start = (a.tag & sa::kDayStart) ? 1 : 0;
+        ch.even = 1;
+        ch.weight = a.w;
+        for (int i = 0; i < sa::kFanInstants; ++i) {
+            const sa::SampleConst &s = samples[std::min(k0 + i, k1 - 1)];
+            dd.dx[i] = s.dx;
+            dd.dy[i] = s.dy;
+            dd.dz[i] = s.dz;
+            if (s.w != a.w) ch.even = 0;
+        }
+        chunks.push_back(ch);
+        dirs.push_back(dd);
+        k0 = k1;
+    }
+}
+
 sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, sa_path **out)
 {
     if (!ctx || !in || !out) return SA_ERR_INVALID_ARG;
@@ -700,6 +791,24 @@ sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, s
         }
     }
     p->d.sample_runs.start.push_back((int32_t)samples.size());
+    std::vector<sa::FanChunk> chunks;
+    std::vector<sa::FanDirs> dirs;
+    fan_chunks(samples, chunks, dirs);
+    p->d.n_chunks = (int32_t)chunks.size();
+    std::vector<char> has(n_bins, 0);
+    p->d.chunk_bins_unique = true;
+    for (size_t c = 0; c < chunks.size(); ++c) {
+        const int b = chunks[c].bin;
+        p->d.chunk_first.push_back(chunks[c].first);
+        p->d.chunk_day_start.push_back((char)chunks[c].day_start);
+        if (c > 0 && chunks[c - 1].bin == b) continue;
+        if (has[b]) p->d.chunk_bins_unique = false;
+        has[b] = 1;
+        p->d.chunk_runs.start.push_back((int32_t)c);
+        p->d.chunk_runs.bin.push_back(b);
+    }
+    p->d.chunk_runs.start.push_back((int32_t)chunks.size());
+    p->d.chunk_bins_all = p->d.chunk_bins_unique && std::count(has.begin(), has.end(), 1) == (long)n_bins;
     if (!merged) {
         p->d.seg_host = std::move(seg_host);
         p->d.sample_t.assign(in->t_min, in->t_min + in->n_samples);
@@ -725,7 +834,15 @@ sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, s
         if (e == hipSuccess)
             e = hipMemcpy(p->d.segs, segs.data(), sizeof(sa::SegConst) * segs.size(), hipMemcpyHostToDevice);
     }
-    for (sa::BinRuns *R : {&p->d.seg_runs, &p->d.sample_runs}) {
+    if (e == hipSuccess && !chunks.empty()) {
+        e = hipMalloc((void **)&p->d.chunks, sizeof(sa::FanChunk) * chunks.size());
+        if (e == hipSuccess)
+            e = hipMemcpy(p->d.chunks, chunks.data(), sizeof(sa::FanChunk) * chunks.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d.chunk_dirs, sizeof(sa::FanDirs) * dirs.size());
+        if (e == hipSuccess)
+            e = hipMemcpy(p->d.chunk_dirs, dirs.data(), sizeof(sa::FanDirs) * dirs.size(), hipMemcpyHostToDevice);
+    }
+    for (sa::BinRuns *R : {&p->d.seg_runs, &p->d.sample_runs, &p->d.chunk_runs}) {
         if (e != hipSuccess || R->start.size() < 2) continue;
         e = hipMalloc((void **)&R->dev, sizeof(int32_t) * R->start.size());
         if (e == hipSuccess)
@@ -771,8 +888,11 @@ void sa_path_destroy(sa_path *path)
     (void)hipFree(path->d.samples);
     (void)hipFree(path->d.sam_slices);
     (void)hipFree(path->d.segs);
+    (void)hipFree(path->d.chunks);
+    (void)hipFree(path->d.chunk_dirs);
     (void)hipFree(path->d.seg_runs.dev);
     (void)hipFree(path->d.sample_runs.dev);
+    (void)hipFree(path->d.chunk_runs.dev);
     delete path;
 }
 
@@ -820,6 +940,21 @@ static bool accrual_stores(const sa_accum_opts *opts, const sa_path *path)
     return opts->mode == SA_ACCRUAL && !(opts->flags & SA_FLAG_ADD) && path->d.bins_contiguous;
 }
 
+// Does a sampled call take the fans of instants?  Unless the caller asked
+// for a packet shape, or the stream is being captured: the fans' scratch may
+// be grown (a synchronisation and an allocation) and is the context's, which
+// a later larger call may free under a captured graph.
+static bool takes_fans(const sa_ctx *ctx)
+{
+    if (ctx->launch.sampled_instants_per_packet != 0) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
+}
+
 sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts, const sa_path *path,
                         const sa_accum_opts *opts, int32_t *counts, float *minutes, uint32_t *bits)
 {
@@ -839,13 +974,26 @@ sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts
     if (!counts && !minutes && !bits && !opts->longest && !opts->minutes64) return SA_OK;
     if (!set_device(ctx)) return fail(ctx, SA_ERR_DEVICE, "hipSetDevice failed");
     const float scale = opts->out_scale == 0.f ? 1.f : opts->out_scale;
+    std::string err;
+    if (opts->mode == SA_SAMPLED && takes_fans(ctx)) {
+        const bool fresh = !(opts->flags & SA_FLAG_ADD) && path->d.chunk_bins_all;
+        if (!fresh) {
+            rc = clear_outputs(ctx, opts->flags, (int64_t)path->d.n_bins * pts->n, counts, minutes, opts->longest);
+            if (rc != SA_OK) return rc;
+        }
+        bool taken = false;
+        rc = sa::launch_sampled_fan(scene->d, path->d, view(pts), scale, counts, minutes, bits, opts->longest,
+                                    opts->work, fresh, tile_launch(ctx), ctx->spill.grab, ctx->scratch_fan,
+                                    ctx->scratch_mask, taken, ctx->stream, err);
+        if (rc != SA_OK) return fail(ctx, rc, "sa_accumulate: " + err);
+        if (taken) return SA_OK;
+    }
     const bool store = accrual_stores(opts, path);
     if (!store) {
         rc = clear_outputs(ctx, opts->flags, (int64_t)path->d.n_bins * pts->n, counts, minutes, opts->longest,
                            opts->minutes64);
         if (rc != SA_OK) return rc;
     }
-    std::string err;
     if (opts->mode == SA_SAMPLED)
         rc = sa::launch_sampled(scene->d, path->d, view(pts), scale, counts, minutes, bits, opts->longest,
                                 opts->work, tile_launch(ctx), ctx->spill.grab, ctx->stream, err);

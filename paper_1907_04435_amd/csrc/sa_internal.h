@@ -93,6 +93,29 @@ struct alignas(64) SegNode {
 };
 static_assert(sizeof(SegNode) == 64, "one line");
 
+// A chunk of the sampled form: up to kFanInstants consecutive instants of one
+// day (never across a multiple of it, so within a word of the bit vectors), whose
+// rays from a point fill the fan f: the per-metre reach box of their
+// horizontal offsets (umnx, umxx, umny, umxy) and the inward normals of its
+// two edges (nax, nay, nbx, nby; zero where the directions spread too far to
+// be bounded by two edges).
+constexpr int kFanInstants = 16;
+struct alignas(64) FanChunk {
+    float f[8];
+    float mdx, mdy;     // middle direction (visit order)
+    int32_t first, n;   // its instants [first, first + n)
+    int32_t bin;
+    int32_t day_start;  // it holds its day's first instant
+    int32_t even;       // every instant weighs the same ...
+    float weight;       // ... this much (minutes)
+};
+static_assert(sizeof(FanChunk) == 64, "one line");
+
+// Their directions; entries past n repeat the last one.
+struct alignas(64) FanDirs {
+    float dx[kFanInstants], dy[kFanInstants], dz[kFanInstants];
+};
+
 struct DeviceScene {
     int32_t n_b = 0;
     int32_t n_vert = 0;
@@ -162,6 +185,14 @@ struct DevicePath {
     bool bins_contiguous = false;      // host: every bin has segments, all in one run
     BinRuns seg_runs;                  // runs of equal bins over the segments
     BinRuns sample_runs;               // and over the instants
+    int32_t n_chunks = 0;              // fans of instants of the sampled form
+    FanChunk *chunks = nullptr;        // [n_chunks]
+    FanDirs *chunk_dirs = nullptr;     // [n_chunks]
+    BinRuns chunk_runs;                // runs of equal bins over the chunks
+    bool chunk_bins_unique = false;    // host: no bin has two runs
+    bool chunk_bins_all = false;       // host: and every bin has one
+    std::vector<int32_t> chunk_first;  // host: each chunk's first instant
+    std::vector<char> chunk_day_start;  // host: whether it is its day's first
     std::vector<double> bin_span;      // host: daylight minutes of each output bin
     bool merged = false;               // host: segments merged into direction-graph edges
     // host, for the raster form: each segment's knot directions, times, its
@@ -221,6 +252,15 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
                          float scale, int32_t *counts, float *minutes, uint32_t *bits, float *longest,
                          uint64_t *work, const TileLaunch &L, uint32_t *grab, hipStream_t st,
                          std::string &err);
+// The sampled form by fans of instants, with node views and mask words in
+// views_scr and mask_scr (grown as needed, with the stream synchronised
+// first).  taken = false, with nothing enqueued, where they cannot be had:
+// launch_sampled gives the same results without scratch.  store: outputs need
+// no clearing (no SA_FLAG_ADD and p.chunk_bins_all).
+sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const PointsView &pts, float scale,
+                             int32_t *counts, float *minutes, uint32_t *bits, float *longest, uint64_t *work, bool store,
+                             const TileLaunch &L, uint32_t *grab, Scratch &views_scr, Scratch &mask_scr, bool &taken,
+                             hipStream_t st, std::string &err);
 // store: outputs need no clearing (no SA_FLAG_ADD and p.bins_contiguous):
 // each bin is stored by the launch holding its first segment.
 // L: the launch choices (segments per launch, persistent grid size).

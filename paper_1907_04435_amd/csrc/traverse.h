@@ -74,6 +74,18 @@ __device__ __forceinline__ bool first_active_lane()
     return __builtin_amdgcn_readfirstlane(lane) == lane;
 }
 
+// Sum a per-lane counter over the wave and add it to a global total.
+__device__ __forceinline__ void flush_work(const Work &w, uint64_t *work)
+{
+    uint32_t v[8] = {w.box, w.prism, w.edges, w.inserts, w.nodes, w.units, w.spills, w.leaves};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        uint64_t s = v[c];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if ((tid() & 63) == 0 && s) atomicAdd((unsigned long long *)&work[c], (unsigned long long)s);
+    }
+}
+
 // One entry of a wave's traversal stack: a deferred node and the mask of
 // the lanes that reached it.
 struct alignas(16) StackEntry {
@@ -933,8 +945,12 @@ struct SegFan {
     float pz, cxl, cxh, cyl, cyh, naP, nbP;
 
     __device__ __forceinline__ SegFan(const SegConst &g, float px, float py, float pz_)
+        : SegFan(fan_geom(g), px, py, pz_)
     {
-        const FanGeom f = fan_geom(g);
+    }
+
+    __device__ __forceinline__ SegFan(const FanGeom &f, float px, float py, float pz_)
+    {
         pz = pz_;
         cxl = round_dn_rel(fmaf(-pz, f.umnx, px));
         cxh = round_up_rel(fmaf(-pz, f.umxx, px));
@@ -1006,6 +1022,24 @@ __device__ __forceinline__ void seg_child(const FanGeom &f, float x0, float y0, 
     c[5] = box_reach(x0, y0, x1, y1, f.nax, f.nay);
     c[6] = box_reach(x0, y0, x1, y1, f.nbx, f.nby);
 }
+
+// The view of node `nd` for a fan whose middle direction is (mdx, mdy), with
+// child references r0 (left) and r1 (right) already in view form (byte
+// offsets, or leaf / absent).
+__device__ __forceinline__ SegNode make_view(const Node &nd, int r0, int r1, const FanGeom &f, float mdx, float mdy)
+{
+    const bool lfirst = seg_key(nd.lx0, nd.ly0, nd.lx1, nd.ly1, mdx, mdy) <=
+                        seg_key(nd.rx0, nd.ry0, nd.rx1, nd.ry1, mdx, mdy);
+    SegNode v;
+    const int a = lfirst ? 0 : 1;
+    seg_child(f, nd.lx0, nd.ly0, nd.lx1, nd.ly1, nd.lz1, nd.left != kNone, v.c[a]);
+    seg_child(f, nd.rx0, nd.ry0, nd.rx1, nd.ry1, nd.rz1, nd.right != kNone, v.c[1 - a]);
+    v.ref[a] = r0;
+    v.ref[1 - a] = r1;
+    return v;
+}
+
+__device__ __forceinline__ int view_ref(int r) { return r >= 0 ? r * (int)sizeof(SegNode) : r; }
 
 // Packet traversal over the per-segment views (see packet_traverse): the
 // children of a view are already in the segment's visit order, interior
