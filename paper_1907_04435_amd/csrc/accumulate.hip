@@ -560,14 +560,17 @@ __global__ void k_seg_nodes(const Node *__restrict__ nodes, int n_nodes, const S
 }
 
 // Roof-covered: inside a footprint (other than the point's own building)
-// and not above that roof -- shadowed from every direction.
+// and not above that roof -- shadowed from every direction.  Without kTops
+// the boxes' tops are not looked at (hierarchies whose heights are not those
+// of `height`: the footprints alone decide what is tested).
+template <bool kTops = true>
 __device__ __forceinline__ bool roof_covered(cNode *nodes, StackEntry *stack, cfloat4 *verts, cfloat *height,
                                              const LanePoint &q, bool valid)
 {
     if (nodes == nullptr) return false;
     uint64_t covm = 0;
     auto bt = [&](float x0, float y0, float x1, float y1, float z1) {
-        return q.px >= x0 && q.px <= x1 && q.py >= y0 && q.py <= y1 && q.pz <= z1;
+        return q.px >= x0 && q.px <= x1 && q.py >= y0 && q.py <= y1 && (!kTops || q.pz <= z1);
     };
     auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
         const bool t = lane_in(want) && prim != q.own && q.pz <= ld(height + prim) &&
@@ -983,125 +986,136 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 
 // ------------------------------------------------------------------ batched
 // Variant v of the scene differs from the base only in the heights of a few
-// buildings.  Each variant gets its own copy of the node array and heights;
-// only the ancestors of the changed leaves need new box tops, which one
-// thread per variant walks up sequentially (no races between its walks).
+// buildings, so its hierarchy differs only in the box tops of those leaves'
+// ancestors ("changed nodes").  Every variant shares the base's views
+// everywhere else and has its own copies of the views of its changed nodes,
+// whose child references point to the variant's copy where the child changed
+// too and to the base view otherwise.  Every ancestor of a changed node is
+// changed, so a walk started at the variant's copy of the root sees exactly
+// the variant's hierarchy.  Copies of variant v live at view index
+// n_nodes + v * cmax + c.
 
-__global__ void k_var_copy(const int4 *__restrict__ base_nodes, int64_t node_words, const float *__restrict__ base_h,
-                           int n_b, int V, int4 *__restrict__ vnodes, float *__restrict__ vh)
+// Heights of the variants (the base's), their changed-node maps (none) and
+// the tile offsets: tile_off[v] = first tile of variant v, 64 points per tile.
+__global__ void k_var_copy(const float *__restrict__ base_h, int n_b, int n_nodes, int V, float *__restrict__ vh,
+                           int32_t *__restrict__ vmap, const int64_t *__restrict__ var_off, int64_t *__restrict__ tile_off)
 {
     const int64_t stride = (int64_t)n_wg() * wg_size();
-    for (int64_t t = (int64_t)wg_id() * wg_size() + tid(); t < (int64_t)V * node_words; t += stride)
-        vnodes[t] = base_nodes[t % node_words];
-    for (int64_t t = (int64_t)wg_id() * wg_size() + tid(); t < (int64_t)V * n_b; t += stride)
-        vh[t] = base_h[t % n_b];
-}
-
-__global__ void k_var_heights(int V, int k, const int32_t *__restrict__ ids, const float *__restrict__ h,
-                              const int32_t *__restrict__ rank, int n_b, float *__restrict__ vh, uint32_t *flag)
-{
-    const int t = wg_id() * wg_size() + tid();
-    if (t >= V * k) return;
-    const int id = ids[t];
-    const float hv = h[t];
-    if (id < 0 || id >= n_b || !(hv > 0.f)) {
-        atomicOr(flag, 4u);
-        return;
-    }
-    vh[(int64_t)(t / k) * n_b + rank[id]] = hv;
-}
-
-__global__ void k_var_refit(int V, int k, const int32_t *__restrict__ ids, const int32_t *__restrict__ rank,
-                            const int32_t *__restrict__ parent, int n_int, int n_b, int n_nodes,
-                            const float *__restrict__ vh, Node *vnodes)
-{
-    const int v = wg_id() * wg_size() + tid();
-    if (v >= V) return;
-    Node *nodes = vnodes + (int64_t)v * n_nodes;
-    for (int j = 0; j < k; ++j) {
-        const int id = ids[v * k + j];
-        if (id < 0 || id >= n_b) continue;
-        const int prim = rank[id];
-        float z = pad_hi(vh[(int64_t)v * n_b + prim]);
-        int pp = parent[n_int + prim];
-        for (int guard = 0; pp >= 0 && guard < 64; ++guard) {
-            Node &nd = nodes[pp >> 1];
-            if (pp & 1) nd.rz1 = z;
-            else nd.lz1 = z;
-            z = fmaxf(nd.lz1, nd.rz1);
-            pp = parent[pp >> 1];
+    const int64_t t0 = (int64_t)wg_id() * wg_size() + tid();
+    for (int64_t t = t0; t < (int64_t)V * n_b; t += stride) vh[t] = base_h[t % n_b];
+    for (int64_t t = t0; t < (int64_t)V * n_nodes; t += stride) vmap[t] = -1;
+    if (t0 < 64) {  // one wave, 64 variants at a time
+        int64_t base = 0;
+        for (int v0 = 0; v0 < V; v0 += 64) {
+            const int v = v0 + (int)t0;
+            int64_t sum = v < V ? (var_off[v + 1] - var_off[v] + 63) / 64 : 0;
+            const int64_t own = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int64_t up = __shfl_up(sum, o, 64);
+                sum += (int)t0 >= o ? up : 0;
+            }
+            if (v < V) tile_off[v] = base + sum - own;
+            base += __shfl(sum, 63, 64);
         }
+        if (t0 == 0) tile_off[V] = base;
     }
 }
 
-// Per-segment views of the variants.  A variant differs from the base only
-// in the boxes of the ancestors of its changed leaves, so it shares the
-// base views everywhere else: each variant gets its own copies of the
-// views of those ancestors ("changed nodes"), whose child references point
-// to the variant's copy where the child changed too and to the base view
-// otherwise.  Every ancestor of a changed node is changed, so a walk
-// started at the variant's copy of the root sees exactly the variant's
-// hierarchy.  Copies of variant v live at view index n_nodes + v * cmax + c.
+// One variant's chain walks, a lane per changed building (further ones in
+// turn): where the chain stands and the top it carries.
+struct VarChain {
+    int32_t link;   // parent link of the node below: node * 2 + side
+    int32_t depth;  // ancestors of the leaf
+    float z;        // its subtree's top
+    int32_t pad;
+};
 
-// vlist[v][0, vcount[v]): the changed interior nodes of variant v (one
-// thread per variant; a chain walk stops at the first node already listed,
-// whose ancestors are listed too); vroot[v]: byte offset of the root's view.
-__global__ void k_var_list(int V, int k, const int32_t *__restrict__ ids, const int32_t *__restrict__ rank,
-                           const int32_t *__restrict__ parent, int n_int, int n_b, int n_nodes, int cmax,
-                           int32_t *__restrict__ vlist, int32_t *__restrict__ vcount, int32_t *__restrict__ vroot)
+// One wave per variant: heights (bad ones skipped and flagged), the list of
+// changed nodes vlist[v][0, vcount[v]) with their place in it (vmap[v][node])
+// and their refitted child tops vz, and the view the walk starts at
+// (vroot[v], a byte offset).  The chains climb together, a level of the tree
+// at a time: all of a level's tops are written before any is read.  With one
+// thread per variant and a search of the list per node, lists, references,
+// refit and a copy of all nodes per variant took 0.95 ms for 32 variants of 8
+// buildings on 20,000 prisms; this and k_var_copy take 0.05 ms.
+__global__ __launch_bounds__(64) void k_var_setup(int k, const int32_t *__restrict__ ids, const float *__restrict__ h,
+                                                  const int32_t *__restrict__ rank, const int32_t *__restrict__ parent,
+                                                  int n_int, int n_b, int n_nodes, int cmax,
+                                                  const Node *__restrict__ nodes, float *vh, int32_t *vmap, int32_t *vlist,
+                                                  float2 *vz, VarChain *chains, int32_t *__restrict__ vcount,
+                                                  int32_t *__restrict__ vroot, uint32_t *flag)
 {
-    const int v = wg_id() * wg_size() + tid();
-    if (v >= V) return;
-    int32_t *L = vlist + (int64_t)v * cmax;
-    int c = 0;
-    for (int j = 0; j < k; ++j) {
-        const int id = ids[v * k + j];
-        if (id < 0 || id >= n_b) continue;
-        int pp = parent[n_int + rank[id]];
-        for (int guard = 0; pp >= 0 && guard < 64 && c < cmax; ++guard) {
-            const int a = pp >> 1;
-            bool seen = false;
-            for (int q = 0; q < c; ++q) seen = seen || L[q] == a;
-            if (seen) break;
-            L[c++] = a;
-            pp = parent[a];
+    __shared__ int s_count, s_depth;
+    const int v = wg_id();
+    const int lane = tid();
+    float *H = vh + (int64_t)v * n_b;
+    int32_t *map = vmap + (int64_t)v * n_nodes, *L = vlist + (int64_t)v * cmax;
+    float2 *Z = vz + (int64_t)v * cmax;
+    VarChain *C = chains + (int64_t)v * k;
+    if (lane == 0) s_count = s_depth = 0;
+    for (int j = lane; j < k; j += 64) {
+        const int id = ids[(int64_t)v * k + j];
+        const float hv = h[(int64_t)v * k + j];
+        if (id < 0 || id >= n_b || !(hv > 0.f)) atomicOr(flag, 4u);
+        else H[rank[id]] = hv;
+    }
+    __syncthreads();
+    for (int j = lane; j < k; j += 64) {
+        const int id = ids[(int64_t)v * k + j];
+        VarChain c{-1, 0, 0.f, 0};
+        if (id >= 0 && id < n_b) {
+            const int prim = rank[id];
+            c.link = parent[n_int + prim];
+            c.z = pad_hi(H[prim]);
+            bool listing = true;  // until a node that another chain has listed, with its ancestors
+            for (int pp = c.link; pp >= 0 && c.depth < 64; ++c.depth) {
+                const int a = pp >> 1;
+                if (listing) {
+                    listing = atomicCAS(&map[a], -1, -2) == -1;
+                    if (listing) {
+                        const int at = atomicAdd(&s_count, 1);
+                        L[at] = a;
+                        Z[at] = make_float2(nodes[a].lz1, nodes[a].rz1);
+                        map[a] = at;
+                    }
+                }
+                pp = parent[a];
+            }
         }
+        C[j] = c;
+        atomicMax(&s_depth, c.depth);
     }
-    vcount[v] = c;
-    int root = 0;
-    for (int q = 0; q < c; ++q)
-        if (L[q] == 0) root = (n_nodes + v * cmax + q) * (int)sizeof(SegNode);
-    vroot[v] = root;
-}
-
-// Child references of the copies, in view form: one thread per (variant,
-// copy).
-__global__ void k_var_refs(int V, int cmax, int n_nodes, const Node *__restrict__ nodes,
-                           const int32_t *__restrict__ vlist, const int32_t *__restrict__ vcount, int2 *__restrict__ vref)
-{
-    const int64_t t = (int64_t)wg_id() * wg_size() + tid();
-    if (t >= (int64_t)V * cmax) return;
-    const int v = (int)(t / cmax), c = (int)(t - (int64_t)v * cmax);
-    const int n = vcount[v];
-    if (c >= n) return;
-    const int32_t *L = vlist + (int64_t)v * cmax;
-    const Node nd = nodes[L[c]];
-    int r[2] = {nd.left, nd.right};
-    for (int s = 0; s < 2; ++s) {
-        if (r[s] < 0) continue;  // a leaf or absent
-        int at = -1;
-        for (int q = 0; q < n; ++q) at = L[q] == r[s] ? q : at;
-        r[s] = (at >= 0 ? n_nodes + v * cmax + at : r[s]) * (int)sizeof(SegNode);
+    __syncthreads();
+    for (int level = s_depth - 1; level >= 0; --level) {
+        for (int j = lane; j < k; j += 64) {
+            const VarChain c = C[j];
+            if (c.depth <= level) continue;
+            float *z = (float *)(Z + map[c.link >> 1]);
+            z[c.link & 1] = c.z;
+        }
+        __syncthreads();
+        for (int j = lane; j < k; j += 64) {
+            VarChain c = C[j];
+            if (c.depth <= level) continue;
+            const float2 z = Z[map[c.link >> 1]];
+            c.z = fmaxf(z.x, z.y);
+            c.link = parent[c.link >> 1];
+            C[j] = c;
+        }
+        __syncthreads();
     }
-    vref[t] = make_int2(r[0], r[1]);
+    if (lane == 0) {
+        vcount[v] = s_count;
+        vroot[v] = s_count > 0 ? (n_nodes + v * cmax + map[0]) * (int)sizeof(SegNode) : 0;
+    }
 }
 
 // The copies' views for segments [j0, j1), from the variants' refitted
-// boxes: one thread per (segment, variant, copy).
-__global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__ vnodes,
+// tops: one thread per (segment, variant, copy).
+__global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__ nodes,
                           const int32_t *__restrict__ vlist, const int32_t *__restrict__ vcount,
-                          const int2 *__restrict__ vref, const SegConst *__restrict__ segs, int j0, int j1,
-                          int64_t stride, SegNode *__restrict__ out)
+                          const int32_t *__restrict__ vmap, const float2 *__restrict__ vz,
+                          const SegConst *__restrict__ segs, int j0, int j1, int64_t stride, SegNode *__restrict__ out)
 {
     const int64_t t = (int64_t)wg_id() * wg_size() + tid();
     const int64_t per = (int64_t)V * cmax;
@@ -1110,22 +1124,16 @@ __global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__
     const int64_t vc = t - jj * per;
     const int v = (int)(vc / cmax), c = (int)(vc - (int64_t)v * cmax);
     if (c >= vcount[v]) return;
-    const Node nd = vnodes[(int64_t)v * n_nodes + vlist[vc]];
-    const int2 r = vref[vc];
+    Node nd = nodes[vlist[vc]];
+    nd.lz1 = vz[vc].x;
+    nd.rz1 = vz[vc].y;
+    auto ref = [&](int r) {
+        if (r < 0) return r;  // a leaf or absent
+        const int at = vmap[(int64_t)v * n_nodes + r];
+        return (at >= 0 ? n_nodes + v * cmax + at : r) * (int)sizeof(SegNode);
+    };
     const SegConst &g = segs[j0 + jj];
-    out[jj * stride + n_nodes + vc] = make_view(nd, r.x, r.y, fan_geom(g), g.mdx, g.mdy);
-}
-
-// tile_off[v] = first tile of variant v, 64 points per tile
-__global__ void k_var_tiles(int V, const int64_t *__restrict__ var_off, int64_t *__restrict__ tile_off)
-{
-    if (wg_id() != 0 || tid() != 0) return;
-    int64_t t = 0;
-    for (int v = 0; v < V; ++v) {
-        tile_off[v] = t;
-        t += (var_off[v + 1] - var_off[v] + 63) / 64;
-    }
-    tile_off[V] = t;
+    out[jj * stride + n_nodes + vc] = make_view(nd, ref(nd.left), ref(nd.right), fan_geom(g), g.mdx, g.mdy);
 }
 
 // Persistent accrual over the (variant, tile) queue.  A wave takes the next
@@ -1135,7 +1143,7 @@ __global__ void k_var_tiles(int V, const int64_t *__restrict__ var_off, int64_t 
 // walking its window left to right with halving / doubling sub-windows.
 // Seven waves per SIMD: 72 VGPRs with a few spilled to scratch, measured
 // faster (64.5 ms on 256 variants) than six waves (77 ms) or eight (75 ms).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(const Node *vnodes_g, int n_nodes, const SegNode *views_g,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(const Node *nodes_g, const SegNode *views_g,
                                                       int64_t stride, const int32_t *voff_g,
                                                       const int32_t *__restrict__ vroot, const float4 *verts_g,
                                                       const float *vh_g, int n_b, const SegConst *segs_g, int j0,
@@ -1172,12 +1180,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
             else hi = mid - 1;
         }
         const int v = uniform(lo);
-        cNode *nodes = (cNode *)(vnodes_g + (int64_t)v * n_nodes);
         cfloat *height = (cfloat *)(vh_g + (int64_t)v * n_b);
         const int64_t i = var_off[v] + (t - tile_off[v]) * 64 + lane;
         const bool valid = i < var_off[v + 1];
         const LanePoint q = load_point(lds_uniform<PointArgs>((lds_int *)s_P), i, valid);
-        const bool covered = roof_covered(nodes, stack, verts, height, q, valid);
+        const bool covered = roof_covered<false>((cNode *)nodes_g, stack, verts, height, q, valid);
         const int root = vroot ? vroot[v] : 0;
         int cnt = 0;
         double mins = 0.0;
@@ -1349,15 +1356,22 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
         return SA_ERR_CAPACITY;
     }
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t node_bytes = up(sizeof(Node) * (size_t)n_var * n_nodes);
-    const size_t h_bytes = up(sizeof(float) * (size_t)n_var * s.n_b);
-    const size_t tile_bytes = up(sizeof(int64_t) * (n_var + 1));
-    const size_t list_bytes = up(sizeof(int32_t) * (size_t)n_var * cmax);
-    const size_t ref_bytes = up(sizeof(int2) * (size_t)n_var * cmax);
-    const size_t cnt_bytes = up(sizeof(int32_t) * (size_t)n_var);
-    const size_t off1 = node_bytes, off2 = off1 + h_bytes, off3 = off2 + tile_bytes, off4 = off3 + list_bytes;
-    const size_t off5 = off4 + ref_bytes, off6 = off5 + cnt_bytes, off7 = off6 + cnt_bytes;
-    const size_t need = off7 + 256;
+    size_t need = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = need;
+        need += up(bytes);
+        return at;
+    };
+    const size_t copies = (size_t)n_var * cmax;
+    const size_t h_at = part(sizeof(float) * (size_t)n_var * s.n_b);
+    const size_t map_at = part(sizeof(int32_t) * (size_t)n_var * n_nodes);
+    const size_t tile_at = part(sizeof(int64_t) * (n_var + 1));
+    const size_t list_at = part(sizeof(int32_t) * copies);
+    const size_t z_at = part(sizeof(float2) * copies);
+    const size_t chain_at = part(sizeof(VarChain) * (size_t)n_var * k);
+    const size_t cnt_at = part(sizeof(int32_t) * (size_t)n_var);
+    const size_t root_at = part(sizeof(int32_t) * (size_t)n_var);
+    const size_t counter_at = part(256);
     if (scr.bytes < need) {
         (void)hipStreamSynchronize(st);
         (void)hipFree(scr.ptr);
@@ -1372,33 +1386,21 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
         scr.bytes = need;
     }
     char *base = (char *)scr.ptr;
-    Node *vnodes = (Node *)base;
-    float *vh = (float *)(base + off1);
-    int64_t *tile_off = (int64_t *)(base + off2);
-    int32_t *vlist = (int32_t *)(base + off3);
-    int2 *vref = (int2 *)(base + off4);
-    int32_t *vcount = (int32_t *)(base + off5);
-    int32_t *vroot = (int32_t *)(base + off6);
-    uint32_t *counter = (uint32_t *)(base + off7);
+    float *vh = (float *)(base + h_at);
+    int32_t *vmap = (int32_t *)(base + map_at);
+    int64_t *tile_off = (int64_t *)(base + tile_at);
+    int32_t *vlist = (int32_t *)(base + list_at);
+    float2 *vz = (float2 *)(base + z_at);
+    int32_t *vcount = (int32_t *)(base + cnt_at);
+    int32_t *vroot = (int32_t *)(base + root_at);
+    uint32_t *counter = (uint32_t *)(base + counter_at);
     const int n_int = s.n_b == 1 ? 1 : s.n_b - 1;
-    if (s.n_b > 0) {
-        hipLaunchKernelGGL(k_var_copy, dim3(2048), dim3(256), 0, st, (const int4 *)s.nodes, (int64_t)n_nodes * 4,
-                           (const float *)s.height, s.n_b, n_var, (int4 *)vnodes, vh);
-        if (k > 0) {
-            hipLaunchKernelGGL(k_var_heights, dim3((n_var * k + 255) / 256), dim3(256), 0, st, n_var, k, ids, h,
-                               (const int32_t *)s.rank, s.n_b, vh, flag);
-            hipLaunchKernelGGL(k_var_refit, dim3((n_var + 63) / 64), dim3(64), 0, st, n_var, k, ids,
-                               (const int32_t *)s.rank, (const int32_t *)s.parent, n_int, s.n_b, n_nodes,
-                               (const float *)vh, vnodes);
-        }
-        hipLaunchKernelGGL(k_var_list, dim3((n_var + 63) / 64), dim3(64), 0, st, n_var, k, ids,
-                           (const int32_t *)s.rank, (const int32_t *)s.parent, n_int, s.n_b, n_nodes, cmax, vlist,
-                           vcount, vroot);
-        const int64_t nr = (int64_t)n_var * cmax;
-        hipLaunchKernelGGL(k_var_refs, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st, n_var, cmax, n_nodes,
-                           (const Node *)s.nodes, (const int32_t *)vlist, (const int32_t *)vcount, vref);
-    }
-    hipLaunchKernelGGL(k_var_tiles, dim3(1), dim3(1), 0, st, n_var, var_off, tile_off);
+    hipLaunchKernelGGL(k_var_copy, dim3(1024), dim3(256), 0, st, (const float *)s.height, s.n_b, n_nodes, n_var, vh, vmap,
+                       var_off, tile_off);
+    if (s.n_b > 0)
+        hipLaunchKernelGGL(k_var_setup, dim3(n_var), dim3(64), 0, st, k, ids, h, (const int32_t *)s.rank,
+                           (const int32_t *)s.parent, n_int, s.n_b, n_nodes, cmax, (const Node *)s.nodes, vh, vmap, vlist,
+                           vz, (VarChain *)(base + chain_at), vcount, vroot, flag);
     SA_CHECK_LAUNCH("variant set-up");
     const PointArgs P = point_args(pts, s);
     const int blocks = grid_blocks > 0 ? grid_blocks : 2048;
@@ -1413,13 +1415,13 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
             if (rc != SA_OK) return rc;
             const int64_t nt = (int64_t)(j1 - j0) * n_var * cmax;
             hipLaunchKernelGGL(k_seg_var, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, n_var, cmax, n_nodes,
-                               (const Node *)vnodes, (const int32_t *)vlist, (const int32_t *)vcount,
-                               (const int2 *)vref, p.segs, (int)j0, j1, stride, views);
+                               (const Node *)s.nodes, (const int32_t *)vlist, (const int32_t *)vcount,
+                               (const int32_t *)vmap, (const float2 *)vz, p.segs, (int)j0, j1, stride, views);
             SA_CHECK_LAUNCH("variant segment views");
         }
         sa_status rc = fill_u32(counter, 2, 0u, st, err);
         if (rc != SA_OK) return rc;
-        hipLaunchKernelGGL(k_batched, dim3(blocks), dim3(kThreads), 0, st, s.n_b > 0 ? vnodes : nullptr, n_nodes,
+        hipLaunchKernelGGL(k_batched, dim3(blocks), dim3(kThreads), 0, st, s.n_b > 0 ? (const Node *)s.nodes : nullptr,
                            views, stride, s.voff, s.n_b > 0 ? (const int32_t *)vroot : nullptr, s.verts,
                            (const float *)vh, s.n_b, p.segs, (int)j0, j1, P, var_off, (const int64_t *)tile_off,
                            n_var, counter, grab, scale, counts, minutes, flag);
