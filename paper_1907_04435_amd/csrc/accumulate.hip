@@ -470,6 +470,7 @@ __device__ __forceinline__ void measure(const Union4 &U, const SegConst &g, floa
     if (!last_window) kmax = min(kmax, (int)ceilf((w1 * scale - g.s0) * inv_step) - 1);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+        if (!ballot(r < U.n)) break;  // no lane's set is this large
         if (r < U.n) {
             m += U.hi[r] - U.lo[r];
             const int klo = max((int)ceilf((U.lo[r] * scale - g.s0) * inv_step), 0);
@@ -509,7 +510,7 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
     if (q.own >= 0) {
         float a, b;
         if (backface_interval(q.nx, q.ny, g, w0, w1, W0u, W0v, W1u, W1v, a, b)) {
-            union_insert(U, a, b);
+            union_first(U, a, b);
             live = !(a <= w0 && b >= w1);
         }
     }
@@ -519,26 +520,20 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
     auto leaf_m = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
         const uint64_t gm = want & ballot(prim != q.own);
         if (!gm) return 0;
-        const bool go = lane_in(gm);
         if constexpr (kCount) {
-            wk.prism += go ? 1u : 0u;
-            wk.edges += go ? (uint32_t)m : 0u;
+            wk.prism += lane_in(gm) ? 1u : 0u;
+            wk.edges += lane_in(gm) ? (uint32_t)m : 0u;
             wk.leaves += first_active_lane() ? 1u : 0u;
         }
-        float a = 0.f, b = 0.f;
-        float da, db;
-        const int r = go ? prism_interval<false>(verts, voff, m, ld(height + prim), q.px, q.py, q.pz, g, w0, w1, W0u,
-                                                 W0v, W1u, W1v, a, b, da, db)
-                         : 0;
-        if constexpr (kCount) wk.inserts += r ? 1u : 0u;
-        bool over = false, full = false;
-        if (r) {
-            over = !union_insert(U, a, b);
-            full = !over && U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1;  // the whole window is in shadow
-        }
-        const uint64_t om = ballot(over);
-        ovm |= om;
-        return om | ballot(full);
+        float a, b, da, db;
+        const uint64_t hit = prism_interval<false>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g, w0, w1,
+                                                   W0u, W0v, W1u, W1v, a, b, da, db);
+        if constexpr (kCount) wk.inserts += lane_in(hit) ? 1u : 0u;
+        if (!hit) return 0;
+        const uint64_t over = union_insert_mask(U, a, b, hit);
+        ovm |= over;
+        // the whole window is in shadow
+        return over | (hit & ballot(U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1));
     };
     const SegFan ft(g, q.px, q.py, q.pz);
     packet_traverse_seg<kCount>(src.nodes, src.voff, stack, ballot(live), ft, leaf_m, wk, src.root);
@@ -966,14 +961,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
             auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
                 const uint64_t gm = want & ballot(prim != q.own);
                 if (!gm) return 0;
-                const bool go = lane_in(gm);
-                float a = 0.f, b = 0.f, da, db;
-                const int r = go ? prism_interval<false>(verts, voff, m, ld(height + prim), q.px, q.py, q.pz, g, 0.f,
-                                                         g.theta, 1.f, 0.f, g.cth, g.sth, a, b, da, db)
-                                 : 0;
+                float a, b, da, db;
+                const uint64_t hit = prism_interval<false>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g,
+                                                           0.f, g.theta, 1.f, 0.f, g.cth, g.sth, a, b, da, db);
+                if (!hit) return 0;
                 // the wave's total for this building (every lane is active
                 // here: the traversal runs on the whole wave)
-                const float v = wave_sum(r ? (b - a) * g.wrate * wt : 0.f);
+                const float v = wave_sum(lane_in(hit) ? (b - a) * g.wrate * wt : 0.f);
                 if (first_active_lane() && v != 0.f) atomicAdd(&row[order[prim]], (double)v);
                 return 0;  // no lane retires: every building counts
             };

@@ -51,7 +51,7 @@ __device__ __forceinline__ void grad_segment(cSegNode *snodes, cint *voff, Stack
     if (q.own >= 0) {
         float a, b;
         if (backface_interval(q.nx, q.ny, g, w0, w1, W0u, W0v, W1u, W1v, a, b)) {
-            union_insert(U, a, b, -1, -1, 0.f, 0.f);
+            union_first(U, a, b, -1, -1, 0.f, 0.f);
             live = !(a <= w0 && b >= w1);
         }
     }
@@ -60,20 +60,14 @@ __device__ __forceinline__ void grad_segment(cSegNode *snodes, cint *voff, Stack
     auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
         const uint64_t gm = want & ballot(prim != q.own);
         if (!gm) return 0;
-        const bool go = lane_in(gm);
-        float a = 0.f, b = 0.f, da = 0.f, db = 0.f;
-        const int r = go ? prism_interval<true>(verts, voff, m, ld(height + prim), q.px, q.py, q.pz, g, w0, w1,
-                                                W0u, W0v, W1u, W1v, a, b, da, db)
-                         : 0;
-        bool over = false, full = false;
-        if (r) {
-            over = !union_insert(U, a, b, prim, prim, da, db);
-            // the whole window is shadowed: no boundary inside it
-            full = !over && U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1;
-        }
-        const uint64_t om = ballot(over);
-        ovm |= om;
-        return om | ballot(full);
+        float a, b, da, db;
+        const uint64_t hit = prism_interval<true>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g, w0, w1,
+                                                  W0u, W0v, W1u, W1v, a, b, da, db);
+        if (!hit) return 0;
+        const uint64_t over = union_insert_mask(U, a, b, prim, da, db, hit);
+        ovm |= over;
+        // the whole window is shadowed: no boundary inside it
+        return over | (hit & ballot(U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1));
     };
     const SegFan ft(g, q.px, q.py, q.pz);
     Work none{0, 0, 0, 0, 0, 0, 0};
@@ -109,6 +103,7 @@ __device__ __forceinline__ void scatter_grad(const UnionG &U, bool ok, float wsc
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const bool in = ok && r < U.n;
+        if (!ballot(in)) break;  // no lane's set is this large
         wave_scatter(in && U.plo[r] >= 0 && U.dlo[r] != 0.f ? U.plo[r] : -1, -(double)(wscale * U.dlo[r]), G);
         wave_scatter(in && U.phi[r] >= 0 && U.dhi[r] != 0.f ? U.phi[r] : -1, (double)(wscale * U.dhi[r]), G);
     }
