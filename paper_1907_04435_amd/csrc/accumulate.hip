@@ -488,7 +488,7 @@ __device__ __forceinline__ void measure(const Union4 &U, const SegConst &g, floa
 // back-face term, then the packet fan traversal.  On return `ov` marks
 // lanes whose set needed more than four pieces.
 // The hierarchy as seen from the current segment: its per-segment node
-// views (SegFan: seven compares per child), the vertex offsets of the
+// views (SegFan: six compares per child), the vertex offsets of the
 // leaves, and the view the walk starts at.
 struct SegSrc {
     cSegNode *nodes;

@@ -83,14 +83,16 @@ struct alignas(64) SegConst {
 static_assert(sizeof(SegConst) == 128, "two lines");
 
 // A hierarchy node seen from one accrual segment: for each child, the box
-// terms of the fan test against that segment (z1; the box edges shifted by
+// terms of the fan test against that segment (the box edges shifted by
 // the fan's per-metre reach: x1 - z1 umnx, x0 - z1 umxx, y1 - z1 umny,
 // y0 - z1 umxy; the two wedge projections), children in the segment's
 // visit order.  64 bytes, one scalar load.
 struct alignas(64) SegNode {
-    float c[2][7];
-    int32_t ref[2];  // interior: byte offset of the child's view; leaf: ~prism; or absent
+    float c[2][6];
+    int32_t ref[2];   // interior: byte offset of the child's view; leaf: ~prism; or absent
+    uint32_t vert[2];  // a leaf's first vertex and, above kLeafVertBits, its vertex count (0: see its offsets)
 };
+constexpr int kLeafVertBits = 27;
 static_assert(sizeof(SegNode) == 64, "one line");
 
 // A chunk of the sampled form: up to kFanInstants consecutive instants of one

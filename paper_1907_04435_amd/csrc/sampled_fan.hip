@@ -4,7 +4,7 @@
 // Between neighbouring instants the sun hardly moves, so a point's rays
 // toward a chunk of instants fill a narrow fan, and the prisms they can meet
 // are those the fan meets.  A wave takes 64 points and one chunk, walks the
-// chunk's node views (the accrual form's traversal: seven compares per child
+// chunk's node views (the accrual form's traversal: six compares per child
 // box, against a fan that holds every ray of the chunk), and at a leaf tests
 // the prism against the chunk's rays one by one, with the arithmetic of
 // ray_prism.  A ray is shadowed if any prism blocks it, whatever the order of
