@@ -615,7 +615,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
     int kx = 0;
     Unit un;
     while (next_unit((lds_int *)s_W, j0, j1, kx, un)) {
-        const int ja = uniform(un.a), jb = uniform(un.b);
+        const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         const PointArgs Pd = lds_uniform<PointArgs>((lds_int *)s_P);
         const int64_t n = Pd.n;
         const int64_t i = (int64_t)un.tile * 64 + lane;
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
         int bin = jb > ja ? ld(segs + ja).bin : 0;
         const BinOut O0 = lds_uniform<BinOut>((lds_int *)s_O);
         bool fresh = (ja == j0 ? O0.fresh_first : O0.fresh_rest) != 0;
-        for (int j = ja; j < jb; ++j) {
+        for (int j = ja; j < jb; j += step) {
             const SegConst g = ld(segs + j);
             if (g.bin != bin) {
                 const BinOut Ob = lds_uniform<BinOut>((lds_int *)s_O);
@@ -926,7 +926,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         // over the bin's segments and added once per bin, with one atomic
         // for the wave when all its contributing lanes share the building
         // (facade points come wall by wall, so they nearly always do).
-        const int ja = uniform(un.a), jb = uniform(un.b);
+        const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         double bf = 0.0;
         int bin = jb > ja ? ld(segs + ja).bin : 0;
         auto flush_backface = [&]() {
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
             }
             bf = 0.0;
         };
-        for (int j = ja; j < jb; ++j) {
+        for (int j = ja; j < jb; j += step) {
             const SegConst g = ld(segs + j);
             if (g.bin != bin) {
                 flush_backface();
@@ -1296,7 +1296,8 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
     }
     res = resident_blocks(kern, L);
     W = plan_units(p.sample_runs, 0, p.n_samples, tiles, split, res, grab);
-    sa_status rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
+    sa_status rc = SA_OK;
+            if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
     if (rc != SA_OK) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, s.verts,
                        s.height, p.samples, p.n_samples, W, point_args(pts, s),
@@ -1518,7 +1519,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             if (rc != SA_OK) return rc;
             const int64_t res = resident_blocks(k_accrual_runs, L);
             const Sched W = plan_units(p.seg_runs, j0, j1, tiles, Split::kUniqueBins, res, q.grab);
-            rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
+            if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
             if (rc != SA_OK) return rc;
             hipLaunchKernelGGL(k_accrual_runs, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
                                st, nodes, views, s.n_nodes, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
@@ -1578,7 +1579,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             O.pcnt = (int32_t *)piece_scr.ptr;
             O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
-        rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
+        if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
         if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, views, s.n_nodes,
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
@@ -1615,7 +1616,7 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
         const int64_t res = resident_blocks(k_contrib, L);
         const Split split = tiles < 2 * res * kWaves ? Split::kChunks : Split::kBinRuns;
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, split, res, grab);
-        rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
+        if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
         if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(k_contrib, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, views,
                            s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, weight,

@@ -130,11 +130,13 @@ __device__ __forceinline__ bool roof_covered_g(cNode *nodes, StackEntry *stack, 
     return lane_in(covm);
 }
 
-// Seven waves per SIMD (72 VGPRs): 2 % faster than the six of the natural
-// allocation.  Persistent: its units are (tile, chunk of segments), enough
-// of them to keep every wave busy on small point sets (the gradient sums
-// are atomic, so any split adds up the same).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_grad(
+// Six waves per SIMD: at seven (72 VGPRs) the interval sets with their owners
+// spill 87 registers, at five there are too few waves (forward and adjoint on
+// 200k points, 1-minute knots: 10.77, 10.15 and 10.69 ms at 7, 6 and 5).
+// Persistent: its units are (tile, every n-th segment), enough of them to
+// keep every wave busy on small point sets (the gradient sums are atomic, so
+// any split adds up the same).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_grad(
     const Node *nodes_g, const SegNode *snodes_g, int n_nodes, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, GradArgs G, SpillArgs S)
 {
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     int kx = 0;
     Unit un;
     while (next_unit((lds_int *)s_W, j0, j1, kx, un)) {
-        const int ja = uniform(un.a), jb = uniform(un.b);
+        const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         const PointArgs Pd = lds_uniform<PointArgs>((lds_int *)s_P);
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < Pd.n;
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const bool covered = roof_covered_g(nodes, stack, verts, height, q, valid);
         int bin = -1;
         float w = 0.f;
-        for (int j = ja; j < jb; ++j) {
+        for (int j = ja; j < jb; j += step) {
             const SegConst g = ld(segs + j);
             if (g.bin != bin) {
                 bin = g.bin;
@@ -278,7 +280,7 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
         hipLaunchKernelGGL(k_zero1, dim3(1), dim3(1), 0, st, q.counters);
         SpillArgs S{q.entries[0], q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
-        rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
+        if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
         if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, s.nodes, views,
                            s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);

@@ -208,14 +208,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     int kx = 0;
     Unit un;
     while (next_unit((lds_int *)s_W, c0, c1, kx, un)) {
-        const int ca = uniform(un.a), cb = uniform(un.b);
+        const int ca = uniform(un.a), cb = uniform(un.b), step = uniform(un.step);
         const PointArgs Pd = lds_uniform<PointArgs>((lds_int *)s_P);
         const int64_t n = Pd.n;
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < n;
         const LanePoint q = load_point(Pd, i, valid);
         const bool facades = ballot(q.own >= 0) != 0;
-        for (int c = ca; c < cb; ++c) {
+        for (int c = ca; c < cb; c += step) {
             const FanChunk ch = ld(chunks + c);
             cDirs *dd = (cDirs *)(dirs_g + c);
             const uint32_t all = (1u << ch.n) - 1u;
@@ -442,7 +442,8 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
             const PointArgs P{n, pts.x + i0, pts.y + i0, pts.z + i0, pts.nx ? pts.nx + i0 : nullptr,
                               pts.ny ? pts.ny + i0 : nullptr, pts.owner ? pts.owner + i0 : nullptr, s.rank, s.n_b};
             const Sched W = plan_units(p.chunk_runs, c0, c1, (n + 63) / 64, Split::kChunks, res, grab);
-            sa_status rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
+            sa_status rc = SA_OK;
+            if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
             if (rc != SA_OK) return rc;
             hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, (const SegNode *)views,
                                s.n_nodes, s.voff, s.verts, s.height, (const FanChunk *)p.chunks,

@@ -1,15 +1,21 @@
 // Persistent launches of the per-tile kernels (accrual, sampled,
 // continuous shadow, contributions, adjoint).
 //
-// Their work is a list of units (64-point tile, part) in tile-major order.
-// A part is a run of the launch's items (segments or instants): one output
-// bin's run, a fixed-size chunk, or all of them.  The units are cut into
-// eight contiguous ranges, one per XCD (block b runs on XCD b mod 8), each
-// with its own counter; a wave takes one unit per atomic from its XCD's
-// range, then from the others'.  Neighbouring tiles share hierarchy nodes
-// and prisms in their XCD's L2, and the waves stay resident until the work
-// runs out: no SIMD idles behind a long tile, and a launch's tail is one
-// unit long.
+// Their work is a list of units (64-point tile, part).  A part is a run of
+// the launch's items (segments or instants): one output bin's run, every n-th
+// item of it or of the launch, or all of them.  The tiles are cut into eight
+// contiguous ranges, one per XCD (block b runs on XCD b mod 8), each with its
+// own counter of units, all its tiles' first parts, then their second ones;
+// a wave takes one unit per atomic from its XCD's range, then from the
+// others'.  So the waves of an XCD walk neighbouring tiles on the same few
+// segments' views, which its L2 holds, and stay resident until the work runs
+// out: no SIMD idles behind a long tile, and a launch's tail is one unit
+// long.  Dealing a run's items out in turn, instead of in consecutive pieces,
+// gives every part its share of the low sun's long walks.  Tile by tile and
+// in consecutive pieces before: contributions (5,000 prisms, 300k points) 1.27
+// -> 1.07 ms, the sampled form (20,000 prisms, 1M points, 3 days) 5.43 -> 4.97
+// ms, forward and adjoint at 1-minute knots (200k points) 12.4 -> 10.2 ms,
+// the accrual form on the block scene 10.15 -> 10.04 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,13 +34,26 @@ constexpr int kSchedThreads = 256;               // threads per block of every p
 constexpr int kSchedWaves = kSchedThreads / 64;  // waves per block
 constexpr int kGrabStride = 32;                  // words between the eight counters (one 128-byte line each)
 
+// Work of at most this many items (tiles x segments or chunks) per resident
+// wave is dealt out, a unit per wave, instead of drawn from the counters: a
+// draw is a round trip to memory, and a wave that finds nothing left has
+// asked all eight counters.  (16,384 points and 64 prisms, a working day: 106
+// -> 62 us; 40,000 points and 400 prisms after an edit: 252 -> 161 us; the
+// sampled form on 20,000 points and 400 prisms: 167 -> 83 us.  More items a
+// wave leave the lengths of the units uneven: at 4, 8 and 16 the sampled form
+// on 60,000 points and 20,000 prisms takes 410, 307 and 306 us, contributions
+// of 120,000 points 691, 710 and 710, the accrual form on 200,000 points 681,
+// 680 and 699.)
+constexpr int64_t kFewUnits = 8;
+
 struct Sched {
     const int32_t *part_start;  // first item of each bin run of the launch (clipped to it), or null
-    uint32_t *grab;             // eight counters, kGrabStride words apart, zero at launch
+    uint32_t *grab;             // eight counters, kGrabStride words apart, zero at launch; null: a
+                                // unit per wave
     uint32_t n_tiles;
     uint32_t n_parts;
-    int32_t chunk;  // without part_start: items per part (0: one part, every item)
-    int32_t sub;    // with part_start: equal pieces each run is cut into (0 or 1: whole runs)
+    int32_t strided;  // without part_start: part p takes items p, p + n_parts, ... (0: one part, every item)
+    int32_t sub;    // with part_start: pieces each run is dealt into, item by item (0 or 1: whole runs)
 };
 
 namespace dev {
@@ -42,7 +61,8 @@ namespace dev {
 struct Unit {
     uint32_t tile;
     uint32_t part;
-    int a, b;  // the unit's items [a, b)
+    int a, b;  // the unit's items a, a + step, ... below b
+    int step;  // 1 but for strided parts
 };
 
 // The next unit of the launch whose Sched is parked at s_W, for items
@@ -53,37 +73,44 @@ struct Unit {
 __device__ __forceinline__ bool next_unit(const lds_int *s_W, int a0, int a1, int &k, Unit &un)
 {
     const Sched W = lds_uniform<Sched>(s_W);
-    const uint32_t n_units = W.n_tiles * W.n_parts;
     const int xcd = wg_id() & 7;
     for (; k < 8; ++k) {
         const int x = (xcd + k) & 7;
-        const uint32_t lo = (uint32_t)((uint64_t)n_units * x >> 3);
-        const uint32_t hi = (uint32_t)((uint64_t)n_units * (x + 1) >> 3);
+        const uint32_t lo = (uint32_t)((uint64_t)W.n_tiles * x >> 3);
+        const uint32_t tiles = (uint32_t)((uint64_t)W.n_tiles * (x + 1) >> 3) - lo;
         uint32_t got = 0;
-        if ((tid() & 63) == 0) got = atomicAdd(W.grab + kGrabStride * x, 1u);
-        got = (uint32_t)__builtin_amdgcn_readlane((int)got, 0);
-        if (got < hi - lo) {
-            const uint32_t u = lo + got;
+        if (W.grab) {
+            if ((tid() & 63) == 0) got = atomicAdd(W.grab + kGrabStride * x, 1u);
+            got = (uint32_t)__builtin_amdgcn_readlane((int)got, 0);
+        } else {
+            // a unit per wave: its own, then none
+            got = (uint32_t)uniform((int)((wg_id() >> 3) * kSchedWaves + (tid() >> 6)));
+            k = 7;
+        }
+        if (got < tiles * W.n_parts) {
             // the division runs on the vector unit: its result is made
             // scalar again for the scalar loads it addresses
-            const uint32_t tile = (uint32_t)uniform((int)(u / W.n_parts));
-            const uint32_t part = u - tile * W.n_parts;
-            un.tile = tile;
+            const uint32_t part = (uint32_t)uniform((int)(got / tiles));
+            un.tile = lo + got - part * tiles;
             un.part = part;
+            un.step = 1;
             if (W.part_start) {
                 const uint32_t sub = W.sub > 1 ? (uint32_t)W.sub : 1u;
                 const uint32_t run = part / sub, piece = part - run * sub;
                 const int ra = max(ld((cint *)W.part_start + run), a0);
                 const int rb = min(ld((cint *)W.part_start + run + 1), a1);
-                un.a = ra + (int)((int64_t)(rb - ra) * piece / sub);
-                un.b = ra + (int)((int64_t)(rb - ra) * (piece + 1) / sub);
-            } else if (W.chunk > 0) {
-                un.a = a0 + (int)part * W.chunk;
-                un.b = min(un.a + W.chunk, a1);
+                un.a = ra + (int)piece;
+                un.b = rb;
+                un.step = (int)sub;
+            } else if (W.strided) {
+                un.a = a0 + (int)part;
+                un.b = a1;
+                un.step = (int)W.n_parts;
             } else {
                 un.a = a0;
                 un.b = a1;
             }
+            k += W.grab ? 0 : 1;
             return true;
         }
     }
@@ -98,10 +125,10 @@ enum class Split {
     kUniqueBins,  // a part per bin run when no bin has two runs in the launch
                   // (each (tile, bin) is then one unit's: plain stores)
     kBinRuns,     // a part per bin run (outputs added atomically)
-    kChunks,      // parts of a fixed number of items, enough units to keep every
-                  // wave busy (outputs added atomically)
-    kRunPieces,   // as kUniqueBins, each run cut into equal pieces, enough units to
-                  // keep every wave busy (per-piece sums, added in a fixed order after)
+    kChunks,      // parts of every n-th item, enough units to keep every wave busy
+                  // (outputs added atomically, or one per item)
+    kRunPieces,   // as kUniqueBins, each run dealt into pieces, enough units to keep
+                  // every wave busy (per-piece sums, added in a fixed order after)
 };
 
 // Blocks of a persistent launch of `kern`: the tuned count, else as many
@@ -126,14 +153,21 @@ static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, 
 {
     Sched W{nullptr, grab, (uint32_t)tiles, 1u, 0, 0};
     if (split == Split::kNone || a1 <= a0) return W;
+    const int64_t waves = blocks * kSchedWaves;
+    // the most parts that give every wave at most one unit (per XCD, whose
+    // tiles are an eighth, rounded up)
+    const int64_t single = (blocks / 8) * kSchedWaves / std::max<int64_t>((tiles + 7) / 8, 1);
     if (split == Split::kChunks) {
         const int64_t items = a1 - a0;
-        const int64_t want = std::max<int64_t>(1, (8 * blocks * kSchedWaves + tiles - 1) / tiles);
+        const int64_t want = std::max<int64_t>(1, (8 * waves + tiles - 1) / tiles);
         int64_t parts = std::min(items, want);
+        if (single >= 1 && tiles * items <= kFewUnits * waves) {
+            parts = std::min(items, single);
+            W.grab = nullptr;
+        }
         while (parts > 1 && (uint64_t)tiles * (uint64_t)parts >= (1ull << 31)) parts /= 2;
-        const int64_t chunk = (items + parts - 1) / parts;
-        W.chunk = (int32_t)chunk;
-        W.n_parts = (uint32_t)((items + chunk - 1) / chunk);
+        W.strided = 1;
+        W.n_parts = (uint32_t)parts;
         return W;
     }
     if (R.dev == nullptr || R.start.size() < 2) return W;
@@ -155,8 +189,12 @@ static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, 
         // than one item, no more parts than the caller can hold
         int shortest = a1 - a0;
         for (int r = r0; r <= r1; ++r) shortest = std::min(shortest, std::min(rs[r + 1], a1) - std::max(rs[r], a0));
-        const int64_t want = (8 * blocks * kSchedWaves + tiles * runs - 1) / (tiles * runs);
+        const int64_t want = (8 * waves + tiles * runs - 1) / (tiles * runs);
         int64_t sub = std::min<int64_t>(std::min<int64_t>(want, shortest), std::max<int64_t>(1, max_parts / runs));
+        if (single >= runs && tiles * (a1 - a0) <= kFewUnits * waves) {
+            sub = std::min(sub, single / runs);
+            W.grab = nullptr;
+        }
         while (sub > 1 && (uint64_t)tiles * (uint64_t)(runs * sub) >= (1ull << 31)) sub /= 2;
         if (sub > 1) {
             W.sub = (int32_t)sub;
@@ -169,6 +207,7 @@ static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, 
 // Blocks to launch: never more than the units need.
 static inline int64_t unit_blocks(int64_t blocks, const Sched &W)
 {
+    if (!W.grab) return 8 * (((int64_t)(W.n_tiles + 7) / 8 * W.n_parts + kSchedWaves - 1) / kSchedWaves);
     const int64_t units = (int64_t)W.n_tiles * W.n_parts;
     return std::max<int64_t>(1, std::min<int64_t>(blocks, (units + kSchedWaves - 1) / kSchedWaves));
 }
