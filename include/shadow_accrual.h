@@ -317,13 +317,13 @@ typedef struct {
  * added with float atomics in no fixed order.
  * The accrual form (here, and in sa_accumulate_batched, sa_grad_heights
  * and sa_building_contribution) keeps a per-segment view of the hierarchy
- * (64 bytes per node and segment, at most 256 MiB per launch; longer paths
+ * (64 bytes per node and segment, at most 1 GiB per launch; longer paths
  * run as several launches, the continuous shadow one day at least) in
  * memory the context owns: grown on first need with the stream
  * synchronised, kept until sa_destroy.  Under stream capture make one
  * eager call of the same (or a larger) size first.  The sampled form keeps
  * the same views per 16 instants and a 16-bit mask per point and 16
- * instants, likewise at most 256 MiB each per launch; it needs neither, nor
+ * instants, at most 256 MiB each per launch; it needs neither, nor
  * an eager call, under stream capture.
  * Errors: INVALID_ARG, CAPACITY (reported by sa_sync if the accrual spill
  * queue overflows), OOM, DEVICE. */

@@ -17,12 +17,14 @@ using namespace dev;
 
 constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
-// Spill rounds: each refines a window 64-fold, so three rounds reach
-// 1/262144 of a segment.
-constexpr int kSpillRounds = 3;
 constexpr int kSpillBlocks = 1024;
 constexpr int64_t kChunkWork = 4000000000ll;  // point-segments per accrual launch
-constexpr int64_t kSegNodeBytes = 256ll << 20;  // per-segment node views per accrual launch
+// Per-segment node views per launch.  A launch has its set-up, its spilled
+// windows and a last unit that others wait for: a year on 45,000 prisms and
+// 500,000 points (97 launches of 256 MiB) takes 236, 219 and 207 ms at 256,
+// 512 and 1024 MiB.  Where that much cannot be had, down to kLeastNodeBytes.
+constexpr int64_t kSegNodeBytes = 1024ll << 20;
+constexpr int64_t kLeastNodeBytes = 256ll << 20;
 constexpr int64_t kPieceBytes = 256ll << 20;    // per-piece sums of an accrual launch on few tiles
 
 // Per-bin outputs of the accrual kernels.  A bin whose first segment lies in
@@ -540,12 +542,15 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
     ov = lane_in(ovm);
 }
 
+__global__ void k_clear_state(LaunchState L) { clear_state(L, tid()); }
+
 // The per-segment node views of segments [j0, j1): one thread per
-// (segment, node), written to out[(j - j0) * stride + node].
+// (segment, node), written to out[(j - j0) * stride + node].  Blocks of 256.
 __global__ void k_seg_nodes(const Node *__restrict__ nodes, int n_nodes, const SegConst *__restrict__ segs, int j0,
-                            int j1, int64_t stride, SegNode *__restrict__ out)
+                            int j1, int64_t stride, SegNode *__restrict__ out, LaunchState L)
 {
     const int64_t t = (int64_t)wg_id() * wg_size() + tid();
+    clear_state(L, t);
     if (t >= (int64_t)(j1 - j0) * n_nodes) return;
     const int jj = (int)(t / n_nodes);
     const int node = (int)(t - (int64_t)jj * n_nodes);
@@ -685,6 +690,7 @@ __global__ void k_add_pieces(Sched W, int j0, int j1, const SegConst *__restrict
         const int64_t i = t - (int64_t)r * n;
         int cnt = 0;
         double mins = 0.0;
+#pragma unroll 8
         for (int p = r * sub; p < (r + 1) * sub; ++p) {
             cnt += O.pcnt[(int64_t)p * n + i];
             mins += O.pmin[(int64_t)p * n + i];
@@ -829,24 +835,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     }
 }
 
-// One spill round: each queued (point, segment, window) is taken by one
-// wave whose 64 lanes take one 64th of the window each.  Every lane follows
-// the same point along the same segment, so the wave's traversal stays
-// coherent (a lane per queued entry would walk 64 unrelated points).  The
-// lanes' measures are summed across the wave and added with one atomic per
-// output; sub-windows that still need more than four pieces go to the
-// next queue.
+// The queued point-segments: each is taken by one wave whose 64 lanes take
+// one 64th of the window each.  Every lane follows the same point along the
+// same segment, so the wave's traversal stays coherent (a lane per queued
+// entry would walk 64 unrelated points).  Sub-windows that still need more
+// than four pieces wait in LDS and are split 64 ways again, three levels in
+// all (1/262144 of a segment; what is left then raises the overflow flag).
+// The lanes' measures are summed across the wave and added with one atomic
+// per output.  One launch: as three rounds over two queues, with their
+// clears, it was seven (4 us each and the gaps where nothing is queued).
 __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int n_nodes, int j0, const int32_t *voff_g,
                                                     const float4 *verts_g, const float *height_g,
                                                     const SegConst *segs_g, PointArgs P, float scale, int32_t *counts,
                                                     float *minutes, double *minutes64, const int4 *in,
-                                                    const uint32_t *in_count, int32_t cap, SpillArgs S)
+                                                    const uint32_t *in_count, int32_t cap, uint32_t *overflow)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
     __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ SpillWindow s_wait[kWaves][kSpillWait];
     StackEntry *stack = s_stack[tid() >> 6];
+    SpillWindow *wait = s_wait[tid() >> 6];
     const int lane = tid() & 63;
     const int64_t total = min((int32_t)*in_count, cap);
     const int64_t stride = (int64_t)n_wg() * kWaves;
@@ -854,23 +864,23 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
         const int4 en = in[e];
         const int64_t i = uniform(en.x);
         const int j = uniform(en.y);
-        const float ew0 = __int_as_float(uniform(en.z)), ew1 = __int_as_float(uniform(en.w));
-        // lane l takes [w0 + l d, w0 + (l + 1) d]: neighbours share the same
-        // rounded boundary, the last lane ends exactly at ew1
-        const float d = (ew1 - ew0) * (1.f / 64.f);
-        const float w0 = lane == 0 ? ew0 : fmaf((float)lane, d, ew0);
-        const float w1 = lane == 63 ? ew1 : fmaf((float)(lane + 1), d, ew0);
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
-        Union4 U;
-        bool ov;
-        Work none{0, 0, 0, 0, 0, 0, 0};
         const SegSrc src{snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr,
                          (cint *)voff_g, 0};
-        accrue_segment<false>(src, stack, verts, height, g, q, true, w0, w1, U, ov, none);
+        SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
         double mins = 0.0;
         int cnt = 0;
-        if (!ov) measure(U, g, w0, w1, w1 >= g.theta, mins, cnt);
+        for (int waiting = 0;;) {
+            float w0, w1;
+            spill_share(win, lane, w0, w1);
+            Union4 U;
+            bool ov;
+            Work none{0, 0, 0, 0, 0, 0, 0};
+            accrue_segment<false>(src, stack, verts, height, g, q, true, w0, w1, U, ov, none);
+            if (!ov) measure(U, g, w0, w1, w1 >= g.theta, mins, cnt);
+            if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
+        }
         for (int o = 32; o > 0; o >>= 1) {
             mins += __shfl_xor(mins, o, 64);
             cnt += __shfl_xor(cnt, o, 64);
@@ -881,7 +891,6 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
             if (minutes64) atomicAdd(&minutes64[o], mins * scale);
             if (counts) atomicAdd(&counts[o], cnt);
         }
-        spill_push(S, ov, i, j, w0, w1);
     }
 }
 
@@ -1240,13 +1249,6 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
     for (int64_t t = (int64_t)wg_id() * wg_size() + tid(); t < n; t += stride) p[t] = v;
 }
 
-__global__ void k_zero_u32(uint32_t *p) { *p = 0u; }
-
-__global__ void k_spill_check(const uint32_t *count, uint32_t *overflow)
-{
-    if (*count) atomicOr(overflow, 2u);
-}
-
 }  // namespace
 
 #define SA_CHECK_LAUNCH(what)                                                   \
@@ -1257,6 +1259,23 @@ __global__ void k_spill_check(const uint32_t *count, uint32_t *overflow)
             return SA_ERR_DEVICE;                                               \
         }                                                                       \
     } while (0)
+
+static bool grow(Scratch &scr, size_t need, hipStream_t st)
+{
+    if (scr.bytes >= need) return true;
+    // the previous contents may still be read by queued kernels
+    (void)hipStreamSynchronize(st);
+    (void)hipFree(scr.ptr);
+    scr.ptr = nullptr;
+    scr.bytes = 0;
+    if (hipMalloc(&scr.ptr, need) != hipSuccess) {
+        (void)hipGetLastError();
+        scr.ptr = nullptr;
+        return false;
+    }
+    scr.bytes = need;
+    return true;
+}
 
 static PointArgs point_args(const PointsView &pts, const DeviceScene &s)
 {
@@ -1296,8 +1315,7 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
     }
     res = resident_blocks(kern, L);
     W = plan_units(p.sample_runs, 0, p.n_samples, tiles, split, res, grab);
-    sa_status rc = SA_OK;
-            if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
+    sa_status rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
     if (rc != SA_OK) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, s.verts,
                        s.height, p.samples, p.n_samples, W, point_args(pts, s),
@@ -1310,17 +1328,9 @@ sa_status run_spill(const DeviceScene &s, const DevicePath &p, const SegNode *vi
                     float scale, int32_t *counts, float *minutes, double *minutes64, SpillQueue &q, hipStream_t st,
                     std::string &err)
 {
-    int cur = 0;
-    for (int r = 0; r < kSpillRounds; ++r) {
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, q.counters + (cur ^ 1));
-        SpillArgs S{q.entries[cur ^ 1], q.counters + (cur ^ 1), q.counters + 2, q.capacity};
-        hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, j0, s.voff, s.verts,
-                           s.height, p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries[cur],
-                           (const uint32_t *)(q.counters + cur), q.capacity, S);
-        cur ^= 1;
-    }
-    // anything still queued after the last round is unfinished work
-    hipLaunchKernelGGL(k_spill_check, dim3(1), dim3(1), 0, st, (const uint32_t *)(q.counters + cur), q.counters + 2);
+    hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, j0, s.voff, s.verts, s.height,
+                       p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries, (const uint32_t *)q.counters,
+                       q.capacity, q.counters + 2);
     SA_CHECK_LAUNCH("accrual spill");
     return SA_OK;
 }
@@ -1367,18 +1377,9 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
     const size_t cnt_at = part(sizeof(int32_t) * (size_t)n_var);
     const size_t root_at = part(sizeof(int32_t) * (size_t)n_var);
     const size_t counter_at = part(256);
-    if (scr.bytes < need) {
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(scr.ptr);
-        scr.ptr = nullptr;
-        scr.bytes = 0;
-        if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-            (void)hipGetLastError();
-            scr.ptr = nullptr;
-            err = "variant scratch allocation failed";
-            return SA_ERR_OOM;
-        }
-        scr.bytes = need;
+    if (!grow(scr, need, st)) {
+        err = "variant scratch allocation failed";
+        return SA_ERR_OOM;
     }
     char *base = (char *)scr.ptr;
     float *vh = (float *)(base + h_at);
@@ -1401,21 +1402,19 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
     const int blocks = grid_blocks > 0 ? grid_blocks : 2048;
     // segment ranges whose views (base and every variant's copies) fit the
     // per-launch budget; outputs accumulate across the launches
-    const int64_t per = std::max<int64_t>(1, kSegNodeBytes / (stride * (int64_t)sizeof(SegNode)));
+    const int64_t per = seg_views_cap(s, p, stride, views_scr, st);
     for (int64_t j0 = 0; j0 < std::max(p.n_segs, 1); j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         SegNode *views = nullptr;
-        if (s.n_b > 0 && j1 > j0) {
-            sa_status rc = build_seg_views(s, p, (int)j0, j1, stride, views_scr, st, views, err);
-            if (rc != SA_OK) return rc;
+        sa_status rc = build_seg_views(s, p, (int)j0, j1, stride, views_scr, {nullptr, counter, 2}, st, views, err);
+        if (rc != SA_OK) return rc;
+        if (views) {
             const int64_t nt = (int64_t)(j1 - j0) * n_var * cmax;
             hipLaunchKernelGGL(k_seg_var, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, n_var, cmax, n_nodes,
                                (const Node *)s.nodes, (const int32_t *)vlist, (const int32_t *)vcount,
                                (const int32_t *)vmap, (const float2 *)vz, p.segs, (int)j0, j1, stride, views);
             SA_CHECK_LAUNCH("variant segment views");
         }
-        sa_status rc = fill_u32(counter, 2, 0u, st, err);
-        if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(k_batched, dim3(blocks), dim3(kThreads), 0, st, s.n_b > 0 ? (const Node *)s.nodes : nullptr,
                            views, stride, s.voff, s.n_b > 0 ? (const int32_t *)vroot : nullptr, s.verts,
                            (const float *)vh, s.n_b, p.segs, (int)j0, j1, P, var_off, (const int64_t *)tile_off,
@@ -1425,18 +1424,32 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
     return SA_OK;
 }
 
-int64_t seg_views_cap(const DeviceScene &s, const Scratch &scr)
+int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, int64_t stride, Scratch &scr, hipStream_t st)
 {
-    const int64_t per_seg = (int64_t)std::max(s.n_nodes, 1) * (int64_t)sizeof(SegNode);
+    const int64_t per_seg = std::max<int64_t>(stride, 1) * (int64_t)sizeof(SegNode);
     if (scr.fixed) return (int64_t)scr.bytes / per_seg;
-    return std::max<int64_t>(1, kSegNodeBytes / per_seg);
+    if (s.n_b == 0) return std::max(p.n_segs, 1);
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(kSegNodeBytes / per_seg, p.n_segs));
+    if (scr.bytes >= (size_t)(want * per_seg)) return want;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+    if (cs != hipStreamCaptureStatusNone) return std::max<int64_t>(1, (int64_t)scr.bytes / per_seg);
+    for (int64_t budget = kSegNodeBytes; budget > kLeastNodeBytes; budget /= 2) {
+        const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(budget / per_seg, p.n_segs));
+        if (grow(scr, (size_t)(cap * per_seg), st)) return cap;
+    }
+    return std::max<int64_t>(1, kLeastNodeBytes / per_seg);
 }
 
 sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int j1, int64_t stride, Scratch &scr,
-                          hipStream_t st, SegNode *&views, std::string &err)
+                          const LaunchState &state, hipStream_t st, SegNode *&views, std::string &err)
 {
     views = nullptr;
-    if (s.n_b == 0 || j1 <= j0) return SA_OK;
+    if (s.n_b == 0 || j1 <= j0) {
+        hipLaunchKernelGGL(k_clear_state, dim3(1), dim3(256), 0, st, state);
+        SA_CHECK_LAUNCH("launch state");
+        return SA_OK;
+    }
     const int64_t nt = (int64_t)(j1 - j0) * s.n_nodes;
     const size_t need = (size_t)(j1 - j0) * stride * sizeof(SegNode);
     if (scr.bytes < need && scr.fixed) {
@@ -1444,23 +1457,13 @@ sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int
               std::to_string(scr.bytes);
         return SA_ERR_CAPACITY;
     }
-    if (scr.bytes < need) {
-        // the previous contents may still be read by queued kernels
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(scr.ptr);
-        scr.ptr = nullptr;
-        scr.bytes = 0;
-        if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-            (void)hipGetLastError();
-            scr.ptr = nullptr;
-            err = "segment node view allocation failed";
-            return SA_ERR_OOM;
-        }
-        scr.bytes = need;
+    if (!grow(scr, need, st)) {
+        err = "segment node view allocation failed";
+        return SA_ERR_OOM;
     }
     views = (SegNode *)scr.ptr;
     hipLaunchKernelGGL(k_seg_nodes, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, s.nodes, s.n_nodes, p.segs,
-                       j0, j1, stride, views);
+                       j0, j1, stride, views, state);
     SA_CHECK_LAUNCH("segment node views");
     return SA_OK;
 }
@@ -1491,7 +1494,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     // each about kChunkWork point-segments and covering at most
     // kSegNodeBytes of per-segment node views (built just before it);
     // outputs are accumulated, so the split is invisible in the results.
-    const int64_t cap = seg_views_cap(s, scr);
+    const int64_t cap = seg_views_cap(s, p, s.n_nodes, scr, st);
     if (s.n_b > 0 && p.n_segs > 0 && cap < 1) {
         err = "one segment's node views (" + std::to_string((int64_t)s.n_nodes * (int64_t)sizeof(SegNode)) +
               " bytes) exceed the fixed scratch (" + std::to_string(scr.bytes) + " bytes)";
@@ -1515,12 +1518,10 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             while (d1 < D && p.day_seg_off[d1 + 1] - p.day_seg_off[d0] <= per) ++d1;
             const int j0 = p.day_seg_off[d0], j1 = p.day_seg_off[d1];
             SegNode *views;
-            sa_status rc = build_seg_views(s, p, j0, j1, s.n_nodes, scr, st, views, err);
+            sa_status rc = build_seg_views(s, p, j0, j1, s.n_nodes, scr, {nullptr, q.grab, 8 * kGrabStride}, st, views, err);
             if (rc != SA_OK) return rc;
             const int64_t res = resident_blocks(k_accrual_runs, L);
             const Sched W = plan_units(p.seg_runs, j0, j1, tiles, Split::kUniqueBins, res, q.grab);
-            if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
-            if (rc != SA_OK) return rc;
             hipLaunchKernelGGL(k_accrual_runs, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
                                st, nodes, views, s.n_nodes, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
                                bin_out(p, j0, store, counts, minutes, minutes64, scale), longest, q.counters + 2);
@@ -1548,18 +1549,9 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
         } else {
             max_parts = std::max<int64_t>(1, kPieceBytes / per_part);
             const size_t need = (size_t)(std::min<int64_t>(max_parts, 8 * res * kWaves) * per_part) + 256;
-            if (piece_scr.bytes < need) {
-                (void)hipStreamSynchronize(st);  // earlier launches may still read it
-                (void)hipFree(piece_scr.ptr);
-                piece_scr.ptr = nullptr;
-                piece_scr.bytes = 0;
-                if (hipMalloc(&piece_scr.ptr, need) != hipSuccess) {
-                    (void)hipGetLastError();
-                    piece_scr.ptr = nullptr;
-                    err = "accrual piece sums allocation failed";
-                    return SA_ERR_OOM;
-                }
-                piece_scr.bytes = need;
+            if (!grow(piece_scr, need, st)) {
+                err = "accrual piece sums allocation failed";
+                return SA_ERR_OOM;
             }
             max_parts = ((int64_t)piece_scr.bytes - 256) / per_part;
         }
@@ -1567,10 +1559,10 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         SegNode *views;
-        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, st, views, err);
+        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {q.counters, q.grab, 8 * kGrabStride},
+                                       st, views, err);
         if (rc != SA_OK) return rc;
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, q.counters);
-        SpillArgs S{q.entries[0], q.counters, q.counters + 2, q.capacity};
+        SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, pieces ? Split::kRunPieces : Split::kUniqueBins,
                                    res, q.grab, max_parts);
         BinOut O = bin_out(p, (int)j0, store, counts, minutes, minutes64, scale);
@@ -1579,8 +1571,6 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             O.pcnt = (int32_t *)piece_scr.ptr;
             O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
-        if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
-        if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, views, s.n_nodes,
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
         SA_CHECK_LAUNCH("accrual kernel");
@@ -1606,18 +1596,17 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
     const PointArgs P = point_args(pts, s);
     // long spans: several launches over consecutive segment ranges
     const int64_t per =
-        std::min(std::max<int64_t>(1, kChunkWork / 2 / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, scr));
+        std::min(std::max<int64_t>(1, kChunkWork / 2 / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, s.n_nodes, scr, st));
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         SegNode *views;
-        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, st, views, err);
+        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {nullptr, grab, 8 * kGrabStride}, st,
+                                       views, err);
         if (rc != SA_OK) return rc;
         // the sums are atomic: on few tiles the units are chunks of segments
         const int64_t res = resident_blocks(k_contrib, L);
         const Split split = tiles < 2 * res * kWaves ? Split::kChunks : Split::kBinRuns;
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, split, res, grab);
-        if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
-        if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(k_contrib, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, views,
                            s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, weight,
                            (const int32_t *)s.order, s.n_b, contrib);

@@ -179,8 +179,7 @@ sa_status sa_create(int32_t device, void *hip_stream, sa_ctx **out)
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
     c->spill.capacity = kSpillCapacity;
-    if (hipMalloc((void **)&c->spill.entries[0], sizeof(int4) * kSpillCapacity) != hipSuccess ||
-        hipMalloc((void **)&c->spill.entries[1], sizeof(int4) * kSpillCapacity) != hipSuccess ||
+    if (hipMalloc((void **)&c->spill.entries, sizeof(int4) * kSpillCapacity) != hipSuccess ||
         hipMalloc((void **)&c->spill.counters, sizeof(uint32_t) * kCounterWords) != hipSuccess ||
         hipMemset(c->spill.counters, 0, sizeof(uint32_t) * kCounterWords) != hipSuccess) {
         sa_destroy(c);
@@ -199,8 +198,7 @@ void sa_destroy(sa_ctx *ctx)
 {
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
-    (void)hipFree(ctx->spill.entries[0]);
-    (void)hipFree(ctx->spill.entries[1]);
+    (void)hipFree(ctx->spill.entries);
     (void)hipFree(ctx->spill.counters);
     (void)hipFree(ctx->scratch.ptr);
     (void)hipFree(ctx->scratch_batched.ptr);
@@ -251,7 +249,7 @@ sa_status sa_measure_valu_peak(sa_ctx *ctx, double *lane_ops_per_s)
     if (!ctx || !lane_ops_per_s) return SA_ERR_INVALID_ARG;
     if (!set_device(ctx)) return fail(ctx, SA_ERR_DEVICE, "hipSetDevice failed");
     std::string err;
-    const sa_status rc = sa::measure_valu_peak(ctx->n_cu, (float *)ctx->spill.entries[0],
+    const sa_status rc = sa::measure_valu_peak(ctx->n_cu, (float *)ctx->spill.entries,
                                                (int64_t)ctx->spill.capacity * 4, ctx->stream, *lane_ops_per_s, err);
     return rc == SA_OK ? SA_OK : fail(ctx, rc, err);
 }

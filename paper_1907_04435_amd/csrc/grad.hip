@@ -27,9 +27,6 @@ using namespace dev;
 
 constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
-// Spill rounds: each refines a window 64-fold (three reach 1/262144 of a
-// segment).
-constexpr int kSpillRounds = 3;
 constexpr int kSpillBlocks = 1024;
 
 struct GradArgs {
@@ -188,21 +185,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     }
 }
 
-// One spill round of the adjoint: as the accrual spill rounds, one wave per
-// queued (point, segment, window), each lane one 64th of the window.  Ends
-// clamped to a sub-window do not move with a height, so splitting adds no
-// gradient terms.
+// The adjoint's spilled point-segments: as the accrual form's, one wave each,
+// every lane one 64th of the window, sub-windows split again.  Ends clamped to
+// a sub-window do not move with a height, so splitting adds no gradient terms.
 __global__ __launch_bounds__(kThreads) void k_grad_spill(const SegNode *snodes_g, int n_nodes, int j0,
                                                          const int32_t *voff_g, const float4 *verts_g,
                                                          const float *height_g, const SegConst *segs_g, PointArgs P,
                                                          GradArgs G, const int4 *in, const uint32_t *in_count,
-                                                         int32_t cap, SpillArgs S)
+                                                         int32_t cap, uint32_t *overflow)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
     __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ SpillWindow s_wait[kWaves][kSpillWait];
     StackEntry *stack = s_stack[tid() >> 6];
+    SpillWindow *wait = s_wait[tid() >> 6];
     const int lane = tid() & 63;
     const int64_t total = min((int32_t)*in_count, cap);
     const int64_t stride = (int64_t)n_wg() * kWaves;
@@ -210,34 +208,28 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const SegNode *snodes_g
         const int4 en = in[e];
         const int64_t i = uniform(en.x);
         const int j = uniform(en.y);
-        const float ew0 = __int_as_float(uniform(en.z)), ew1 = __int_as_float(uniform(en.w));
-        const float d = (ew1 - ew0) * (1.f / 64.f);
-        const float w0 = lane == 0 ? ew0 : fmaf((float)lane, d, ew0);
-        const float w1 = lane == 63 ? ew1 : fmaf((float)(lane + 1), d, ew0);
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
         const float w = G.dl ? G.dl[(int64_t)g.bin * P.n + i] : 1.f;
-        UnionG U;
-        bool ov;
         cSegNode *sn = snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr;
-        grad_segment(sn, (cint *)voff_g, stack, verts, height, g, q, true, w0, w1, U, ov);
-        scatter_grad(U, !ov, w * g.wrate, G);
-        spill_push(S, ov, i, j, w0, w1);
+        SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
+        for (int waiting = 0;;) {
+            float w0, w1;
+            spill_share(win, lane, w0, w1);
+            UnionG U;
+            bool ov;
+            grad_segment(sn, (cint *)voff_g, stack, verts, height, g, q, true, w0, w1, U, ov);
+            scatter_grad(U, !ov, w * g.wrate, G);
+            if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
+        }
     }
 }
-
-__global__ void k_zero1(uint32_t *p) { *p = 0u; }
 
 // grad[b] = (add ? grad[b] : 0) + scale * acc[b], rounded once to float.
 __global__ void k_grad_out(const double *acc, int32_t n_b, double scale, int add, float *grad)
 {
     const int b = wg_id() * wg_size() + tid();
     if (b < n_b) grad[b] = (float)((add ? (double)grad[b] : 0.0) + scale * acc[b]);
-}
-
-__global__ void k_spill_left(const uint32_t *count, uint32_t *overflow)
-{
-    if (*count) atomicOr(overflow, 2u);
 }
 
 }  // namespace
@@ -271,30 +263,19 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     const GradArgs G{dl, acc, s.order};
     // segment ranges whose per-segment node views fit the budget, each
     // followed by its spill rounds
-    const int64_t per = seg_views_cap(s, scr);
+    const int64_t per = seg_views_cap(s, p, s.n_nodes, scr, st);
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         SegNode *views;
-        rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, st, views, err);
+        rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
         if (rc != SA_OK) return rc;
-        hipLaunchKernelGGL(k_zero1, dim3(1), dim3(1), 0, st, q.counters);
-        SpillArgs S{q.entries[0], q.counters, q.counters + 2, q.capacity};
+        SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
-        if (W.grab) rc = fill_u32(q.grab, 8 * kGrabStride, 0u, st, err);
-        if (rc != SA_OK) return rc;
         hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, s.nodes, views,
                            s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
-        int cur = 0;
-        for (int r = 0; r < kSpillRounds; ++r) {
-            hipLaunchKernelGGL(k_zero1, dim3(1), dim3(1), 0, st, q.counters + (cur ^ 1));
-            SpillArgs S2{q.entries[cur ^ 1], q.counters + (cur ^ 1), q.counters + 2, q.capacity};
-            hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, (int)j0,
-                               s.voff, s.verts, s.height, p.segs, P, G, (const int4 *)q.entries[cur],
-                               (const uint32_t *)(q.counters + cur), q.capacity, S2);
-            cur ^= 1;
-        }
-        hipLaunchKernelGGL(k_spill_left, dim3(1), dim3(1), 0, st, (const uint32_t *)(q.counters + cur),
-                           q.counters + 2);
+        hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, (int)j0, s.voff,
+                           s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, (const uint32_t *)q.counters,
+                           q.capacity, q.counters + 2);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
             err = std::string("gradient kernels: ") + hipGetErrorString(e);

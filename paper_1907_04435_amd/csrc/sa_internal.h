@@ -231,10 +231,17 @@ struct Scratch {
 };
 
 struct SpillQueue {
-    int4 *entries[2] = {nullptr, nullptr};  // (point, segment, w0 bits, w1 bits)
-    uint32_t *counters = nullptr;           // [0],[1] queue lengths, [2] overflow flag
-    uint32_t *grab = nullptr;               // the accrual launch's work counters (eight, 128 B apart)
+    int4 *entries = nullptr;       // (point, segment, w0 bits, w1 bits)
+    uint32_t *counters = nullptr;  // [0] queue length, [2] overflow flag
+    uint32_t *grab = nullptr;      // the accrual launch's work counters (eight, 128 B apart)
     int32_t capacity = 0;
+};
+
+// Device words a launch finds at zero (either may be null); n_counters <= 256.
+struct LaunchState {
+    uint32_t *queue_length;
+    uint32_t *counters;
+    int32_t n_counters;
 };
 
 // Launch choices of the per-tile kernels: the most segments one accrual
@@ -288,12 +295,14 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
                               Scratch &scr, hipStream_t st, std::string &err);
 // Per-segment node views (SegNode) of segments [j0, j1) into scr (grown as
 // needed, with the stream synchronised first; a fixed scr that is too small
-// is a CAPACITY error), segment j's views at (j - j0) * stride; views =
-// nullptr for an empty scene.  seg_views_cap: segments whose views fit the
-// per-launch budget (a fixed scr: its size; 0 if not even one fits).
+// is a CAPACITY error), segment j's views at (j - j0) * stride, and `state`
+// cleared; views = nullptr for an empty scene.  seg_views_cap: segments whose
+// views (stride each) a launch takes: the per-launch budget, less where scr
+// cannot be grown to it (a fixed scr, or one under stream capture: its size;
+// 0 if not even one fits).
 sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int j1, int64_t stride, Scratch &scr,
-                          hipStream_t st, SegNode *&views, std::string &err);
-int64_t seg_views_cap(const DeviceScene &s, const Scratch &scr);
+                          const LaunchState &state, hipStream_t st, SegNode *&views, std::string &err);
+int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, int64_t stride, Scratch &scr, hipStream_t st);
 // Gross shadow by raster shadow accrual maps (Sec. 4) into counts/minutes
 // [n_bins * n] (already cleared): per segment a map of slices x nu x nv
 // 64-bit words (stamp, depth) in scr (grown as needed; max_texels caps one

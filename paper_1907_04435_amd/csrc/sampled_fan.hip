@@ -253,11 +253,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
 }
 
 // Views of the hierarchy for the fans of chunks [c0, c1): one thread per
-// (chunk, node).
+// (chunk, node), in blocks of 256.
 __global__ void k_fan_nodes(const Node *__restrict__ nodes, int n_nodes, const FanChunk *__restrict__ chunks, int c0,
-                            int c1, SegNode *__restrict__ out)
+                            int c1, SegNode *__restrict__ out, LaunchState L)
 {
     const int64_t t = (int64_t)wg_id() * wg_size() + tid();
+    clear_state(L, t);
     if (t >= (int64_t)(c1 - c0) * n_nodes) return;
     const int cc = (int)(t / n_nodes);
     const Node nd = nodes[t - (int64_t)cc * n_nodes];
@@ -430,7 +431,8 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
             views = (SegNode *)views_scr.ptr;
             const int64_t nt = (int64_t)(c1 - c0) * s.n_nodes;
             hipLaunchKernelGGL(k_fan_nodes, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, (const Node *)s.nodes,
-                               s.n_nodes, (const FanChunk *)p.chunks, c0, c1, views);
+                               s.n_nodes, (const FanChunk *)p.chunks, c0, c1, views,
+                               LaunchState{nullptr, grab, 8 * kGrabStride});
             SA_CHECK_LAUNCH("fan node views");
         }
         // bin runs of the launch: summed by a thread each where no bin has two
@@ -442,9 +444,10 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
             const PointArgs P{n, pts.x + i0, pts.y + i0, pts.z + i0, pts.nx ? pts.nx + i0 : nullptr,
                               pts.ny ? pts.ny + i0 : nullptr, pts.owner ? pts.owner + i0 : nullptr, s.rank, s.n_b};
             const Sched W = plan_units(p.chunk_runs, c0, c1, (n + 63) / 64, Split::kChunks, res, grab);
-            sa_status rc = SA_OK;
-            if (W.grab) rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
-            if (rc != SA_OK) return rc;
+            if (W.grab && (i0 > 0 || !views)) {  // later ranges: the views' kernel cleared the first's
+                sa_status rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
+                if (rc != SA_OK) return rc;
+            }
             hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, (const SegNode *)views,
                                s.n_nodes, s.voff, s.verts, s.height, (const FanChunk *)p.chunks,
                                (const FanDirs *)p.chunk_dirs, c0, c1, W, P, masks, work);

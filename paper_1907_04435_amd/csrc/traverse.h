@@ -957,6 +957,53 @@ __device__ __forceinline__ void spill_push(const SpillArgs &S, bool want, int64_
 //     x1 max(nx,0) + x0 min(nx,0) + y1 max(ny,0) + y0 min(ny,0),
 // a wave-uniform value (the box is the wave's node) compared with the
 // lane's n.p.
+// What a launch's persistent waves start from: an empty spill queue and work
+// counters at zero, cleared by the kernel before it (thread t < 256 of it).
+__device__ __forceinline__ void clear_state(const LaunchState &L, int64_t t)
+{
+    if (L.queue_length && t == 0) *L.queue_length = 0u;
+    if (t < L.n_counters) L.counters[t] = 0u;
+}
+
+// A spilled window (or one's sub-window) taken 64 ways by a wave.
+struct SpillWindow {
+    float w0, w1;
+    int level;
+};
+constexpr int kSpillLevels = 3;
+constexpr int kSpillWait = 64 * kSpillLevels;  // each level leaves at most 64, one of which the next takes
+
+// Lane l takes [w0 + l d, w0 + (l + 1) d]: neighbours share the same rounded
+// boundary, the last lane ends exactly at the window's end.
+__device__ __forceinline__ void spill_share(const SpillWindow &win, int lane, float &w0, float &w1)
+{
+    const float d = (win.w1 - win.w0) * (1.f / 64.f);
+    w0 = lane == 0 ? win.w0 : fmaf((float)lane, d, win.w0);
+    w1 = lane == 63 ? win.w1 : fmaf((float)(lane + 1), d, win.w0);
+}
+
+// Lines up the sub-windows of the lanes with `ov` and takes the next one in
+// line; false when none is left.
+__device__ __forceinline__ bool spill_next(SpillWindow *wait, int &waiting, bool ov, float w0, float w1,
+                                           uint32_t *overflow, SpillWindow &win)
+{
+    const uint64_t m = ballot(ov);
+    if (m && win.level + 1 < kSpillLevels) {
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (ov) wait[waiting + rank] = SpillWindow{w0, w1, win.level + 1};
+        waiting += __builtin_popcountll(m);
+    } else if (m && first_active_lane()) {
+        atomicOr(overflow, 2u);  // unfinished work
+    }
+    if (waiting == 0) return false;
+    --waiting;
+    const SpillWindow next = wait[waiting];
+    win.w0 = __int_as_float(uniform(__float_as_int(next.w0)));
+    win.w1 = __int_as_float(uniform(__float_as_int(next.w1)));
+    win.level = uniform(next.level);
+    return true;
+}
+
 // The fan of a segment seen from the xy plane: over the segment the rays
 // from p sweep the wedge between the horizontal offsets ua (first knot) and
 // ub (last knot), reaching (z - pz) * u at height z.  Returned: the
