@@ -679,25 +679,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
 // Adds the pieces of every run of a launch, in piece order, into the run's
 // bin: the launch's first run is stored or added to as O says for the
 // launch's first bin, the others as for its later bins.
-__global__ void k_add_pieces(Sched W, int j0, int j1, const SegConst *__restrict__ segs, int64_t n, BinOut O)
+// One point and run (the y index) per thread.  A round trip to rows that other
+// XCDs have just written takes 2 us, so 24 rows are asked for at once, the
+// run's bin beside them (16,384 points, 20 rows: 9.3 -> 4.7 us).
+constexpr int kRowsInFlight = 24;
+
+__global__ __launch_bounds__(64) void k_add_pieces(Sched W, int j0, int j1, const SegConst *__restrict__ segs, int64_t n,
+                                                   BinOut O)
 {
     const int sub = W.sub > 1 ? W.sub : 1;
-    const int runs = (int)W.n_parts / sub;
-    const int64_t total = (int64_t)runs * n;
-    const int64_t stride = (int64_t)n_wg() * wg_size();
-    for (int64_t t = (int64_t)wg_id() * wg_size() + tid(); t < total; t += stride) {
-        const int r = (int)(t / n);
-        const int64_t i = t - (int64_t)r * n;
-        int cnt = 0;
-        double mins = 0.0;
-#pragma unroll 8
-        for (int p = r * sub; p < (r + 1) * sub; ++p) {
-            cnt += O.pcnt[(int64_t)p * n + i];
-            mins += O.pmin[(int64_t)p * n + i];
+    const int r = wg_id_y();
+    const int64_t i = (int64_t)wg_id() * 64 + tid();
+    if (i >= n) return;
+    int cnt = 0;
+    double mins = 0.0;
+    for (int p0 = r * sub; p0 < (r + 1) * sub; p0 += kRowsInFlight) {
+        int c[kRowsInFlight];
+        double m[kRowsInFlight];
+#pragma unroll
+        for (int u = 0; u < kRowsInFlight; ++u) {
+            const int64_t row = (int64_t)min(p0 + u, (r + 1) * sub - 1) * n + i;
+            c[u] = O.pcnt[row];
+            m[u] = O.pmin[row];
         }
-        const int bin = segs[max(W.part_start[r], j0)].bin;
-        put_bin(O, (int64_t)bin * n + i, (r == 0 ? O.fresh_first : O.fresh_rest) != 0, cnt, mins);
+#pragma unroll
+        for (int u = 0; u < kRowsInFlight; ++u) {
+            const bool in = p0 + u < (r + 1) * sub;
+            cnt += in ? c[u] : 0;
+            mins += in ? m[u] : 0.0;
+        }
     }
+    const int bin = segs[max(W.part_start[r], j0)].bin;
+    put_bin(O, (int64_t)bin * n + i, (r == 0 ? O.fresh_first : O.fresh_rest) != 0, cnt, mins);
 }
 
 // Continuous shadow (Sec. 3.1) over one window [w0, w1] whose occluded set
@@ -1575,9 +1588,8 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
         SA_CHECK_LAUNCH("accrual kernel");
         if (W.sub > 1) {
-            const int64_t total = (int64_t)(W.n_parts / W.sub) * pts.n;
-            hipLaunchKernelGGL(k_add_pieces, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65536)), dim3(256),
-                               0, st, W, (int)j0, j1, (const SegConst *)p.segs, pts.n, O);
+            hipLaunchKernelGGL(k_add_pieces,
+                               dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W, (int)j0, j1, (const SegConst *)p.segs, pts.n, O);
             SA_CHECK_LAUNCH("accrual piece sums");
         }
         rc = run_spill(s, p, views, (int)j0, P, scale, counts, minutes, minutes64, q, st, err);

@@ -26,6 +26,7 @@ struct sa_ctx {
     sa::Scratch scratch_sam;      // one segment's raster shadow accrual map
     sa::Scratch scratch_grad;     // FP64 height-gradient accumulator
     sa::Scratch scratch_w;        // per-bin weights of a region score
+    sa::Scratch scratch_edit;     // staging of long height edits
     sa::Scratch scratch_piece;    // per-piece sums of accrual launches on few tiles
     sa::Scratch scratch_fan;      // node views of the sampled form's fans (their own: a graph captured
                                   // over accrual calls keeps scratch_seg)
@@ -206,6 +207,7 @@ void sa_destroy(sa_ctx *ctx)
     (void)hipFree(ctx->scratch_sam.ptr);
     (void)hipFree(ctx->scratch_grad.ptr);
     (void)hipFree(ctx->scratch_w.ptr);
+    (void)hipFree(ctx->scratch_edit.ptr);
     (void)hipFree(ctx->scratch_piece.ptr);
     (void)hipFree(ctx->scratch_fan.ptr);
     (void)hipFree(ctx->scratch_mask.ptr);
@@ -363,20 +365,29 @@ sa_status sa_scene_set_heights(sa_ctx *ctx, sa_scene *scene, int32_t n, const in
         return SA_OK;
     }
     std::vector<int32_t> pos(n);
+    std::vector<float> hv(h, h + n);
     for (int32_t k = 0; k < n; ++k) {
         if (ids[k] < 0 || ids[k] >= scene->d.n_b)
             return fail(ctx, SA_ERR_INVALID_ARG, "sa_scene_set_heights: building id out of range");
         if (!(h[k] > 0.f) || !std::isfinite(h[k])) return fail(ctx, SA_ERR_GEOMETRY, "height must be > 0");
         pos[k] = scene->rank_h[ids[k]];
     }
-    // heights are few: scatter them with small copies, then refit on device
-    for (int32_t k = 0; k < n; ++k) {
-        hipError_t e = hipMemcpyAsync(scene->d.height + pos[k], h + k, sizeof(float), hipMemcpyHostToDevice,
-                                      ctx->stream);
-        if (e != hipSuccess) return hip_fail(ctx, e, "sa_scene_set_heights: copy");
+    // a building named twice keeps its last height
+    std::vector<int32_t> last(pos);
+    std::sort(last.begin(), last.end());
+    if (std::adjacent_find(last.begin(), last.end()) != last.end()) {
+        std::map<int32_t, float> by;
+        for (int32_t k = 0; k < n; ++k) by[pos[k]] = h[k];
+        pos.clear();
+        hv.clear();
+        for (const auto &e : by) {
+            pos.push_back(e.first);
+            hv.push_back(e.second);
+        }
     }
     std::string err;
-    sa_status rc = sa::scene_refit(scene->d, ctx->stream, err);
+    sa_status rc = sa::scene_edit_heights(scene->d, (int32_t)pos.size(), pos.data(), hv.data(), ctx->scratch_edit,
+                                          ctx->stream, err);
     if (rc != SA_OK) return fail(ctx, rc, "sa_scene_set_heights: " + err);
     float mh = 0.f;
     for (int32_t k = 0; k < n; ++k) mh = std::max(mh, h[k]);
@@ -556,7 +567,7 @@ void merge_segments(std::vector<sa::SegConst> &segs, const std::vector<std::arra
 constexpr double kFanArc = 30.0 * M_PI / 180.0;
 
 void fan_chunks(const std::vector<sa::SampleConst> &samples, std::vector<sa::FanChunk> &chunks,
-                std::vector<sa::FanDirs> &dirs)
+                std::vector<sa::FanDirs> &dirs, std::vector<sa::ChunkSum> &sums)
 {
     for (size_t k0 = 0; k0 < samples.size();) {
         const sa::SampleConst &a = samples[k0];
@@ -615,19 +626,18 @@ void fan_chunks(const std::vector<sa::SampleConst> &samples, std::vector<sa::Fan
         ch.mdy = mid.dy;
         ch.first = (int32_t)k0;
         ch.n = (int32_t)(k1 - k0);
-        ch.bin = a.tag & sa::kBinMask;
-        ch.day_start = (a.tag & sa::kDayStart) ? 1 : 0;
-        ch.even = 1;
-        ch.weight = a.w;
+        sa::ChunkSum cs{ch.first, ch.n | ((a.tag & sa::kDayStart) ? sa::kSumDayStart : 0) | sa::kSumEven,
+                        a.tag & sa::kBinMask, a.w};
         for (int i = 0; i < sa::kFanInstants; ++i) {
             const sa::SampleConst &s = samples[std::min(k0 + i, k1 - 1)];
             dd.dx[i] = s.dx;
             dd.dy[i] = s.dy;
             dd.dz[i] = s.dz;
-            if (s.w != a.w) ch.even = 0;
+            if (s.w != a.w) cs.n_flags &= ~sa::kSumEven;
         }
         chunks.push_back(ch);
         dirs.push_back(dd);
+        sums.push_back(cs);
         k0 = k1;
     }
 }
@@ -791,15 +801,16 @@ sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, s
     p->d.sample_runs.start.push_back((int32_t)samples.size());
     std::vector<sa::FanChunk> chunks;
     std::vector<sa::FanDirs> dirs;
-    fan_chunks(samples, chunks, dirs);
+    std::vector<sa::ChunkSum> sums;
+    fan_chunks(samples, chunks, dirs, sums);
     p->d.n_chunks = (int32_t)chunks.size();
     std::vector<char> has(n_bins, 0);
     p->d.chunk_bins_unique = true;
     for (size_t c = 0; c < chunks.size(); ++c) {
-        const int b = chunks[c].bin;
+        const int b = sums[c].bin;
         p->d.chunk_first.push_back(chunks[c].first);
-        p->d.chunk_day_start.push_back((char)chunks[c].day_start);
-        if (c > 0 && chunks[c - 1].bin == b) continue;
+        p->d.chunk_day_start.push_back((sums[c].n_flags & sa::kSumDayStart) != 0);
+        if (c > 0 && sums[c - 1].bin == b) continue;
         if (has[b]) p->d.chunk_bins_unique = false;
         has[b] = 1;
         p->d.chunk_runs.start.push_back((int32_t)c);
@@ -839,6 +850,9 @@ sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, s
         if (e == hipSuccess) e = hipMalloc((void **)&p->d.chunk_dirs, sizeof(sa::FanDirs) * dirs.size());
         if (e == hipSuccess)
             e = hipMemcpy(p->d.chunk_dirs, dirs.data(), sizeof(sa::FanDirs) * dirs.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d.chunk_sums, sizeof(sa::ChunkSum) * sums.size());
+        if (e == hipSuccess)
+            e = hipMemcpy(p->d.chunk_sums, sums.data(), sizeof(sa::ChunkSum) * sums.size(), hipMemcpyHostToDevice);
     }
     for (sa::BinRuns *R : {&p->d.seg_runs, &p->d.sample_runs, &p->d.chunk_runs}) {
         if (e != hipSuccess || R->start.size() < 2) continue;
@@ -888,6 +902,7 @@ void sa_path_destroy(sa_path *path)
     (void)hipFree(path->d.segs);
     (void)hipFree(path->d.chunks);
     (void)hipFree(path->d.chunk_dirs);
+    (void)hipFree(path->d.chunk_sums);
     (void)hipFree(path->d.seg_runs.dev);
     (void)hipFree(path->d.sample_runs.dev);
     (void)hipFree(path->d.chunk_runs.dev);
@@ -1151,6 +1166,7 @@ sa_status sa_region_score(sa_ctx *ctx, const sa_path *path, const float *values,
     if (ctx->scratch_w.bytes < need) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->scratch_w.ptr);
+    (void)hipFree(ctx->scratch_edit.ptr);
         ctx->scratch_w.ptr = nullptr;
         ctx->scratch_w.bytes = 0;
         hipError_t e = hipMalloc(&ctx->scratch_w.ptr, need);

@@ -106,12 +106,18 @@ struct alignas(64) FanChunk {
     float f[8];
     float mdx, mdy;     // middle direction (visit order)
     int32_t first, n;   // its instants [first, first + n)
-    int32_t bin;
-    int32_t day_start;  // it holds its day's first instant
-    int32_t even;       // every instant weighs the same ...
-    float weight;       // ... this much (minutes)
+    int32_t pad[4];
 };
 static_assert(sizeof(FanChunk) == 64, "one line");
+
+// What adding up a chunk's shadowed instants takes, four to a line.
+struct alignas(16) ChunkSum {
+    int32_t first;
+    int32_t n_flags;  // instants | kSumDayStart: it holds its day's first instant | kSumEven: they weigh the same
+    int32_t bin;
+    float weight;     // of each instant, if even (minutes)
+};
+constexpr int32_t kSumDayStart = 1 << 8, kSumEven = 1 << 9;
 
 // Their directions; entries past n repeat the last one.
 struct alignas(64) FanDirs {
@@ -134,6 +140,15 @@ struct DeviceScene {
     int32_t *parent = nullptr;   // [n_nodes + n_b] parent*2+side of interior nodes then leaves
     int32_t *flags = nullptr;    // [n_nodes] refit arrival counters
     float4 *pbox = nullptr;      // [n_b] prism footprint boxes, hierarchy order
+    int32_t *leaf_depth = nullptr;  // [n_b] nodes above each prism, hierarchy order
+};
+
+// A few heights by hierarchy position, passed to a kernel by value.
+constexpr int kMaxEdits = 64;
+struct HeightEdits {
+    int32_t n;
+    int32_t pos[kMaxEdits];
+    float h[kMaxEdits];
 };
 
 // Raster shadow accrual map (Sec. 4) of one segment: the shadow plane
@@ -190,6 +205,7 @@ struct DevicePath {
     int32_t n_chunks = 0;              // fans of instants of the sampled form
     FanChunk *chunks = nullptr;        // [n_chunks]
     FanDirs *chunk_dirs = nullptr;     // [n_chunks]
+    ChunkSum *chunk_sums = nullptr;    // [n_chunks]
     BinRuns chunk_runs;                // runs of equal bins over the chunks
     bool chunk_bins_unique = false;    // host: no bin has two runs
     bool chunk_bins_all = false;       // host: and every bin has one
@@ -203,10 +219,22 @@ struct DevicePath {
     std::vector<double> sample_t, sample_w;
 };
 
+// Scratch owned by a context (grown on demand, freed with it), or a fixed
+// buffer the library never grows or frees (fixed = true).
+struct Scratch {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    bool fixed = false;
+};
+
 // Host-side builders implemented in the .hip sources.
 sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t *voff,
                       const float *xy, const float *h, std::string &err);
 sa_status scene_refit(DeviceScene &s, hipStream_t st, std::string &err);
+// Heights h of the prisms at hierarchy positions pos (host arrays, no position
+// twice) into the scene, with the tops above them; scr: staging of long edits.
+sa_status scene_edit_heights(DeviceScene &s, int32_t n, const int32_t *pos, const float *h, Scratch &scr, hipStream_t st,
+                             std::string &err);
 // Heights from device arrays ids / h (original ids) into the scene, on the
 // stream; an id out of range or a height that is not a positive finite
 // number is skipped and raises bit 2 of *flag.
@@ -220,14 +248,6 @@ struct PointsView {
     int64_t n;
     const float *x, *y, *z, *nx, *ny;
     const int32_t *owner;
-};
-
-// Scratch owned by a context (grown on demand, freed with it), or a fixed
-// buffer the library never grows or frees (fixed = true).
-struct Scratch {
-    void *ptr = nullptr;
-    size_t bytes = 0;
-    bool fixed = false;
 };
 
 struct SpillQueue {
