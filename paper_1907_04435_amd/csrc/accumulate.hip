@@ -951,6 +951,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         double bf = 0.0;
         int bin = jb > ja ? ld(segs + ja).bin : 0;
+        // Sums of the bin by building: lane l holds the one of a building with
+        // rank l modulo 64, until another takes its place or the bin ends.  An
+        // atomic per leaf before: waves of an XCD meet the same few buildings
+        // at the same time, and their adds to one word queue up (600 prisms
+        // and 20,000 points 226 -> 190 us, 60,000 points 420 -> 379; 5,000
+        // prisms and 300,000 points 1,089 -> 1,065).
+        int key = -1;
+        double held = 0.0;
+        auto flush_held = [&]() {
+            if (key >= 0) atomicAdd(contrib + (int64_t)bin * n_b + order[key], held);
+            key = -1;
+        };
         auto flush_backface = [&]() {
             const uint64_t has = ballot(bf != 0.0);
             if (!has) return;
@@ -969,10 +981,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         for (int j = ja; j < jb; j += step) {
             const SegConst g = ld(segs + j);
             if (g.bin != bin) {
+                flush_held();
                 flush_backface();
                 bin = g.bin;
             }
-            double *row = contrib + (int64_t)g.bin * n_b;
             if (active && q.own >= 0) {
                 float a, b;
                 if (backface_interval(q.nx, q.ny, g, 0.f, g.theta, 1.f, 0.f, g.cth, g.sth, a, b))
@@ -990,12 +1002,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
                 // the wave's total for this building (every lane is active
                 // here: the traversal runs on the whole wave)
                 const float v = wave_sum(lane_in(hit) ? (b - a) * g.wrate * wt : 0.f);
-                if (first_active_lane() && v != 0.f) atomicAdd(&row[order[prim]], (double)v);
+                if (lane == (prim & 63)) {
+                    if (key != prim) {
+                        flush_held();
+                        key = prim;
+                        held = 0.0;
+                    }
+                    held += (double)v;
+                }
                 return 0;  // no lane retires: every building counts
             };
             packet_traverse_seg<false>((cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes), (cint *)voff_g, stack,
                                        ballot(active), ft, leaf, none);
         }
+        flush_held();
         flush_backface();
     }
 }
