@@ -81,7 +81,7 @@ sa_status sa_set_stream(sa_ctx *ctx, void *hip_stream);
  * measures them per device and sets them; zero fields keep the defaults. */
 typedef struct {
     int32_t accrual_segments_per_launch; /* accrual form: the most path segments one launch covers
-                                            (their per-segment hierarchy views are the launch's working
+                                            (their per-segment views are the launch's working
                                             set); 0 = as many as the view budget allows */
     int32_t batched_grid_blocks;         /* sa_accumulate_batched: blocks of the persistent launch when
                                             opts->grid_blocks is 0; 0 = 2048 */
@@ -274,9 +274,9 @@ typedef struct {
                             launch (0 = default 2048); ignored elsewhere */
     /* Optional device uint64 [8], added to (not cleared): when non-NULL the
      * launch runs an instrumented instantiation that counts, per lane, the
-     * work its own traversal needed -- [0] child-box tests, [1] prism tests,
+     * work its own traversal needed -- [0] box tests, [1] prism tests,
      * [2] footprint edges visited in prism tests, [3] interval insertions,
-     * [4] node fetches (per wave), [5] lanes x units (point-instants or
+     * [4] box tests (per wave), [5] lanes x units (point-instants or
      * point-segments), [6] spilled windows, [7] leaf visits (per wave).  Slower; for
      * measurement only. */
     uint64_t *work;
@@ -317,7 +317,7 @@ typedef struct {
  * added with float atomics in no fixed order.
  * The accrual form (here, and in sa_accumulate_batched, sa_grad_heights
  * and sa_building_contribution) keeps a per-segment view of the hierarchy
- * (64 bytes per node and segment, at most 1 GiB per launch; longer paths
+ * (32 bytes per prism and segment, at most 1 GiB per launch; longer paths
  * run as several launches, the continuous shadow one day at least) in
  * memory the context owns: grown on first need with the stream
  * synchronised, kept until sa_destroy.  Under stream capture make one
@@ -335,18 +335,18 @@ sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): sa_accumulate with the same arguments, outputs and results,
  * except that it allocates nothing.  The accrual form's per-segment
- * hierarchy views (64 bytes per node and segment) go to a fixed device
+ * views (32 bytes per prism and segment) go to a fixed device
  * array of SA_NOALLOC_SCRATCH_BYTES that every device the library runs on
  * holds from its first sa_create until the process ends, and the spill
  * queue is the one sa_create made for the context; the sampled form needs
  * no scratch.  A launch covers as many segments as the array holds
- * (SA_NOALLOC_SCRATCH_BYTES / (64 x interior nodes): 52 on a 20,000-prism
+ * (SA_NOALLOC_SCRATCH_BYTES / (33 x prisms): 101 on a 20,000-prism
  * scene), longer paths run as several launches; with opts->longest a
  * launch must hold a whole day.  Every call on one device shares the array
  * and its contents are rebuilt by each launch, so calls that overlap on one
  * device (other streams or contexts) race and must be ordered by the
  * caller.  Errors: as sa_accumulate; CAPACITY (before any work is
- * enqueued) when one segment's views (a scene of more than about 1M
+ * enqueued) when one segment's views (a scene of more than about 2M
  * prisms) or, with longest, one day's views exceed the array; DEVICE if the
  * array's address could not be obtained at sa_create. */
 #define SA_NOALLOC_SCRATCH_BYTES (64ll << 20)

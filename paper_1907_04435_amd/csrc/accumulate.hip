@@ -10,6 +10,7 @@
 #include "sa_internal.h"
 #include "traverse.h"
 #include "unit_sched.h"
+#include "views.h"
 
 namespace sa {
 namespace {
@@ -19,12 +20,12 @@ constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
 constexpr int kSpillBlocks = 1024;
 constexpr int64_t kChunkWork = 4000000000ll;  // point-segments per accrual launch
-// Per-segment node views per launch.  A launch has its set-up, its spilled
+// Views per launch.  A launch has its set-up, its spilled
 // windows and a last unit that others wait for: a year on 45,000 prisms and
-// 500,000 points (97 launches of 256 MiB) takes 236, 219 and 207 ms at 256,
-// 512 and 1024 MiB.  Where that much cannot be had, down to kLeastNodeBytes.
-constexpr int64_t kSegNodeBytes = 1024ll << 20;
-constexpr int64_t kLeastNodeBytes = 256ll << 20;
+// 500,000 points takes 236, 219 and 207 ms in launches of 150, 300 and 600
+// segments (views of 256, 512 and 1024 MiB then, of half as much now).  Where that much cannot be had, down to kLeastViewBytes.
+constexpr int64_t kViewBytes = 1024ll << 20;
+constexpr int64_t kLeastViewBytes = 256ll << 20;
 constexpr int64_t kPieceBytes = 256ll << 20;    // per-piece sums of an accrual launch on few tiles
 
 // Per-bin outputs of the accrual kernels.  A bin whose first segment lies in
@@ -486,40 +487,39 @@ __device__ __forceinline__ void measure(const Union4 &U, const SegConst &g, floa
     cnt += c * g.mult;
 }
 
-// The occluded set of every live lane's point over its window of segment g:
-// back-face term, then the packet fan traversal.  On return `ov` marks
-// lanes whose set needed more than four pieces.
-// The hierarchy as seen from the current segment: its per-segment node
-// views (SegFan: six compares per child), the vertex offsets of the
-// leaves, and the view the walk starts at.
+// The scene as the current segment sees it, the vertex offsets of the leaves,
+// and the heights.
 struct SegSrc {
-    cSegNode *nodes;
+    const ViewEntry *view;
+    int n_b;
     cint *voff;
-    int root;  // byte offset of the root's view
+    TileFan *tile;  // the wave's slot
+    cfloat *height;
 };
 
+// The occluded set of every active lane's point over its window of segment g:
+// back-face term, then the walk of the view (which takes the whole wave).  On
+// return `ov` marks lanes whose set needed more than four pieces.
 template <bool kCount>
-__device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cfloat4 *verts, cfloat *height,
-                                               const SegConst &g, const LanePoint &q, bool active, float w0,
-                                               float w1, Union4 &U, bool &ov, Work &wk)
+__device__ __forceinline__ void accrue_segment(const SegSrc &src, cfloat4 *verts, const SegConst &g, const LanePoint &q,
+                                               bool active, float w0, float w1, Union4 &U, bool &ov, Work &wk)
 {
     union_clear(U);
     ov = false;
-    if (!active) return;
     float W0u, W0v, W1u, W1v;
     window_dirs(g, w0, w1, W0u, W0v, W1u, W1v);
-    bool live = true;
-    if (q.own >= 0) {
+    bool live = active;
+    if (active && q.own >= 0) {
         float a, b;
         if (backface_interval(q.nx, q.ny, g, w0, w1, W0u, W0v, W1u, W1v, a, b)) {
             union_first(U, a, b);
             live = !(a <= w0 && b >= w1);
         }
     }
-    if (src.nodes == nullptr) return;
-    // liveness and overflow as wave masks (see packet_traverse)
+    if (src.view == nullptr) return;
+    // liveness and overflow as wave masks (see walk_view)
     uint64_t ovm = 0;
-    auto leaf_m = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
+    auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
         const uint64_t gm = want & ballot(prim != q.own);
         if (!gm) return 0;
         if constexpr (kCount) {
@@ -528,8 +528,9 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
             wk.leaves += first_active_lane() ? 1u : 0u;
         }
         float a, b, da, db;
-        const uint64_t hit = prism_interval<false>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g, w0, w1,
-                                                   W0u, W0v, W1u, W1v, a, b, da, db);
+        const float H = ld(src.height + prim);
+        const uint64_t hit = prism_interval<false>(verts, voff, m, H, gm, q.px, q.py, q.pz, g, w0, w1, W0u, W0v, W1u,
+                                                   W1v, a, b, da, db);
         if constexpr (kCount) wk.inserts += lane_in(hit) ? 1u : 0u;
         if (!hit) return 0;
         const uint64_t over = union_insert_mask(U, a, b, hit);
@@ -538,26 +539,11 @@ __device__ __forceinline__ void accrue_segment(SegSrc src, StackEntry *stack, cf
         return over | (hit & ballot(U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1));
     };
     const SegFan ft(g, q.px, q.py, q.pz);
-    packet_traverse_seg<kCount>(src.nodes, src.voff, stack, ballot(live), ft, leaf_m, wk, src.root);
+    walk_view<kCount>(src.view, src.n_b, src.voff, src.tile, ballot(live), ft, leaf, wk);
     ov = lane_in(ovm);
 }
 
 __global__ void k_clear_state(LaunchState L) { clear_state(L, tid()); }
-
-// The per-segment node views of segments [j0, j1): one thread per
-// (segment, node), written to out[(j - j0) * stride + node].  Blocks of 256.
-__global__ void k_seg_nodes(const Node *__restrict__ nodes, int n_nodes, const SegConst *__restrict__ segs, int j0,
-                            int j1, int64_t stride, SegNode *__restrict__ out, LaunchState L)
-{
-    const int64_t t = (int64_t)wg_id() * wg_size() + tid();
-    clear_state(L, t);
-    if (t >= (int64_t)(j1 - j0) * n_nodes) return;
-    const int jj = (int)(t / n_nodes);
-    const int node = (int)(t - (int64_t)jj * n_nodes);
-    const Node nd = nodes[node];
-    const SegConst &g = segs[j0 + jj];
-    out[jj * stride + node] = make_view(nd, view_ref(nd.left), view_ref(nd.right), fan_geom(g), g.mdx, g.mdy);
-}
 
 // Roof-covered: inside a footprint (other than the point's own building)
 // and not above that roof -- shadowed from every direction.  Without kTops
@@ -591,7 +577,7 @@ __device__ __forceinline__ bool roof_covered(cNode *nodes, StackEntry *stack, cf
 // compare-chain latency of the traversal loop.
 template <bool kCount, int kOcc>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))) void k_accrual(
-    const Node *nodes_g, const SegNode *snodes_g, int n_nodes, const int32_t *voff_g, const float4 *verts_g,
+    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, SpillArgs S,
     uint64_t *work)
 {
@@ -616,6 +602,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
     }
     __syncthreads();
     StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     int kx = 0;
     Unit un;
@@ -645,9 +633,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
             }
             Union4 U;
             bool ov;
-            const SegSrc src{snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr,
-                             (cint *)voff_g, 0};
-            accrue_segment<kCount>(src, stack, verts, height, g, q, valid && !covered, 0.f, g.theta, U, ov, wk);
+            const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b, (cint *)voff_g,
+                             tile, height};
+            accrue_segment<kCount>(src, verts, g, q, valid && !covered, 0.f, g.theta, U, ov, wk);
             if constexpr (kCount) {
                 wk.units += valid ? 1u : 0u;
                 wk.spills += (valid && ov) ? 1u : 0u;
@@ -742,7 +730,7 @@ __device__ __forceinline__ void runs_update(const Union4 &U, float w0, float w1,
 // waves per SIMD (the compiler fits the kernel in 72 VGPRs) measured 4 %
 // faster than the six its natural allocation allows.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_accrual_runs(
-    const Node *nodes_g, const SegNode *snodes_g, int n_nodes, const int32_t *voff_g, const float4 *verts_g,
+    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, float *longest,
     uint32_t *overflow)
 {
@@ -768,6 +756,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     }
     __syncthreads();
     StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     Work none{0, 0, 0, 0, 0, 0, 0};
     int kx = 0;
@@ -822,9 +812,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 const float w1 = fminf(w0 + s, g.theta);
                 Union4 U;
                 bool ov;
-                const SegSrc src{snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr,
-                                 (cint *)voff_g, 0};
-                accrue_segment<false>(src, stack, verts, height, g, q, pending, w0, w1, U, ov, none);
+                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b,
+                                 (cint *)voff_g, tile, height};
+                accrue_segment<false>(src, verts, g, q, pending, w0, w1, U, ov, none);
                 if (pending) {
                     if (ov) {
                         if (s < g.theta * (1.0f / 4096.0f)) {
@@ -857,7 +847,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
 // The lanes' measures are summed across the wave and added with one atomic
 // per output.  One launch: as three rounds over two queues, with their
 // clears, it was seven (4 us each and the gaps where nothing is queued).
-__global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int n_nodes, int j0, const int32_t *voff_g,
+__global__ __launch_bounds__(kThreads) void k_spill(const ViewEntry *views_g, int n_b, int j0, const int32_t *voff_g,
                                                     const float4 *verts_g, const float *height_g,
                                                     const SegConst *segs_g, PointArgs P, float scale, int32_t *counts,
                                                     float *minutes, double *minutes64, const int4 *in,
@@ -866,10 +856,10 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
     __shared__ SpillWindow s_wait[kWaves][kSpillWait];
-    StackEntry *stack = s_stack[tid() >> 6];
     SpillWindow *wait = s_wait[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     const int64_t total = min((int32_t)*in_count, cap);
     const int64_t stride = (int64_t)n_wg() * kWaves;
@@ -879,8 +869,8 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
         const int j = uniform(en.y);
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
-        const SegSrc src{snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr,
-                         (cint *)voff_g, 0};
+        const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b, (cint *)voff_g,
+                         tile, height};
         SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
         double mins = 0.0;
         int cnt = 0;
@@ -890,7 +880,7 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
             Union4 U;
             bool ov;
             Work none{0, 0, 0, 0, 0, 0, 0};
-            accrue_segment<false>(src, stack, verts, height, g, q, true, w0, w1, U, ov, none);
+            accrue_segment<false>(src, verts, g, q, true, w0, w1, U, ov, none);
             if (!ov) measure(U, g, w0, w1, w1 >= g.theta, mins, cnt);
             if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
         }
@@ -915,16 +905,15 @@ __global__ __launch_bounds__(kThreads) void k_spill(const SegNode *snodes_g, int
 // the wave and added with one FP64 atomic; a back-facing wall counts for
 // the point's own building.  Eight waves per SIMD (56 VGPRs): 17.5 ms on
 // the block scene against 19.4 at the compiler's seven.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_contrib(const SegNode *snodes_g, int n_nodes, const int32_t *voff_g,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_contrib(const ViewEntry *views_g, int n_b, const int32_t *voff_g,
                                                       const float4 *verts_g, const float *height_g,
                                                       const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P,
-                                                      const float *weight, const int32_t *order, int n_b,
+                                                      const float *weight, const int32_t *order,
                                                       double *contrib)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
     __shared__ int s_W[sizeof(Sched) / 4];
     __shared__ int s_P[sizeof(PointArgs) / 4];
     if (tid() == 0) {
@@ -932,7 +921,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         lds_park((lds_int *)s_P, P);
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     Work none{0, 0, 0, 0, 0, 0, 0};
     int kx = 0;
@@ -990,14 +980,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
                 if (backface_interval(q.nx, q.ny, g, 0.f, g.theta, 1.f, 0.f, g.cth, g.sth, a, b))
                     bf += (double)((b - a) * g.wrate * wt);
             }
-            if (snodes_g == nullptr) continue;
+            if (views_g == nullptr) continue;
             const SegFan ft(g, q.px, q.py, q.pz);
             auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
                 const uint64_t gm = want & ballot(prim != q.own);
                 if (!gm) return 0;
                 float a, b, da, db;
-                const uint64_t hit = prism_interval<false>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g,
-                                                           0.f, g.theta, 1.f, 0.f, g.cth, g.sth, a, b, da, db);
+                const uint64_t hit = prism_interval<false>(verts, voff, m, ld(height + prim), gm, q.px, q.py, q.pz, g, 0.f,
+                                                           g.theta, 1.f, 0.f, g.cth, g.sth, a, b, da, db);
                 if (!hit) return 0;
                 // the wave's total for this building (every lane is active
                 // here: the traversal runs on the whole wave)
@@ -1012,8 +1002,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
                 }
                 return 0;  // no lane retires: every building counts
             };
-            packet_traverse_seg<false>((cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes), (cint *)voff_g, stack,
-                                       ballot(active), ft, leaf, none);
+            walk_view<false>(views_g + (int64_t)(j - j0) * view_shape(n_b).all, n_b, (cint *)voff_g, tile, ballot(active),
+                             ft, leaf, none);
         }
         flush_held();
         flush_backface();
@@ -1022,24 +1012,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 
 // ------------------------------------------------------------------ batched
 // Variant v of the scene differs from the base only in the heights of a few
-// buildings, so its hierarchy differs only in the box tops of those leaves'
-// ancestors ("changed nodes").  Every variant shares the base's views
-// everywhere else and has its own copies of the views of its changed nodes,
-// whose child references point to the variant's copy where the child changed
-// too and to the base view otherwise.  Every ancestor of a changed node is
-// changed, so a walk started at the variant's copy of the root sees exactly
-// the variant's hierarchy.  Copies of variant v live at view index
-// n_nodes + v * cmax + c.
+// buildings.  One set of views serves them all: it is built for the tallest a
+// prism is in any of them, so a walk passes every prism that meets a point's
+// fan in its variant (boxes only decide what is tested), and the leaf takes
+// the variant's own height.
 
-// Heights of the variants (the base's), their changed-node maps (none) and
-// the tile offsets: tile_off[v] = first tile of variant v, 64 points per tile.
-__global__ void k_var_copy(const float *__restrict__ base_h, int n_b, int n_nodes, int V, float *__restrict__ vh,
-                           int32_t *__restrict__ vmap, const int64_t *__restrict__ var_off, int64_t *__restrict__ tile_off)
+// Heights of the variants (the base's), the greatest of each prism (the
+// base's) and the tile offsets: tile_off[v] = first tile of variant v, 64
+// points per tile.
+__global__ void k_var_copy(const float *__restrict__ base_h, int n_b, int V, float *__restrict__ vh, float *__restrict__ tops,
+                           const int64_t *__restrict__ var_off, int64_t *__restrict__ tile_off)
 {
     const int64_t stride = (int64_t)n_wg() * wg_size();
     const int64_t t0 = (int64_t)wg_id() * wg_size() + tid();
     for (int64_t t = t0; t < (int64_t)V * n_b; t += stride) vh[t] = base_h[t % n_b];
-    for (int64_t t = t0; t < (int64_t)V * n_nodes; t += stride) vmap[t] = -1;
+    for (int64_t t = t0; t < n_b; t += stride) tops[t] = base_h[t];
     if (t0 < 64) {  // one wave, 64 variants at a time
         int64_t base = 0;
         for (int v0 = 0; v0 < V; v0 += 64) {
@@ -1057,119 +1044,22 @@ __global__ void k_var_copy(const float *__restrict__ base_h, int n_b, int n_node
     }
 }
 
-// One variant's chain walks, a lane per changed building (further ones in
-// turn): where the chain stands and the top it carries.
-struct VarChain {
-    int32_t link;   // parent link of the node below: node * 2 + side
-    int32_t depth;  // ancestors of the leaf
-    float z;        // its subtree's top
-    int32_t pad;
-};
-
-// One wave per variant: heights (bad ones skipped and flagged), the list of
-// changed nodes vlist[v][0, vcount[v]) with their place in it (vmap[v][node])
-// and their refitted child tops vz, and the view the walk starts at
-// (vroot[v], a byte offset).  The chains climb together, a level of the tree
-// at a time: all of a level's tops are written before any is read.  With one
-// thread per variant and a search of the list per node, lists, references,
-// refit and a copy of all nodes per variant took 0.95 ms for 32 variants of 8
-// buildings on 20,000 prisms; this and k_var_copy take 0.05 ms.
-__global__ __launch_bounds__(64) void k_var_setup(int k, const int32_t *__restrict__ ids, const float *__restrict__ h,
-                                                  const int32_t *__restrict__ rank, const int32_t *__restrict__ parent,
-                                                  int n_int, int n_b, int n_nodes, int cmax,
-                                                  const Node *__restrict__ nodes, float *vh, int32_t *vmap, int32_t *vlist,
-                                                  float2 *vz, VarChain *chains, int32_t *__restrict__ vcount,
-                                                  int32_t *__restrict__ vroot, uint32_t *flag)
-{
-    __shared__ int s_count, s_depth;
-    const int v = wg_id();
-    const int lane = tid();
-    float *H = vh + (int64_t)v * n_b;
-    int32_t *map = vmap + (int64_t)v * n_nodes, *L = vlist + (int64_t)v * cmax;
-    float2 *Z = vz + (int64_t)v * cmax;
-    VarChain *C = chains + (int64_t)v * k;
-    if (lane == 0) s_count = s_depth = 0;
-    for (int j = lane; j < k; j += 64) {
-        const int id = ids[(int64_t)v * k + j];
-        const float hv = h[(int64_t)v * k + j];
-        if (id < 0 || id >= n_b || !(hv > 0.f)) atomicOr(flag, 4u);
-        else H[rank[id]] = hv;
-    }
-    __syncthreads();
-    for (int j = lane; j < k; j += 64) {
-        const int id = ids[(int64_t)v * k + j];
-        VarChain c{-1, 0, 0.f, 0};
-        if (id >= 0 && id < n_b) {
-            const int prim = rank[id];
-            c.link = parent[n_int + prim];
-            c.z = pad_hi(H[prim]);
-            bool listing = true;  // until a node that another chain has listed, with its ancestors
-            for (int pp = c.link; pp >= 0 && c.depth < 64; ++c.depth) {
-                const int a = pp >> 1;
-                if (listing) {
-                    listing = atomicCAS(&map[a], -1, -2) == -1;
-                    if (listing) {
-                        const int at = atomicAdd(&s_count, 1);
-                        L[at] = a;
-                        Z[at] = make_float2(nodes[a].lz1, nodes[a].rz1);
-                        map[a] = at;
-                    }
-                }
-                pp = parent[a];
-            }
-        }
-        C[j] = c;
-        atomicMax(&s_depth, c.depth);
-    }
-    __syncthreads();
-    for (int level = s_depth - 1; level >= 0; --level) {
-        for (int j = lane; j < k; j += 64) {
-            const VarChain c = C[j];
-            if (c.depth <= level) continue;
-            float *z = (float *)(Z + map[c.link >> 1]);
-            z[c.link & 1] = c.z;
-        }
-        __syncthreads();
-        for (int j = lane; j < k; j += 64) {
-            VarChain c = C[j];
-            if (c.depth <= level) continue;
-            const float2 z = Z[map[c.link >> 1]];
-            c.z = fmaxf(z.x, z.y);
-            c.link = parent[c.link >> 1];
-            C[j] = c;
-        }
-        __syncthreads();
-    }
-    if (lane == 0) {
-        vcount[v] = s_count;
-        vroot[v] = s_count > 0 ? (n_nodes + v * cmax + map[0]) * (int)sizeof(SegNode) : 0;
-    }
-}
-
-// The copies' views for segments [j0, j1), from the variants' refitted
-// tops: one thread per (segment, variant, copy).
-__global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__ nodes,
-                          const int32_t *__restrict__ vlist, const int32_t *__restrict__ vcount,
-                          const int32_t *__restrict__ vmap, const float2 *__restrict__ vz,
-                          const SegConst *__restrict__ segs, int j0, int j1, int64_t stride, SegNode *__restrict__ out)
+// The variants' heights, bad ones skipped and flagged; a thread each.  (Heights
+// are positive, so their order is that of their bits.)
+__global__ void k_var_heights(int64_t n, int k, const int32_t *__restrict__ ids, const float *__restrict__ h,
+                              const int32_t *__restrict__ rank, int n_b, float *__restrict__ vh, int32_t *tops, uint32_t *flag)
 {
     const int64_t t = (int64_t)wg_id() * wg_size() + tid();
-    const int64_t per = (int64_t)V * cmax;
-    if (t >= (int64_t)(j1 - j0) * per) return;
-    const int jj = (int)(t / per);
-    const int64_t vc = t - jj * per;
-    const int v = (int)(vc / cmax), c = (int)(vc - (int64_t)v * cmax);
-    if (c >= vcount[v]) return;
-    Node nd = nodes[vlist[vc]];
-    nd.lz1 = vz[vc].x;
-    nd.rz1 = vz[vc].y;
-    auto ref = [&](int r) {
-        if (r < 0) return r;  // a leaf or absent
-        const int at = vmap[(int64_t)v * n_nodes + r];
-        return (at >= 0 ? n_nodes + v * cmax + at : r) * (int)sizeof(SegNode);
-    };
-    const SegConst &g = segs[j0 + jj];
-    out[jj * stride + n_nodes + vc] = make_view(nd, ref(nd.left), ref(nd.right), fan_geom(g), g.mdx, g.mdy);
+    if (t >= n) return;
+    const int id = ids[t];
+    const float hv = h[t];
+    if (id < 0 || id >= n_b || !(hv > 0.f)) {
+        atomicOr(flag, 4u);
+        return;
+    }
+    const int prim = rank[id];
+    vh[t / k * n_b + prim] = hv;
+    atomicMax(&tops[prim], __float_as_int(hv));
 }
 
 // Persistent accrual over the (variant, tile) queue.  A wave takes the next
@@ -1179,9 +1069,8 @@ __global__ void k_seg_var(int V, int cmax, int n_nodes, const Node *__restrict__
 // walking its window left to right with halving / doubling sub-windows.
 // Seven waves per SIMD: 72 VGPRs with a few spilled to scratch, measured
 // faster (64.5 ms on 256 variants) than six waves (77 ms) or eight (75 ms).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(const Node *nodes_g, const SegNode *views_g,
-                                                      int64_t stride, const int32_t *voff_g,
-                                                      const int32_t *__restrict__ vroot, const float4 *verts_g,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(const Node *nodes_g, const ViewEntry *views_g,
+                                                      const int32_t *voff_g, const float4 *verts_g,
                                                       const float *vh_g, int n_b, const SegConst *segs_g, int j0,
                                                       int j1, PointArgs P, const int64_t *__restrict__ var_off,
                                                       const int64_t *__restrict__ tile_off, int V,
@@ -1193,6 +1082,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     __shared__ StackEntry s_stack[kWaves][kStackDepth];
     __shared__ int s_P[sizeof(PointArgs) / 4];
     StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     const int64_t T = tile_off[V];
     const int64_t n = P.n;
@@ -1221,7 +1112,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const bool valid = i < var_off[v + 1];
         const LanePoint q = load_point(lds_uniform<PointArgs>((lds_int *)s_P), i, valid);
         const bool covered = roof_covered<false>((cNode *)nodes_g, stack, verts, height, q, valid);
-        const int root = vroot ? vroot[v] : 0;
         int cnt = 0;
         double mins = 0.0;
         int bin = j1 > j0 ? ld(segs + j0).bin : 0;
@@ -1240,17 +1130,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
             if (covered && valid) {
                 mins += (double)g.dt;
                 cnt += g.ns_all;
-                continue;
             }
             float w0 = 0.f, s = g.theta;
-            bool pending = valid;
+            bool pending = valid && !covered;
             while (ballot(pending)) {
                 const float w1 = fminf(w0 + s, g.theta);
                 Union4 U;
                 bool ov;
-                const SegSrc src{views_g ? (cSegNode *)(views_g + (int64_t)(j - j0) * stride) : nullptr,
-                                 (cint *)voff_g, root};
-                accrue_segment<false>(src, stack, verts, height, g, q, pending, w0, w1, U, ov, none);
+                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b,
+                                 (cint *)voff_g, tile, height};
+                accrue_segment<false>(src, verts, g, q, pending, w0, w1, U, ov, none);
                 if (pending) {
                     if (ov) {
                         if (s < g.theta * (1.0f / 4096.0f)) {
@@ -1357,12 +1246,12 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
     return SA_OK;
 }
 
-sa_status run_spill(const DeviceScene &s, const DevicePath &p, const SegNode *views, int j0, const PointArgs &P,
+sa_status run_spill(const DeviceScene &s, const DevicePath &p, const ViewEntry *views, int j0, const PointArgs &P,
                     float scale, int32_t *counts, float *minutes, double *minutes64, SpillQueue &q, hipStream_t st,
                     std::string &err)
 {
-    hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, j0, s.voff, s.verts, s.height,
-                       p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries, (const uint32_t *)q.counters,
+    hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, j0, s.voff, s.verts,
+                       s.height, p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries, (const uint32_t *)q.counters,
                        q.capacity, q.counters + 2);
     SA_CHECK_LAUNCH("accrual spill");
     return SA_OK;
@@ -1384,15 +1273,6 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
 {
     if (n_var == 0 || pts.n == 0) return SA_OK;
     grab = std::max(grab, 1);
-    const int n_nodes = s.n_b > 0 ? s.n_nodes : 0;
-    // copies of changed nodes per variant: at most one chain of ancestors
-    // per changed building
-    const int cmax = std::max(1, k * std::max(s.depth, 1));
-    const int64_t stride = (int64_t)n_nodes + (int64_t)n_var * cmax;  // views per segment
-    if (stride * (int64_t)sizeof(SegNode) >= (1ll << 31)) {
-        err = "too many variants x changed buildings for one call (views are addressed with 32-bit offsets)";
-        return SA_ERR_CAPACITY;
-    }
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     size_t need = 0;
     auto part = [&](size_t bytes) {
@@ -1400,82 +1280,62 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
         need += up(bytes);
         return at;
     };
-    const size_t copies = (size_t)n_var * cmax;
     const size_t h_at = part(sizeof(float) * (size_t)n_var * s.n_b);
-    const size_t map_at = part(sizeof(int32_t) * (size_t)n_var * n_nodes);
+    const size_t tops_at = part(sizeof(float) * (size_t)s.n_b);
     const size_t tile_at = part(sizeof(int64_t) * (n_var + 1));
-    const size_t list_at = part(sizeof(int32_t) * copies);
-    const size_t z_at = part(sizeof(float2) * copies);
-    const size_t chain_at = part(sizeof(VarChain) * (size_t)n_var * k);
-    const size_t cnt_at = part(sizeof(int32_t) * (size_t)n_var);
-    const size_t root_at = part(sizeof(int32_t) * (size_t)n_var);
     const size_t counter_at = part(256);
     if (!grow(scr, need, st)) {
         err = "variant scratch allocation failed";
         return SA_ERR_OOM;
     }
     char *base = (char *)scr.ptr;
-    float *vh = (float *)(base + h_at);
-    int32_t *vmap = (int32_t *)(base + map_at);
+    float *vh = (float *)(base + h_at), *tops = (float *)(base + tops_at);
     int64_t *tile_off = (int64_t *)(base + tile_at);
-    int32_t *vlist = (int32_t *)(base + list_at);
-    float2 *vz = (float2 *)(base + z_at);
-    int32_t *vcount = (int32_t *)(base + cnt_at);
-    int32_t *vroot = (int32_t *)(base + root_at);
     uint32_t *counter = (uint32_t *)(base + counter_at);
-    const int n_int = s.n_b == 1 ? 1 : s.n_b - 1;
-    hipLaunchKernelGGL(k_var_copy, dim3(1024), dim3(256), 0, st, (const float *)s.height, s.n_b, n_nodes, n_var, vh, vmap,
-                       var_off, tile_off);
-    if (s.n_b > 0)
-        hipLaunchKernelGGL(k_var_setup, dim3(n_var), dim3(64), 0, st, k, ids, h, (const int32_t *)s.rank,
-                           (const int32_t *)s.parent, n_int, s.n_b, n_nodes, cmax, (const Node *)s.nodes, vh, vmap, vlist,
-                           vz, (VarChain *)(base + chain_at), vcount, vroot, flag);
+    hipLaunchKernelGGL(k_var_copy, dim3(1024), dim3(256), 0, st, (const float *)s.height, s.n_b, n_var, vh, tops, var_off,
+                       tile_off);
+    const int64_t edits = (int64_t)n_var * k;
+    if (s.n_b > 0 && edits > 0)
+        hipLaunchKernelGGL(k_var_heights, dim3((unsigned)((edits + 255) / 256)), dim3(256), 0, st, edits, k, ids, h,
+                           (const int32_t *)s.rank, s.n_b, vh, (int32_t *)tops, flag);
     SA_CHECK_LAUNCH("variant set-up");
     const PointArgs P = point_args(pts, s);
     const int blocks = grid_blocks > 0 ? grid_blocks : 2048;
-    // segment ranges whose views (base and every variant's copies) fit the
-    // per-launch budget; outputs accumulate across the launches
-    const int64_t per = seg_views_cap(s, p, stride, views_scr, st);
+    // segment ranges whose views fit the per-launch budget; outputs accumulate
+    // across the launches
+    const int64_t per = seg_views_cap(s, p, views_scr, st);
     for (int64_t j0 = 0; j0 < std::max(p.n_segs, 1); j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
-        SegNode *views = nullptr;
-        sa_status rc = build_seg_views(s, p, (int)j0, j1, stride, views_scr, {nullptr, counter, 2}, st, views, err);
+        ViewEntry *views = nullptr;
+        sa_status rc = build_seg_views(s, p, tops, (int)j0, j1, views_scr, {nullptr, counter, 2}, st, views, err);
         if (rc != SA_OK) return rc;
-        if (views) {
-            const int64_t nt = (int64_t)(j1 - j0) * n_var * cmax;
-            hipLaunchKernelGGL(k_seg_var, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, n_var, cmax, n_nodes,
-                               (const Node *)s.nodes, (const int32_t *)vlist, (const int32_t *)vcount,
-                               (const int32_t *)vmap, (const float2 *)vz, p.segs, (int)j0, j1, stride, views);
-            SA_CHECK_LAUNCH("variant segment views");
-        }
         hipLaunchKernelGGL(k_batched, dim3(blocks), dim3(kThreads), 0, st, s.n_b > 0 ? (const Node *)s.nodes : nullptr,
-                           views, stride, s.voff, s.n_b > 0 ? (const int32_t *)vroot : nullptr, s.verts,
-                           (const float *)vh, s.n_b, p.segs, (int)j0, j1, P, var_off, (const int64_t *)tile_off,
-                           n_var, counter, grab, scale, counts, minutes, flag);
+                           views, s.voff, s.verts, (const float *)vh, s.n_b, p.segs, (int)j0, j1, P, var_off,
+                           (const int64_t *)tile_off, n_var, counter, grab, scale, counts, minutes, flag);
         SA_CHECK_LAUNCH("batched accrual");
     }
     return SA_OK;
 }
 
-int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, int64_t stride, Scratch &scr, hipStream_t st)
+int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, hipStream_t st)
 {
-    const int64_t per_seg = std::max<int64_t>(stride, 1) * (int64_t)sizeof(SegNode);
+    const int64_t per_seg = std::max<int64_t>(view_bytes(s.n_b), 1);
     if (scr.fixed) return (int64_t)scr.bytes / per_seg;
     if (s.n_b == 0) return std::max(p.n_segs, 1);
-    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(kSegNodeBytes / per_seg, p.n_segs));
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(kViewBytes / per_seg, p.n_segs));
     if (scr.bytes >= (size_t)(want * per_seg)) return want;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
     if (cs != hipStreamCaptureStatusNone) return std::max<int64_t>(1, (int64_t)scr.bytes / per_seg);
-    for (int64_t budget = kSegNodeBytes; budget > kLeastNodeBytes; budget /= 2) {
+    for (int64_t budget = kViewBytes; budget > kLeastViewBytes; budget /= 2) {
         const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(budget / per_seg, p.n_segs));
         if (grow(scr, (size_t)(cap * per_seg), st)) return cap;
     }
-    return std::max<int64_t>(1, kLeastNodeBytes / per_seg);
+    return std::max<int64_t>(1, kLeastViewBytes / per_seg);
 }
 
-sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int j1, int64_t stride, Scratch &scr,
-                          const LaunchState &state, hipStream_t st, SegNode *&views, std::string &err)
+sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, const float *tops, int j0, int j1, Scratch &scr,
+                          const LaunchState &state, hipStream_t st, ViewEntry *&views, std::string &err)
 {
     views = nullptr;
     if (s.n_b == 0 || j1 <= j0) {
@@ -1483,21 +1343,19 @@ sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int
         SA_CHECK_LAUNCH("launch state");
         return SA_OK;
     }
-    const int64_t nt = (int64_t)(j1 - j0) * s.n_nodes;
-    const size_t need = (size_t)(j1 - j0) * stride * sizeof(SegNode);
+    const size_t need = (size_t)(j1 - j0) * view_bytes(s.n_b);
     if (scr.bytes < need && scr.fixed) {
-        err = "per-segment node views need " + std::to_string(need) + " bytes, more than the fixed " +
+        err = "per-segment views need " + std::to_string(need) + " bytes, more than the fixed " +
               std::to_string(scr.bytes);
         return SA_ERR_CAPACITY;
     }
     if (!grow(scr, need, st)) {
-        err = "segment node view allocation failed";
+        err = "segment view allocation failed";
         return SA_ERR_OOM;
     }
-    views = (SegNode *)scr.ptr;
-    hipLaunchKernelGGL(k_seg_nodes, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, s.nodes, s.n_nodes, p.segs,
-                       j0, j1, stride, views, state);
-    SA_CHECK_LAUNCH("segment node views");
+    views = (ViewEntry *)scr.ptr;
+    launch_views(s, tops, (const SegConst *)p.segs, j0, j1, views, state, st);
+    SA_CHECK_LAUNCH("segment views");
     return SA_OK;
 }
 
@@ -1525,11 +1383,11 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     const PointArgs P = point_args(pts, s);
     // Long spans run as several launches over consecutive segment ranges,
     // each about kChunkWork point-segments and covering at most
-    // kSegNodeBytes of per-segment node views (built just before it);
+    // kViewBytes of views (built just before it);
     // outputs are accumulated, so the split is invisible in the results.
-    const int64_t cap = seg_views_cap(s, p, s.n_nodes, scr, st);
+    const int64_t cap = seg_views_cap(s, p, scr, st);
     if (s.n_b > 0 && p.n_segs > 0 && cap < 1) {
-        err = "one segment's node views (" + std::to_string((int64_t)s.n_nodes * (int64_t)sizeof(SegNode)) +
+        err = "one segment's view (" + std::to_string(view_bytes(s.n_b)) +
               " bytes) exceed the fixed scratch (" + std::to_string(scr.bytes) + " bytes)";
         return SA_ERR_CAPACITY;
     }
@@ -1542,7 +1400,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
         if (scr.fixed && s.n_b > 0)
             for (int d = 0; d < D; ++d)
                 if (p.day_seg_off[d + 1] - p.day_seg_off[d] > cap) {
-                    err = "one day's node views (" + std::to_string(p.day_seg_off[d + 1] - p.day_seg_off[d]) +
+                    err = "one day's views (" + std::to_string(p.day_seg_off[d + 1] - p.day_seg_off[d]) +
                           " segments) exceed the fixed scratch (" + std::to_string(cap) + " segments fit)";
                     return SA_ERR_CAPACITY;
                 }
@@ -1550,13 +1408,13 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             int d1 = d0 + 1;
             while (d1 < D && p.day_seg_off[d1 + 1] - p.day_seg_off[d0] <= per) ++d1;
             const int j0 = p.day_seg_off[d0], j1 = p.day_seg_off[d1];
-            SegNode *views;
-            sa_status rc = build_seg_views(s, p, j0, j1, s.n_nodes, scr, {nullptr, q.grab, 8 * kGrabStride}, st, views, err);
+            ViewEntry *views;
+            sa_status rc = build_seg_views(s, p, s.height, j0, j1, scr, {nullptr, q.grab, 8 * kGrabStride}, st, views, err);
             if (rc != SA_OK) return rc;
             const int64_t res = resident_blocks(k_accrual_runs, L);
             const Sched W = plan_units(p.seg_runs, j0, j1, tiles, Split::kUniqueBins, res, q.grab);
             hipLaunchKernelGGL(k_accrual_runs, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
-                               st, nodes, views, s.n_nodes, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
+                               st, nodes, views, s.n_b, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
                                bin_out(p, j0, store, counts, minutes, minutes64, scale), longest, q.counters + 2);
             SA_CHECK_LAUNCH("accrual kernel (continuous shadow)");
             d0 = d1;
@@ -1591,8 +1449,8 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     }
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
-        SegNode *views;
-        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {q.counters, q.grab, 8 * kGrabStride},
+        ViewEntry *views;
+        sa_status rc = build_seg_views(s, p, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride},
                                        st, views, err);
         if (rc != SA_OK) return rc;
         SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
@@ -1604,7 +1462,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             O.pcnt = (int32_t *)piece_scr.ptr;
             O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, views, s.n_nodes,
+        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, views, s.n_b,
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
         SA_CHECK_LAUNCH("accrual kernel");
         if (W.sub > 1) {
@@ -1628,11 +1486,11 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
     const PointArgs P = point_args(pts, s);
     // long spans: several launches over consecutive segment ranges
     const int64_t per =
-        std::min(std::max<int64_t>(1, kChunkWork / 2 / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, s.n_nodes, scr, st));
+        std::min(std::max<int64_t>(1, kChunkWork / 2 / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
-        SegNode *views;
-        sa_status rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {nullptr, grab, 8 * kGrabStride}, st,
+        ViewEntry *views;
+        sa_status rc = build_seg_views(s, p, s.height, (int)j0, j1, scr, {nullptr, grab, 8 * kGrabStride}, st,
                                        views, err);
         if (rc != SA_OK) return rc;
         // the sums are atomic: on few tiles the units are chunks of segments
@@ -1640,8 +1498,8 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
         const Split split = tiles < 2 * res * kWaves ? Split::kChunks : Split::kBinRuns;
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, split, res, grab);
         hipLaunchKernelGGL(k_contrib, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, views,
-                           s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, weight,
-                           (const int32_t *)s.order, s.n_b, contrib);
+                           s.n_b, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, weight,
+                           (const int32_t *)s.order, contrib);
         SA_CHECK_LAUNCH("contribution kernel");
     }
     return SA_OK;

@@ -22,13 +22,13 @@ struct sa_ctx {
     sa::SpillQueue spill;
     sa::Scratch scratch;          // region sums
     sa::Scratch scratch_batched;  // per-variant hierarchy copies
-    sa::Scratch scratch_seg;      // per-segment node views of the accrual form
+    sa::Scratch scratch_seg;      // per-segment views of the accrual form
     sa::Scratch scratch_sam;      // one segment's raster shadow accrual map
     sa::Scratch scratch_grad;     // FP64 height-gradient accumulator
     sa::Scratch scratch_w;        // per-bin weights of a region score
     sa::Scratch scratch_edit;     // staging of long height edits
     sa::Scratch scratch_piece;    // per-piece sums of accrual launches on few tiles
-    sa::Scratch scratch_fan;      // node views of the sampled form's fans (their own: a graph captured
+    sa::Scratch scratch_fan;      // views of the sampled form's fans (their own: a graph captured
                                   // over accrual calls keeps scratch_seg)
     sa::Scratch scratch_mask;     // and their mask words
     uint32_t sam_stamp = 0;       // the last segment stamp written into it
@@ -301,8 +301,8 @@ sa_status sa_scene_upload(sa_ctx *ctx, int32_t n_b, const int32_t *vert_off_in, 
     if (he != hipSuccess) return hip_fail(ctx, he, "sa_scene_upload: reading xy");
     const float *height = n_b > 0 ? host_view(height_in, (size_t)n_b, h_h, he) : height_in;
     if (he != hipSuccess) return hip_fail(ctx, he, "sa_scene_upload: reading height");
-    // the accrual traversal addresses per-segment node views (64 bytes
-    // each) with 32-bit byte offsets
+    // the walks address a view's entries (32 bytes each) with 32-bit byte
+    // offsets, the hierarchy's nodes (64) with signed ones
     if (n_b > (1 << 25)) return fail(ctx, SA_ERR_CAPACITY, "sa_scene_upload: more than 2^25 prisms");
     for (int32_t b = 0; b < n_b; ++b) {
         const int32_t o = vert_off[b], m = vert_off[b + 1] - o;
@@ -1039,7 +1039,7 @@ sa_status sa_accumulate_noalloc(sa_ctx *ctx, const sa_scene *scene, const sa_poi
     if (opts->mode == SA_ACCRUAL && scene->d.n_b > 0 && path->d.n_segs > 0 && pts->n > 0) {
         // refuse before any work: a launch must hold one segment's views, and
         // with the continuous shadow a whole day's
-        const int64_t per_seg = (int64_t)std::max(scene->d.n_nodes, 1) * (int64_t)sizeof(sa::SegNode);
+        const int64_t per_seg = sa::view_bytes(scene->d.n_b);
         const int64_t cap = (int64_t)SA_NOALLOC_SCRATCH_BYTES / per_seg;
         int64_t need = 1;
         if (opts->longest)
@@ -1047,7 +1047,7 @@ sa_status sa_accumulate_noalloc(sa_ctx *ctx, const sa_scene *scene, const sa_poi
                 need = std::max<int64_t>(need, path->d.day_seg_off[d + 1] - path->d.day_seg_off[d]);
         if (need > cap)
             return fail(ctx, SA_ERR_CAPACITY,
-                        "sa_accumulate_noalloc: " + std::to_string(need) + " segments of node views (" +
+                        "sa_accumulate_noalloc: " + std::to_string(need) + " segments of views (" +
                             std::to_string(per_seg) + " bytes each) must fit the fixed scratch of " +
                             std::to_string((int64_t)SA_NOALLOC_SCRATCH_BYTES) + " bytes");
     }

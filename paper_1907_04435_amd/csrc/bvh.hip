@@ -91,20 +91,54 @@ __device__ inline uint32_t spread16(uint32_t v)
     return v;
 }
 
-// 32-bit Morton code of the footprint-box centre on a square 65536^2 grid
-// over the scene (one scale for both axes keeps cells square).
+// Cell of the footprint-box centre on a square 65536^2 grid over the scene
+// (one scale for both axes keeps cells square).
+__device__ __forceinline__ void grid_cell(float4 q, const float *bounds, uint32_t &ix, uint32_t &iy)
+{
+    float ext = fmaxf(fmaxf(bounds[2] - bounds[0], bounds[3] - bounds[1]), 1e-6f);
+    float cx = 0.5f * (q.x + q.z), cy = 0.5f * (q.y + q.w);
+    float sx = (cx - bounds[0]) / ext * 65535.0f, sy = (cy - bounds[1]) / ext * 65535.0f;
+    ix = (uint32_t)fminf(fmaxf(sx, 0.f), 65535.f);
+    iy = (uint32_t)fminf(fmaxf(sy, 0.f), 65535.f);
+}
+
+// 32-bit Morton code of the cell.
 __global__ void k_morton(int n_b, const float4 *__restrict__ box, const float *__restrict__ bounds,
                          uint32_t *__restrict__ key, int32_t *__restrict__ val)
 {
     int b = wg_id() * wg_size() + tid();
     if (b >= n_b) return;
-    float ext = fmaxf(fmaxf(bounds[2] - bounds[0], bounds[3] - bounds[1]), 1e-6f);
-    float4 q = box[b];
-    float cx = 0.5f * (q.x + q.z), cy = 0.5f * (q.y + q.w);
-    float sx = (cx - bounds[0]) / ext * 65535.0f, sy = (cy - bounds[1]) / ext * 65535.0f;
-    uint32_t ix = (uint32_t)fminf(fmaxf(sx, 0.f), 65535.f);
-    uint32_t iy = (uint32_t)fminf(fmaxf(sy, 0.f), 65535.f);
+    uint32_t ix, iy;
+    grid_cell(box[b], bounds, ix, iy);
     key[b] = spread16(ix) | (spread16(iy) << 1);
+    val[b] = b;
+}
+
+// 32-bit Hilbert index of the cell, for the views' order: its runs
+// stay compact, where a Morton run may jump across the scene (of a view's
+// groups, 1.8 and 2.2 are then looked into a wave and segment of the block
+// scene, against 2.4 and 3.4, and prisms come nearer first).
+__global__ void k_hilbert(int n_b, const float4 *__restrict__ box, const float *__restrict__ bounds,
+                          uint32_t *__restrict__ key, int32_t *__restrict__ val)
+{
+    const int b = wg_id() * wg_size() + tid();
+    if (b >= n_b) return;
+    uint32_t x, y, d = 0;
+    grid_cell(box[b], bounds, x, y);
+    for (uint32_t s = 1u << 15; s; s >>= 1) {
+        const uint32_t rx = (x & s) ? 1u : 0u, ry = (y & s) ? 1u : 0u;
+        d = d << 2 | ((3u * rx) ^ ry);
+        if (!ry) {
+            if (rx) {
+                x = ~x;
+                y = ~y;
+            }
+            const uint32_t t = x;
+            x = y;
+            y = t;
+        }
+    }
+    key[b] = d;
     val[b] = b;
 }
 
@@ -410,6 +444,30 @@ __global__ void k_put_heights(int32_t n, const int32_t *__restrict__ pos, const 
     if (k < n) height[pos[k]] = h[k];
 }
 
+// Footprint boxes of the views' groups, a wave each: [0, n1) the groups of
+// prisms, then the groups of groups.
+__global__ __launch_bounds__(64) void k_group_boxes(int n_b, const int32_t *__restrict__ vorder,
+                                                    const float4 *__restrict__ pbox, float4 *__restrict__ gbox)
+{
+    const ViewShape sh = view_shape(n_b);
+    const int g = wg_id();
+    const bool super = g >= sh.n1;
+    const int bits = super ? kGroupBits + kSuperBits : kGroupBits;
+    const int a = (super ? g - sh.n1 : g) << bits, b = min(a + (1 << bits), n_b);
+    float4 q = make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    for (int j = a + tid(); j < b; j += 64) {
+        const float4 r = pbox[vorder[j]];
+        q = make_float4(fminf(q.x, r.x), fminf(q.y, r.y), fmaxf(q.z, r.z), fmaxf(q.w, r.w));
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+        q.x = fminf(q.x, __shfl_xor(q.x, o, 64));
+        q.y = fminf(q.y, __shfl_xor(q.y, o, 64));
+        q.z = fmaxf(q.z, __shfl_xor(q.z, o, 64));
+        q.w = fmaxf(q.w, __shfl_xor(q.w, o, 64));
+    }
+    if (tid() == 0) gbox[g] = q;
+}
+
 // A single prism: one node whose right child is absent.
 __global__ void k_single(const int32_t *__restrict__ voff, Node *nodes, int32_t *parent)
 {
@@ -451,6 +509,8 @@ void scene_free(DeviceScene &s)
     (void)hipFree(s.parent);
     (void)hipFree(s.flags);
     (void)hipFree(s.pbox);
+    (void)hipFree(s.vorder);
+    (void)hipFree(s.gbox);
     (void)hipFree(s.leaf_depth);
     s = DeviceScene();
 }
@@ -570,6 +630,9 @@ sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t
     SA_TRY(dalloc(s.parent, s.n_nodes + n_b, err));
     SA_TRY(dalloc(s.flags, s.n_nodes, err));
     SA_TRY(dalloc(s.pbox, n_b, err));
+    const ViewShape groups = view_shape(n_b);
+    SA_TRY(dalloc(s.vorder, n_b, err));
+    SA_TRY(dalloc(s.gbox, (size_t)groups.n1 + groups.n2, err));
     SA_TRY(dalloc(s.leaf_depth, n_b, err));
 #undef SA_TRY
     auto fail = [&](hipError_t e, const char *what) -> sa_status {
@@ -593,15 +656,18 @@ sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t
     hipLaunchKernelGGL(k_morton, dim3(blocks(n_b, 256)), dim3(256), 0, st, n_b, (const float4 *)box_in,
                        (const float *)bounds_d, keys[0], vals[0]);
     int cur = 0;
-    for (int shift = 0; shift < 32; shift += 8) {
-        hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(kSortThreads), 0, st, n_b, shift, nblk,
-                           (const uint32_t *)keys[cur], hist);
-        hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, st, 256 * nblk, hist);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(kSortThreads), 0, st, n_b, shift, nblk,
-                           (const uint32_t *)keys[cur], (const int32_t *)vals[cur], (const uint32_t *)hist,
-                           keys[cur ^ 1], vals[cur ^ 1]);
-        cur ^= 1;
-    }
+    auto sort = [&]() {  // (keys, vals)[cur]
+        for (int shift = 0; shift < 32; shift += 8) {
+            hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(kSortThreads), 0, st, n_b, shift, nblk,
+                               (const uint32_t *)keys[cur], hist);
+            hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, st, 256 * nblk, hist);
+            hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(kSortThreads), 0, st, n_b, shift, nblk,
+                               (const uint32_t *)keys[cur], (const int32_t *)vals[cur], (const uint32_t *)hist,
+                               keys[cur ^ 1], vals[cur ^ 1]);
+            cur ^= 1;
+        }
+    };
+    sort();
     if ((e = hipMemcpyAsync(s.order, vals[cur], sizeof(int32_t) * n_b, hipMemcpyDeviceToDevice, st)))
         return fail(e, "order copy");
     hipLaunchKernelGGL(k_scatter_rank, dim3(blocks(n_b + 1, 256)), dim3(256), 0, st, n_b,
@@ -615,6 +681,13 @@ sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t
         hipLaunchKernelGGL(k_karras, dim3(blocks(n_b - 1, 256)), dim3(256), 0, st, n_b,
                            (const uint32_t *)keys[cur], (const int32_t *)s.voff, s.nodes, s.parent);
     }
+    hipLaunchKernelGGL(k_hilbert, dim3(blocks(n_b, 256)), dim3(256), 0, st, n_b, (const float4 *)s.pbox,
+                       (const float *)bounds_d, keys[cur], vals[cur]);
+    sort();
+    if ((e = hipMemcpyAsync(s.vorder, vals[cur], sizeof(int32_t) * n_b, hipMemcpyDeviceToDevice, st)))
+        return fail(e, "view order copy");
+    hipLaunchKernelGGL(k_group_boxes, dim3(groups.n1 + groups.n2), dim3(64), 0, st, n_b,
+                       (const int32_t *)s.vorder, (const float4 *)s.pbox, s.gbox);
     if ((e = hipGetLastError())) return fail(e, "hierarchy kernels");
     rc = scene_refit(s, st, err);
     if (rc != SA_OK) {

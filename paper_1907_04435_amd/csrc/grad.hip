@@ -35,24 +35,23 @@ struct GradArgs {
     const int32_t *order;  // hierarchy position -> original id
 };
 
-__device__ __forceinline__ void grad_segment(cSegNode *snodes, cint *voff, StackEntry *stack, cfloat4 *verts,
-                                             cfloat *height, const SegConst &g, const LanePoint &q, bool active,
+__device__ __forceinline__ void grad_segment(const ViewEntry *view, int n_b, cint *voff, TileFan *tile, cfloat4 *verts, cfloat *height,
+                                             const SegConst &g, const LanePoint &q, bool active,
                                              float w0, float w1, UnionG &U, bool &ov)
 {
     union_clear(U);
     ov = false;
-    if (!active) return;
     float W0u, W0v, W1u, W1v;
     window_dirs(g, w0, w1, W0u, W0v, W1u, W1v);
-    bool live = true;
-    if (q.own >= 0) {
+    bool live = active;
+    if (active && q.own >= 0) {
         float a, b;
         if (backface_interval(q.nx, q.ny, g, w0, w1, W0u, W0v, W1u, W1v, a, b)) {
             union_first(U, a, b, -1, -1, 0.f, 0.f);
             live = !(a <= w0 && b >= w1);
         }
     }
-    if (snodes == nullptr) return;
+    if (view == nullptr) return;
     uint64_t ovm = 0;
     auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
         const uint64_t gm = want & ballot(prim != q.own);
@@ -68,7 +67,7 @@ __device__ __forceinline__ void grad_segment(cSegNode *snodes, cint *voff, Stack
     };
     const SegFan ft(g, q.px, q.py, q.pz);
     Work none{0, 0, 0, 0, 0, 0, 0};
-    packet_traverse_seg<false>(snodes, voff, stack, ballot(live), ft, leaf, none);
+    walk_view<false>(view, n_b, voff, tile, ballot(live), ft, leaf, none);
     ov = lane_in(ovm);
 }
 
@@ -134,7 +133,7 @@ __device__ __forceinline__ bool roof_covered_g(cNode *nodes, StackEntry *stack, 
 // keep every wave busy on small point sets (the gradient sums are atomic, so
 // any split adds up the same).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_grad(
-    const Node *nodes_g, const SegNode *snodes_g, int n_nodes, const int32_t *voff_g, const float4 *verts_g,
+    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, GradArgs G, SpillArgs S)
 {
     cNode *nodes = nodes_g ? (cNode *)nodes_g : nullptr;
@@ -154,6 +153,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     }
     __syncthreads();
     StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     int kx = 0;
     Unit un;
@@ -175,8 +176,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
             }
             UnionG U;
             bool ov;
-            cSegNode *sn = snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr;
-            grad_segment(sn, (cint *)voff_g, stack, verts, height, g, q, valid && !covered && w != 0.f, 0.f, g.theta,
+            const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr;
+            grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, valid && !covered && w != 0.f, 0.f, g.theta,
                          U, ov);
             scatter_grad(U, valid && !covered && !ov && w != 0.f, w * g.wrate, lds_uniform<GradArgs>((lds_int *)s_G));
             if (ballot(valid && ov))
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
 // The adjoint's spilled point-segments: as the accrual form's, one wave each,
 // every lane one 64th of the window, sub-windows split again.  Ends clamped to
 // a sub-window do not move with a height, so splitting adds no gradient terms.
-__global__ __launch_bounds__(kThreads) void k_grad_spill(const SegNode *snodes_g, int n_nodes, int j0,
+__global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_g, int n_b, int j0,
                                                          const int32_t *voff_g, const float4 *verts_g,
                                                          const float *height_g, const SegConst *segs_g, PointArgs P,
                                                          GradArgs G, const int4 *in, const uint32_t *in_count,
@@ -197,10 +198,10 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const SegNode *snodes_g
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
     __shared__ SpillWindow s_wait[kWaves][kSpillWait];
-    StackEntry *stack = s_stack[tid() >> 6];
     SpillWindow *wait = s_wait[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     const int64_t total = min((int32_t)*in_count, cap);
     const int64_t stride = (int64_t)n_wg() * kWaves;
@@ -211,14 +212,14 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const SegNode *snodes_g
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
         const float w = G.dl ? G.dl[(int64_t)g.bin * P.n + i] : 1.f;
-        cSegNode *sn = snodes_g ? (cSegNode *)(snodes_g + (int64_t)(j - j0) * n_nodes) : nullptr;
+        const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr;
         SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
         for (int waiting = 0;;) {
             float w0, w1;
             spill_share(win, lane, w0, w1);
             UnionG U;
             bool ov;
-            grad_segment(sn, (cint *)voff_g, stack, verts, height, g, q, true, w0, w1, U, ov);
+            grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, true, w0, w1, U, ov);
             scatter_grad(U, !ov, w * g.wrate, G);
             if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
         }
@@ -261,19 +262,19 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     const int64_t res = resident_blocks(k_grad, L);
     const PointArgs P{pts.n, pts.x, pts.y, pts.z, pts.nx, pts.ny, pts.owner, s.rank, s.n_b};
     const GradArgs G{dl, acc, s.order};
-    // segment ranges whose per-segment node views fit the budget, each
+    // segment ranges whose per-segment views fit the budget, each
     // followed by its spill rounds
-    const int64_t per = seg_views_cap(s, p, s.n_nodes, scr, st);
+    const int64_t per = seg_views_cap(s, p, scr, st);
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
-        SegNode *views;
-        rc = build_seg_views(s, p, (int)j0, j1, s.n_nodes, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
+        ViewEntry *views;
+        rc = build_seg_views(s, p, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
         if (rc != SA_OK) return rc;
         SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
         hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, s.nodes, views,
-                           s.n_nodes, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
-        hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_nodes, (int)j0, s.voff,
+                           s.n_b, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
+        hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, (int)j0, s.voff,
                            s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, (const uint32_t *)q.counters,
                            q.capacity, q.counters + 2);
         const hipError_t e = hipGetLastError();

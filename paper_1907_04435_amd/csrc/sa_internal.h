@@ -82,18 +82,36 @@ struct alignas(64) SegConst {
 };
 static_assert(sizeof(SegConst) == 128, "two lines");
 
-// A hierarchy node seen from one accrual segment: for each child, the box
-// terms of the fan test against that segment (the box edges shifted by
-// the fan's per-metre reach: x1 - z1 umnx, x0 - z1 umxx, y1 - z1 umny,
-// y0 - z1 umxy; the two wedge projections), children in the segment's
-// visit order.  64 bytes, one scalar load.
-struct alignas(64) SegNode {
-    float c[2][6];
-    int32_t ref[2];   // interior: byte offset of the child's view; leaf: ~prism; or absent
-    uint32_t vert[2];  // a leaf's first vertex and, above kLeafVertBits, its vertex count (0: see its offsets)
+// What a segment (or a chunk of instants) makes of a prism or of a group of
+// them: the box terms of the fan test (the box edges shifted by the fan's
+// per-metre reach: x1 - z1 umnx, x0 - z1 umxx, y1 - z1 umny, y0 - z1 umxy; the
+// two wedge projections), of a group the least strict of its members'.  A
+// fan's view of the scene is the entries of the groups of 64 groups (two or
+// more of them), of the groups of 32 prisms (two or more), and of the prisms,
+// group by group along a Hilbert curve; siblings (up to 64 groups of groups, a
+// group's prisms) nearest along the fan's middle direction first.
+struct alignas(32) ViewEntry {
+    float c[6];
+    int32_t ref;    // prism (hierarchy position) or group
+    uint32_t vert;  // prism: first vertex and, above kLeafVertBits, their number (0: see its offsets)
 };
+static_assert(sizeof(ViewEntry) == 32, "two 16-byte loads a lane");
+constexpr int kGroupBits = 5;  // prisms per group
+constexpr int kSuperBits = 6;  // groups per group of groups: as many as a wave has lanes
 constexpr int kLeafVertBits = 27;
-static_assert(sizeof(SegNode) == 64, "one line");
+struct ViewShape {
+    int32_t n_b, n1, n2;     // prisms, groups, groups of groups
+    uint32_t at1, at0, all;  // entries before the groups, before the prisms, in all
+};
+constexpr ViewShape view_shape(int32_t n_b)
+{
+    const int32_t n1 = (int32_t)(((uint32_t)n_b + (1u << kGroupBits) - 1u) >> kGroupBits);
+    const int32_t n2 = (n1 + (1 << kSuperBits) - 1) >> kSuperBits;
+    const uint32_t at1 = n2 > 1 ? (uint32_t)n2 : 0u;
+    const uint32_t at0 = at1 + (n1 > 1 ? (uint32_t)n1 : 0u);
+    return {n_b, n1, n2, at1, at0, at0 + (uint32_t)n_b};
+}
+inline int64_t view_bytes(int32_t n_b) { return (int64_t)view_shape(n_b).all * (int64_t)sizeof(ViewEntry); }
 
 // A chunk of the sampled form: up to kFanInstants consecutive instants of one
 // day (never across a multiple of it, so within a word of the bit vectors), whose
@@ -140,6 +158,8 @@ struct DeviceScene {
     int32_t *parent = nullptr;   // [n_nodes + n_b] parent*2+side of interior nodes then leaves
     int32_t *flags = nullptr;    // [n_nodes] refit arrival counters
     float4 *pbox = nullptr;      // [n_b] prism footprint boxes, hierarchy order
+    int32_t *vorder = nullptr;   // [n_b] views' order: hierarchy positions along a Hilbert curve
+    float4 *gbox = nullptr;      // [n1 + n2] footprint boxes of the groups and groups of groups (ViewShape)
     int32_t *leaf_depth = nullptr;  // [n_b] nodes above each prism, hierarchy order
 };
 
@@ -281,7 +301,7 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
                          float scale, int32_t *counts, float *minutes, uint32_t *bits, float *longest,
                          uint64_t *work, const TileLaunch &L, uint32_t *grab, hipStream_t st,
                          std::string &err);
-// The sampled form by fans of instants, with node views and mask words in
+// The sampled form by fans of instants, with views and mask words in
 // views_scr and mask_scr (grown as needed, with the stream synchronised
 // first).  taken = false, with nothing enqueued, where they cannot be had:
 // launch_sampled gives the same results without scratch.  store: outputs need
@@ -313,16 +333,16 @@ sa_status measure_valu_peak(int n_cu, float *sink, int64_t sink_floats, hipStrea
 sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const PointsView &pts,
                               const float *weight, double *contrib, const TileLaunch &L, uint32_t *grab,
                               Scratch &scr, hipStream_t st, std::string &err);
-// Per-segment node views (SegNode) of segments [j0, j1) into scr (grown as
-// needed, with the stream synchronised first; a fixed scr that is too small
-// is a CAPACITY error), segment j's views at (j - j0) * stride, and `state`
-// cleared; views = nullptr for an empty scene.  seg_views_cap: segments whose
-// views (stride each) a launch takes: the per-launch budget, less where scr
-// cannot be grown to it (a fixed scr, or one under stream capture: its size;
-// 0 if not even one fits).
-sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, int j0, int j1, int64_t stride, Scratch &scr,
-                          const LaunchState &state, hipStream_t st, SegNode *&views, std::string &err);
-int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, int64_t stride, Scratch &scr, hipStream_t st);
+// Views of segments [j0, j1) into scr (grown as needed, with the stream
+// synchronised first; a fixed scr that is too small is a CAPACITY error), one
+// after the other, and `state` cleared; views = nullptr for an empty scene.
+// `tops`: the prisms' heights the views take (hierarchy order).
+// seg_views_cap: segments whose views a launch takes: the per-launch budget,
+// less where scr cannot be grown to it (a fixed scr, or one under stream
+// capture: its size; 0 if not even one fits).
+sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, const float *tops, int j0, int j1, Scratch &scr,
+                          const LaunchState &state, hipStream_t st, ViewEntry *&views, std::string &err);
+int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, hipStream_t st);
 // Gross shadow by raster shadow accrual maps (Sec. 4) into counts/minutes
 // [n_bins * n] (already cleared): per segment a map of slices x nu x nv
 // 64-bit words (stamp, depth) in scr (grown as needed; max_texels caps one

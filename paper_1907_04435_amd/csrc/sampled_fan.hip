@@ -1,11 +1,11 @@
-// The sampled form by fans of instants: one walk of the hierarchy serves all
+// The sampled form by fans of instants: one walk of the scene serves all
 // the rays from a point toward up to 16 consecutive instants of a day.
 //
 // Between neighbouring instants the sun hardly moves, so a point's rays
 // toward a chunk of instants fill a narrow fan, and the prisms they can meet
 // are those the fan meets.  A wave takes 64 points and one chunk, walks the
-// chunk's node views (the accrual form's traversal: six compares per child
-// box, against a fan that holds every ray of the chunk), and at a leaf tests
+// chunk's view (the accrual form's walk, against a fan that holds every ray
+// of the chunk), and at a leaf tests
 // the prism against the chunk's rays one by one, with the arithmetic of
 // ray_prism.  A ray is shadowed if any prism blocks it, whatever the order of
 // the walk, so the predicate per (point, instant) is the packet kernels' own.
@@ -25,6 +25,7 @@
 #include "sa_internal.h"
 #include "traverse.h"
 #include "unit_sched.h"
+#include "views.h"
 
 namespace sa {
 namespace {
@@ -32,7 +33,7 @@ using namespace dev;
 
 constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
-constexpr int64_t kViewBytes = 256ll << 20;  // node views per launch
+constexpr int64_t kViewBytes = 256ll << 20;  // views per launch
 constexpr int64_t kMaskBytes = 256ll << 20;  // mask words per launch
 
 typedef __attribute__((address_space(4))) const FanChunk cChunk;
@@ -184,7 +185,7 @@ __device__ __forceinline__ uint32_t chunk_back(std::integer_sequence<int, K...>,
 // registers spilled at 7 and 8 are felt.
 template <bool kCount>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_sampled_fan(
-    const SegNode *views_g, int n_nodes, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
+    const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
     const FanChunk *chunks_g, const FanDirs *dirs_g, int c0, int c1, Sched W, PointArgs P, uint16_t *masks,
     uint64_t *work)
 {
@@ -193,7 +194,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cChunk *chunks = (cChunk *)chunks_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
     __shared__ int s_W[sizeof(Sched) / 4];
     __shared__ int s_P[sizeof(PointArgs) / 4];
     __shared__ uint16_t *s_masks;
@@ -203,7 +203,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         s_masks = masks;
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
+    __shared__ TileFan s_tile[kWaves];
+    TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     int kx = 0;
     Unit un;
@@ -241,30 +242,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                     pend &= lane_in(gm) ? ~hits : ~0u;
                     return gm & ballot(pend == 0u);
                 };
-                const FanGeom f{ch.f[0], ch.f[1], ch.f[2], ch.f[3], ch.f[4], ch.f[5], ch.f[6], ch.f[7]};
-                const SegFan ft(f, q.px, q.py, q.pz);
-                packet_traverse_seg<kCount>((cSegNode *)(views_g + (int64_t)(c - c0) * n_nodes), (cint *)voff_g, stack,
-                                            ballot(pend != 0u), ft, leaf, wk);
+                const SegFan ft(fan_geom(ch), q.px, q.py, q.pz);
+                walk_view<kCount>(views_g + (int64_t)(c - c0) * view_shape(n_b).all, n_b, (cint *)voff_g, tile,
+                                  ballot(pend != 0u), ft, leaf, wk);
             }
             if (valid) s_masks[(int64_t)(c - c0) * n + i] = (uint16_t)(all & ~pend);
         }
     }
     if constexpr (kCount) flush_work(wk, work);
-}
-
-// Views of the hierarchy for the fans of chunks [c0, c1): one thread per
-// (chunk, node), in blocks of 256.
-__global__ void k_fan_nodes(const Node *__restrict__ nodes, int n_nodes, const FanChunk *__restrict__ chunks, int c0,
-                            int c1, SegNode *__restrict__ out, LaunchState L)
-{
-    const int64_t t = (int64_t)wg_id() * wg_size() + tid();
-    clear_state(L, t);
-    if (t >= (int64_t)(c1 - c0) * n_nodes) return;
-    const int cc = (int)(t / n_nodes);
-    const Node nd = nodes[t - (int64_t)cc * n_nodes];
-    const FanChunk &ch = chunks[c0 + cc];
-    const FanGeom f{ch.f[0], ch.f[1], ch.f[2], ch.f[3], ch.f[4], ch.f[5], ch.f[6], ch.f[7]};
-    out[t] = make_view(nd, view_ref(nd.left), view_ref(nd.right), f, ch.mdx, ch.mdy);
 }
 
 struct FanSums {
@@ -411,7 +396,7 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     }
     // chunks per launch: their views fit the budget; whole days where runs
     // of shadow must not be cut
-    const int64_t view = s.n_b > 0 ? (int64_t)s.n_nodes * (int64_t)sizeof(SegNode) : 0;
+    const int64_t view = s.n_b > 0 ? view_bytes(s.n_b) : 0;
     const int64_t per = std::max<int64_t>(1, view > 0 ? kViewBytes / view : p.n_chunks);
     std::vector<int> cut{0};
     for (int c = 1; c < p.n_chunks; ++c) {
@@ -440,14 +425,12 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     const auto &rs = p.chunk_runs.start;
     for (size_t k = 0; k + 1 < cut.size(); ++k) {
         const int c0 = cut[k], c1 = cut[k + 1];
-        SegNode *views = nullptr;
+        ViewEntry *views = nullptr;
         if (view > 0) {
-            views = (SegNode *)views_scr.ptr;
-            const int64_t nt = (int64_t)(c1 - c0) * s.n_nodes;
-            hipLaunchKernelGGL(k_fan_nodes, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, (const Node *)s.nodes,
-                               s.n_nodes, (const FanChunk *)p.chunks, c0, c1, views,
-                               LaunchState{nullptr, grab, 8 * kGrabStride});
-            SA_CHECK_LAUNCH("fan node views");
+            views = (ViewEntry *)views_scr.ptr;
+            launch_views(s, s.height, (const FanChunk *)p.chunks, c0, c1, views,
+                         LaunchState{nullptr, grab, 8 * kGrabStride}, st);
+            SA_CHECK_LAUNCH("fan views");
         }
         // bin runs of the launch: summed by a thread each where no bin has two
         const int r0 = (int)(std::upper_bound(rs.begin(), rs.end(), c0) - rs.begin()) - 1;
@@ -462,8 +445,8 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
                 sa_status rc = fill_u32(grab, 8 * kGrabStride, 0u, st, err);
                 if (rc != SA_OK) return rc;
             }
-            hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, (const SegNode *)views,
-                               s.n_nodes, s.voff, s.verts, s.height, (const FanChunk *)p.chunks,
+            hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, (const ViewEntry *)views,
+                               s.n_b, s.voff, s.verts, s.height, (const FanChunk *)p.chunks,
                                (const FanDirs *)p.chunk_dirs, c0, c1, W, P, masks, work);
             SA_CHECK_LAUNCH("sampled fan kernel");
             const unsigned blocks = (unsigned)((n + kThreads - 1) / kThreads);

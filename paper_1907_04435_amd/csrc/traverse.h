@@ -1,8 +1,10 @@
 // Device-side building blocks shared by the traversal kernels.
 //
 // Traversal is wave-coherent: a wave of 64 lanes (64 neighbouring points,
-// one sun instant or one path segment) walks the hierarchy as one packet.
-// The node index is wave-uniform, so a node is fetched once per wave with a
+// one sun instant or one path segment) walks the scene as one packet.
+// Segments and fans of instants go by views of it (walk_view, below); single
+// instants and roof tests by the binary hierarchy.  There the
+// node index is wave-uniform, so a node is fetched once per wave with a
 // scalar load into SGPRs; each lane tests the two child boxes against its
 // own ray or fan; a child is entered when any still-live lane needs it.
 // The traversal stack is wave-uniform too: one 64-entry array per wave in
@@ -1051,19 +1053,19 @@ __device__ __forceinline__ float seg_key(float x0, float y0, float x1, float y1,
     return fmaf(x0 + x1, mdx, (y0 + y1) * mdy);
 }
 
-// ---- the accrual fan test on per-segment node views ----
+// ---- the fan test on a segment's view of the scene ----
 //
-// A direct fan test of a child box (the wedge edges' box_reach against
+// A direct fan test of a box (the wedge edges' box_reach against
 // each lane's n . p, and the box against the fan's bounding box, whose
 // corners move with the box top by the per-metre reach) spends most of its
 // arithmetic on values that are the same for every lane.  CDNA has no
 // scalar floating point, so those values would cost full vector
-// instructions at every node visit.  Moving the lane's
+// instructions at every visit.  Moving the lane's
 // terms to the other side of each inequality,
 //   x1 >= px + (z1 - pz) umnx   <=>   x1 - z1 umnx >= px - pz umnx,
 // leaves one side that depends only on (segment, box), computed once per
-// segment for the whole hierarchy (SegNode), and one that depends only on
-// (segment, point), computed once per lane and segment (SegFan): a child
+// segment for the whole scene (ViewEntry), and one that depends only on
+// (segment, point), computed once per lane and segment (SegFan): a
 // test becomes six compares.  (A box whose top is below pz has no compare of
 // its own: the bounds shifted by its negative rise nearly always exclude it.
 // On the block scene, half its points on facades, 1 in 8,500 more box tests
@@ -1071,7 +1073,7 @@ __device__ __forceinline__ float seg_key(float x0, float y0, float x1, float y1,
 // test passes every box that meets the fan exactly (boxes only decide
 // what is tested, never a result).
 
-typedef __attribute__((address_space(4))) const SegNode cSegNode;
+typedef __attribute__((address_space(4))) const ViewEntry cView;
 
 __device__ __forceinline__ float round_up_rel(float v) { return v + fabsf(v) * 0x1p-22f; }
 __device__ __forceinline__ float round_dn_rel(float v) { return v - fabsf(v) * 0x1p-22f; }
@@ -1094,10 +1096,10 @@ struct SegFan {
         nbP = fmaf(f.nbx, px, f.nby * py);
     }
 
-    // Both children at once, for the lanes in cur.
-    __device__ __forceinline__ void both(const SegNode &nd, uint64_t cur, uint64_t &h0, uint64_t &h1) const
+    // The lanes of cur whose fan meets the entry's box.
+    __device__ __forceinline__ uint64_t one(const ViewEntry &v, uint64_t cur) const
     {
-        uint64_t sv;
+        uint64_t sv, h;
         asm volatile(
             "s_mov_b64 %[sv], exec\n"
             "s_mov_b64 exec, %[cur]\n"
@@ -1107,24 +1109,84 @@ struct SegFan {
             "v_cmpx_le_f32 vcc, %[a3], %[cyh]\n"
             "v_cmpx_ge_f32 vcc, %[a4], %[naP]\n"
             "v_cmpx_ge_f32 vcc, %[a5], %[nbP]\n"
-            "s_mov_b64 %[h0], exec\n"
-            "s_mov_b64 exec, %[cur]\n"
-            "v_cmpx_ge_f32 vcc, %[b0], %[cxl]\n"
-            "v_cmpx_le_f32 vcc, %[b1], %[cxh]\n"
-            "v_cmpx_ge_f32 vcc, %[b2], %[cyl]\n"
-            "v_cmpx_le_f32 vcc, %[b3], %[cyh]\n"
-            "v_cmpx_ge_f32 vcc, %[b4], %[naP]\n"
-            "v_cmpx_ge_f32 vcc, %[b5], %[nbP]\n"
-            "s_mov_b64 %[h1], exec\n"
+            "s_mov_b64 %[h], exec\n"
             "s_mov_b64 exec, %[sv]\n"
-            : [h0] "=&s"(h0), [h1] "=&s"(h1), [sv] "=&s"(sv)
+            "s_nop 1\n"  // a lane read waits four states for compares into exec
+            : [h] "=&s"(h), [sv] "=&s"(sv)
             : [cur] "s"(cur), [cxl] "v"(cxl), [cxh] "v"(cxh), [cyl] "v"(cyl), [cyh] "v"(cyh), [naP] "v"(naP),
-              [nbP] "v"(nbP), [a0] "s"(nd.c[0][0]), [a1] "s"(nd.c[0][1]), [a2] "s"(nd.c[0][2]), [a3] "s"(nd.c[0][3]),
-              [a4] "s"(nd.c[0][4]), [a5] "s"(nd.c[0][5]), [b0] "s"(nd.c[1][0]), [b1] "s"(nd.c[1][1]),
-              [b2] "s"(nd.c[1][2]), [b3] "s"(nd.c[1][3]), [b4] "s"(nd.c[1][4]), [b5] "s"(nd.c[1][5])
+              [nbP] "v"(nbP), [a0] "s"(v.c[0]), [a1] "s"(v.c[1]), [a2] "s"(v.c[2]), [a3] "s"(v.c[3]), [a4] "s"(v.c[4]),
+              [a5] "s"(v.c[5])
             : "vcc");
+        return h;
     }
 };
+
+// The extremes of SegFan's terms over the lanes of a mask: the weakest a box
+// must meet to be met by any of their fans.  They lie in LDS, a slot per wave:
+// scalar registers are what a walk has least of (as six of them they were
+// spilled to lanes and read back for every test).
+struct alignas(16) TileFan {
+    float cxl, cxh, cyl, cyh, naP, nbP;
+};
+
+__device__ __forceinline__ void tile_fan(TileFan *out, const SegFan &f, uint64_t lanes)
+{
+    float a = f.cxl, b = f.cxh, c = f.cyl, d = f.cyh, e = f.naP, g = f.nbP;
+    if (lanes != ~0ull) {
+        const bool in = lane_in(lanes);
+        a = in ? a : INFINITY;
+        b = in ? b : -INFINITY;
+        c = in ? c : INFINITY;
+        d = in ? d : -INFINITY;
+        e = in ? e : INFINITY;
+        g = in ? g : INFINITY;
+    }
+    // six reductions side by side: each step reads what was written five
+    // instructions before
+#define SA_STEP(ctrl)                       \
+    "v_min_f32_dpp %[a], %[a], %[a] " ctrl  \
+    "v_max_f32_dpp %[b], %[b], %[b] " ctrl  \
+    "v_min_f32_dpp %[c], %[c], %[c] " ctrl  \
+    "v_max_f32_dpp %[d], %[d], %[d] " ctrl  \
+    "v_min_f32_dpp %[e], %[e], %[e] " ctrl  \
+    "v_min_f32_dpp %[g], %[g], %[g] " ctrl
+    asm volatile("s_nop 4\n" SA_STEP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n")
+                     SA_STEP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n")
+                         SA_STEP("row_ror:4 row_mask:0xf bank_mask:0xf\n")
+                             SA_STEP("row_ror:8 row_mask:0xf bank_mask:0xf\n")
+                                 SA_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf\n")
+                                     SA_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf\n") "s_nop 0"
+                 : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [e] "+v"(e), [g] "+v"(g));
+#undef SA_STEP
+    if ((tid() & 63) == 63) *out = TileFan{a, b, c, d, e, g};
+    // (the wave's other lanes read it: LDS keeps a wave's order, and so must
+    // the compiler)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// An entry per lane: the lanes whose box is met.
+__device__ __forceinline__ uint64_t tile_meets(const TileFan *tile, const float4 &u, const float4 &v)
+{
+    const TileFan f = *tile;
+    uint64_t sv, h;
+    asm volatile(
+        "s_mov_b64 %[sv], exec\n"
+        "v_cmpx_le_f32 vcc, %[cxl], %[a0]\n"
+        "v_cmpx_ge_f32 vcc, %[cxh], %[a1]\n"
+        "v_cmpx_le_f32 vcc, %[cyl], %[a2]\n"
+        "v_cmpx_ge_f32 vcc, %[cyh], %[a3]\n"
+        "v_cmpx_le_f32 vcc, %[naP], %[a4]\n"
+        "v_cmpx_le_f32 vcc, %[nbP], %[a5]\n"
+        "s_mov_b64 %[h], exec\n"
+        "s_mov_b64 exec, %[sv]\n"
+        "s_nop 1\n"  // a lane read waits four states for compares into exec
+        : [h] "=&s"(h), [sv] "=&s"(sv)
+        : [cxl] "v"(f.cxl), [cxh] "v"(f.cxh), [cyl] "v"(f.cyl), [cyh] "v"(f.cyh), [naP] "v"(f.naP), [nbP] "v"(f.nbP),
+          [a0] "v"(u.x), [a1] "v"(u.y), [a2] "v"(u.z), [a3] "v"(u.w), [a4] "v"(v.x), [a5] "v"(v.y)
+        : "vcc");
+    return h;
+}
 
 // The box-only side of SegFan's inequalities for one child box.  The
 // shifted edges are formed in double and rounded outward; the wedge
@@ -1146,7 +1208,7 @@ __device__ __forceinline__ void seg_child(const FanGeom &f, float x0, float y0, 
     c[5] = box_reach(x0, y0, x1, y1, f.nbx, f.nby);
 }
 
-// A leaf's vertex range in one word of the view; 0 above kLeafVertBits where
+// A prism's vertex range in one word of its entry; 0 above kLeafVertBits where
 // it does not fit.
 __device__ __forceinline__ uint32_t leaf_word(int voff, int m)
 {
@@ -1164,93 +1226,97 @@ __device__ __forceinline__ void leaf_range(uint32_t word, cint *voff, int prim, 
     }
 }
 
-// The view of node `nd` for a fan whose middle direction is (mdx, mdy), with
-// child references r0 (left) and r1 (right) already in view form (byte
-// offsets, or leaf / absent).
-__device__ __forceinline__ SegNode make_view(const Node &nd, int r0, int r1, const FanGeom &f, float mdx, float mdy)
-{
-    const bool lfirst = seg_key(nd.lx0, nd.ly0, nd.lx1, nd.ly1, mdx, mdy) <=
-                        seg_key(nd.rx0, nd.ry0, nd.rx1, nd.ry1, mdx, mdy);
-    SegNode v;
-    const int a = lfirst ? 0 : 1;
-    seg_child(f, nd.lx0, nd.ly0, nd.lx1, nd.ly1, nd.lz1, nd.left != kNone, v.c[a]);
-    seg_child(f, nd.rx0, nd.ry0, nd.rx1, nd.ry1, nd.rz1, nd.right != kNone, v.c[1 - a]);
-    v.ref[a] = r0;
-    v.ref[1 - a] = r1;
-    v.vert[a] = leaf_word(nd.l_voff, nd.l_m);
-    v.vert[1 - a] = leaf_word(nd.r_voff, nd.r_m);
-    return v;
-}
-
-__device__ __forceinline__ int view_ref(int r) { return r >= 0 ? r * (int)sizeof(SegNode) : r; }
-
-// Packet traversal over the per-segment views (see packet_traverse): the
-// children of a view are already in the segment's visit order, interior
-// references are byte offsets of views (one scalar load with a register
-// offset, no address arithmetic), and a leaf's vertex range lies in the view
-// (large ones in the hierarchy-order offsets `voff`).
-// Liveness is a wave mask throughout: `leaf(prim, voff, m, want)` returns
-// the mask of lanes it retires, so no per-lane flag is carried around the
-// loop (each such flag costs scalar merges with the exec mask at every
-// iteration).  All leaf handling sits behind one branch, taken only at
-// nodes with a leaf child.
-// `root` is the byte offset of the view the walk starts at.
+// A fan's walk over its view of the scene, for the lanes in `alive`: a lane
+// takes an entry of a group at a time and tests its box against the tile's
+// extremes, so 64 boxes cost six vector compares; only a prism that passes is
+// tested by every lane for itself.  Groups lie in the view nearest along the
+// fan's middle direction first (within 64), so shadowed lanes retire early.
+// `leaf(prim, voff, m, want)` returns the mask of lanes it retires.  All 64
+// lanes of the wave must be here: each stands for a box.
+// Bound by VALU issue.  A binary tree with both children's boxes tested by
+// every lane visited 26 nodes a wave and segment of the block scene (4M
+// points, 20,000 prisms, three days); this makes 3 tests of groups, 1 or 2 of
+// prisms and 3 of a single one: 10.07 -> 7.20 ms, VALU instructions 5.2e9 ->
+// 4.1e9.  Also there: longest runs 1.77 -> 1.33 ms, the sampled form 4.96 ->
+// 4.06; contributions 1.08 -> 0.88, forward and adjoint at 1-minute knots
+// 10.1 -> 7.5, a year on 45,000 prisms 207 -> 143, small calls 0 to 20 % less.
+// Groups in Morton order instead (whose runs jump, so far groups come before
+// near ones): 10.0 ms, eight times the spilled sets.  The extremes in scalar
+// registers and the shape held across the walk: 0.1 ms more.
 template <bool kCount, class LeafFn>
-__device__ __forceinline__ void packet_traverse_seg(cSegNode *nodes, cint *voff, StackEntry *stack, uint64_t alive,
-                                                    const SegFan &ft, LeafFn leaf, Work &w, int root = 0)
+__device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *voff, TileFan *tile, uint64_t alive,
+                                          const SegFan &ft, LeafFn leaf, Work &w)
 {
-    typedef __attribute__((address_space(4))) const char cchar;
-    uint64_t cur = alive;
-    int sp = 0, node = root;  // byte offset of the current view
-    while (cur) {
-        const SegNode nd = ld((cSegNode *)((cchar *)nodes + (uint32_t)node));
+    if (!alive) return;
+    tile_fan(tile, ft, alive);
+    const int lane = (int)(tid() & 63);
+    // the shape is worked out where it is used, on the scalar unit, not held
+    auto shape = [&]() {
+        int n = n_b;
+        asm volatile("" : "+s"(n));
+        return view_shape(n);
+    };
+    cView *cv = (cView *)view;
+    auto test = [&](uint32_t at, int &ref) -> uint64_t {
+        const char *e = (const char *)view + at * (uint32_t)sizeof(ViewEntry);
         if constexpr (kCount) {
-            w.box += lane_in(cur) ? 2u : 0u;
+            w.box += 1u;
             w.nodes += first_active_lane() ? 1u : 0u;
         }
-        uint64_t h0, h1;
-        ft.both(nd, cur, h0, h1);
-        if ((nd.ref[0] | nd.ref[1]) < 0) {
-            uint64_t out = 0;
-            if (nd.ref[0] < 0) {
-                if (h0) {
-                    const int prim = ~nd.ref[0];
-                    int v0, m;
-                    leaf_range(nd.vert[0], voff, prim, v0, m);
-                    out |= leaf(prim, v0, m, h0);
+        const float4 v = *(const float4 *)(e + 16);
+        ref = __float_as_int(v.z);
+        return tile_meets(tile, *(const float4 *)e, v);
+    };
+    auto first_of = [](int n) -> uint64_t { return n >= 64 ? ~0ull : (1ull << n) - 1ull; };
+    int ref, none;
+    for (int c2 = 0;;) {
+        ViewShape sh = shape();
+        uint64_t m2 = 1ull;
+        if (sh.n2 > 1) m2 = test((uint32_t)min(c2 + lane, sh.n2 - 1), none) & first_of(sh.n2 - c2);
+        while (m2) {
+            sh = shape();
+            const int b1 = sh.n2 > 1 ? ld(cv + c2 + (int)__builtin_ctzll(m2)).ref << kSuperBits : 0;
+            m2 &= m2 - 1ull;
+            uint64_t m1 = 1ull;
+            if (sh.n1 > 1) m1 = test(sh.at1 + (uint32_t)min(b1 + lane, sh.n1 - 1), ref) & first_of(sh.n1 - b1);
+            while (m1) {
+                // two groups at a time, half a wave each
+                sh = shape();
+                const int ka = (int)__builtin_ctzll(m1);
+                m1 &= m1 - 1ull;
+                const int kb = m1 ? (int)__builtin_ctzll(m1) : ka;
+                const uint64_t both = m1 ? ~0ull : 0xffffffffull;
+                m1 &= m1 - 1ull;
+                int fa = 0, fb = 0;  // their first prisms
+                if (sh.n1 > 1) {
+                    fa = __builtin_amdgcn_readlane(ref, ka) << kGroupBits;
+                    fb = __builtin_amdgcn_readlane(ref, kb) << kGroupBits;
                 }
-                h0 = 0;
-            }
-            if (nd.ref[1] < 0) {
-                if (h1) {
-                    const int prim = ~nd.ref[1];
-                    int v0, m;
-                    leaf_range(nd.vert[1], voff, prim, v0, m);
-                    out |= leaf(prim, v0, m, h1);
+                const int mine = (lane & 31) + (lane < 32 ? fa : fb);
+                uint64_t m0 = test(sh.at0 + (uint32_t)min(mine, sh.n_b - 1), none) & both & ballot(mine < sh.n_b);
+                cView *prisms = cv + sh.at0;
+                while (m0) {
+                    const int k = (int)__builtin_ctzll(m0);
+                    m0 &= m0 - 1ull;
+                    const ViewEntry v = ld(prisms + (k < 32 ? fa : fb) + (k & 31));
+                    const uint64_t h = ft.one(v, alive);
+                    if constexpr (kCount) {
+                        w.box += lane_in(alive) ? 1u : 0u;
+                        w.nodes += first_active_lane() ? 1u : 0u;
+                    }
+                    if (h) {
+                        int v0, m;
+                        leaf_range(v.vert, voff, v.ref, v0, m);
+                        alive &= ~leaf(v.ref, v0, m, h);
+                        m0 = alive ? m0 : 0ull;
+                    }
                 }
-                h1 = 0;
+                m1 = alive ? m1 : 0ull;
             }
-            alive &= ~out;
-            h0 &= alive;
-            h1 &= alive;
+            m2 = alive ? m2 : 0ull;
         }
-        // both children wanted: defer the second; go to the first wanted
-        const uint64_t defer = defer_mask(h0, h1);
-        if (defer) {
-            stack[sp] = StackEntry{nd.ref[1], (uint32_t)defer, (uint32_t)(defer >> 32), 0u};
-            ++sp;
-        }
-        descend(h0, h1, nd.ref[0], nd.ref[1], node, cur);
-        if (!cur) {
-            const uint64_t keep = alive;
-            while (sp > 0) {
-                --sp;
-                const StackEntry e = stack[sp];
-                node = uniform(e.node);
-                cur = uniform64(e.lo, e.hi) & keep;
-                if (cur) break;
-            }
-        }
+        c2 += 64;
+        if (!alive || c2 >= shape().n2) break;
     }
 }
 
