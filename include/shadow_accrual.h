@@ -84,9 +84,8 @@ typedef struct {
                                             (their per-segment views are the launch's working
                                             set); 0 = as many as the view budget allows */
     int32_t batched_grid_blocks;         /* sa_accumulate_batched: blocks of the persistent launch when
-                                            opts->grid_blocks is 0; 0 = 2048 */
-    int32_t batched_tiles_per_grab;      /* sa_accumulate_batched: consecutive 64-point tiles a wave takes
-                                            from the work queue per atomic; 0 = 1 */
+                                            opts->grid_blocks is 0; 0 = as many as the device holds */
+    int32_t batched_tiles_per_grab;      /* kept for callers that set it; the waves take one unit at a time */
     int32_t tile_grid_blocks;            /* sa_accumulate (both forms) and sa_building_contribution:
                                             blocks (of 256 threads) of their persistent launches, whose
                                             waves take (64-point tile, bin) units from a work counter
@@ -271,7 +270,7 @@ typedef struct {
     uint32_t flags;   /* SA_FLAG_ADD */
     float out_scale;  /* minutes are multiplied by this (0 = 1; 1/60 gives hours) */
     int32_t grid_blocks; /* sa_accumulate_batched: blocks of 256 threads in the persistent
-                            launch (0 = default 2048); ignored elsewhere */
+                            launch (0 = the launch setting); ignored elsewhere */
     /* Optional device uint64 [8], added to (not cleared): when non-NULL the
      * launch runs an instrumented instantiation that counts, per lane, the
      * work its own traversal needed -- [0] box tests, [1] prism tests,
@@ -359,8 +358,8 @@ sa_status sa_accumulate_noalloc(sa_ctx *ctx, const sa_scene *scene, const sa_poi
  * var_ids[v*k .. v*k+k) by var_h[v*k ..) (device arrays, original ids,
  * k = ids_per_var), each evaluated on its own points
  * pts[var_off[v] .. var_off[v+1]) (var_off: device int64 [n_var+1]).  One
- * refit per variant and one persistent accrual launch over a (variant,
- * tile) work queue.  Outputs as sa_accumulate over the concatenated points
+ * set of views serves all variants, and one persistent accrual launch their
+ * tiles.  Outputs as sa_accumulate over the concatenated points
  * (SA_ACCRUAL only). */
 sa_status sa_accumulate_batched(sa_ctx *ctx, const sa_scene *scene, int32_t n_var,
                                 int32_t ids_per_var, const int32_t *var_ids, const float *var_h,

@@ -673,12 +673,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
 constexpr int kRowsInFlight = 24;
 
 __global__ __launch_bounds__(64) void k_add_pieces(Sched W, int j0, int j1, const SegConst *__restrict__ segs, int64_t n,
-                                                   BinOut O)
+                                                   BinOut O, const int64_t *__restrict__ var_off, int V)
 {
     const int sub = W.sub > 1 ? W.sub : 1;
     const int r = wg_id_y();
     const int64_t i = (int64_t)wg_id() * 64 + tid();
     if (i >= n) return;
+    if (var_off && (i < var_off[0] || i >= var_off[V])) return;  // no variant's point
     int cnt = 0;
     double mins = 0.0;
     for (int p0 = r * sub; p0 < (r + 1) * sub; p0 += kRowsInFlight) {
@@ -1062,67 +1063,66 @@ __global__ void k_var_heights(int64_t n, int k, const int32_t *__restrict__ ids,
     atomicMax(&tops[prim], __float_as_int(hv));
 }
 
-// Persistent accrual over the (variant, tile) queue.  A wave takes the next
-// tile with one atomic, finds its variant by binary search, and runs every
-// segment for its 64 points on that variant's hierarchy.  A point-segment
-// whose occluded set needs more than four pieces is finished in place by
-// walking its window left to right with halving / doubling sub-windows.
-// Seven waves per SIMD: 72 VGPRs with a few spilled to scratch, measured
-// faster (64.5 ms on 256 variants) than six waves (77 ms) or eight (75 ms).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(const Node *nodes_g, const ViewEntry *views_g,
-                                                      const int32_t *voff_g, const float4 *verts_g,
-                                                      const float *vh_g, int n_b, const SegConst *segs_g, int j0,
-                                                      int j1, PointArgs P, const int64_t *__restrict__ var_off,
-                                                      const int64_t *__restrict__ tile_off, int V,
-                                                      uint32_t *tile_counter, int32_t grab, float scale,
-                                                      int32_t *counts, float *minutes, uint32_t *flag)
+// The accrual form over the variants' tiles, in units as k_accrual's: tile t
+// is variant v's (t - tile_off[v])-th, found by binary search (the launch has
+// as many tiles as there could be; those past the last are empty).  A
+// point-segment whose occluded set needs more than four pieces is finished in
+// place by walking its window left to right with halving / doubling
+// sub-windows.  Seven waves per SIMD: 72 VGPRs with a few spilled to scratch,
+// measured faster than eight (2.39 and 2.46 ms on 32 variants of 1M points) and
+// no slower than six.  Whole tiles as units before, drawn from one counter: 32
+// variants of 1M points on 20,000 prisms took 2.37 ms, in (tile, bin) units
+// 1.70; 40 of 60,000 points on 3,000 prisms 1.05, in pieces 0.25; 5 of 300,000
+// on 400 prisms 1.51 and 0.67.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(
+    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
+    const float *vh_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O,
+    const int64_t *__restrict__ var_off, const int64_t *__restrict__ tile_off, int V, uint32_t *flag)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cSeg *segs = (cSeg *)segs_g;
     __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ int s_O[sizeof(BinOut) / 4];
+    __shared__ int s_W[sizeof(Sched) / 4];
     __shared__ int s_P[sizeof(PointArgs) / 4];
-    StackEntry *stack = s_stack[tid() >> 6];
     __shared__ TileFan s_tile[kWaves];
+    if (tid() == 0) {
+        lds_park((lds_int *)s_O, O);
+        lds_park((lds_int *)s_W, W);
+        lds_park((lds_int *)s_P, P);
+    }
+    __syncthreads();
+    StackEntry *stack = s_stack[tid() >> 6];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
-    const int64_t T = tile_off[V];
-    const int64_t n = P.n;
-    if (tid() == 0) lds_park((lds_int *)s_P, P);
-    __syncthreads();
-    // a wave takes `grab` consecutive (variant, tile) items per atomic
-    int64_t t = 0, t_end = 0;
-    for (;;) {
-        if (t >= t_end) {
-            int64_t g0 = 0;
-            if (lane == 0) g0 = atomicAdd((unsigned long long *)tile_counter, (unsigned long long)grab);
-            g0 = __shfl(g0, 0, 64);
-            t = g0;
-            t_end = min(g0 + (int64_t)grab, T);
-        }
-        if (t >= T) break;
-        int lo = 0, hi = V - 1;               // last v with tile_off[v] <= t
+    Work none{0, 0, 0, 0, 0, 0, 0};
+    int kx = 0;
+    Unit un;
+    while (next_unit((lds_int *)s_W, j0, j1, kx, un)) {
+        const int64_t t = un.tile;
+        if (t >= tile_off[V]) continue;
+        int lo = 0, hi = V - 1;  // last v with tile_off[v] <= t
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (tile_off[mid] <= t) lo = mid;
             else hi = mid - 1;
         }
         const int v = uniform(lo);
+        const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         cfloat *height = (cfloat *)(vh_g + (int64_t)v * n_b);
+        const PointArgs Pd = lds_uniform<PointArgs>((lds_int *)s_P);
+        const int64_t n = Pd.n;
         const int64_t i = var_off[v] + (t - tile_off[v]) * 64 + lane;
         const bool valid = i < var_off[v + 1];
-        const LanePoint q = load_point(lds_uniform<PointArgs>((lds_int *)s_P), i, valid);
+        const LanePoint q = load_point(Pd, i, valid);
         const bool covered = roof_covered<false>((cNode *)nodes_g, stack, verts, height, q, valid);
         int cnt = 0;
         double mins = 0.0;
-        int bin = j1 > j0 ? ld(segs + j0).bin : 0;
-        Work none{0, 0, 0, 0, 0, 0, 0};
-        for (int j = j0; j < j1; ++j) {
+        int bin = jb > ja ? ld(segs + ja).bin : 0;
+        for (int j = ja; j < jb; j += step) {
             const SegConst g = ld(segs + j);
             if (g.bin != bin) {
-                if (valid) {
-                    if (counts) counts[(int64_t)bin * n + i] += cnt;
-                    if (minutes) minutes[(int64_t)bin * n + i] += (float)(mins * scale);
-                }
+                if (valid) put_bin(lds_uniform<BinOut>((lds_int *)s_O), (int64_t)bin * n + i, false, cnt, mins);
                 cnt = 0;
                 mins = 0.0;
                 bin = g.bin;
@@ -1157,11 +1157,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 }
             }
         }
-        if (valid && j1 > j0) {
-            if (counts) counts[(int64_t)bin * n + i] += cnt;
-            if (minutes) minutes[(int64_t)bin * n + i] += (float)(mins * scale);
+        const BinOut Oe = lds_uniform<BinOut>((lds_int *)s_O);
+        if (Oe.pcnt) {
+            // a piece of one bin's run: its sums go to the part's row
+            if (valid) {
+                Oe.pcnt[(int64_t)un.part * n + i] = cnt;
+                Oe.pmin[(int64_t)un.part * n + i] = mins;
+            }
+        } else if (valid && jb > ja) {
+            put_bin(Oe, (int64_t)bin * n + i, false, cnt, mins);
         }
-        ++t;
     }
 }
 
@@ -1268,11 +1273,13 @@ sa_status fill_u32(void *p, int64_t n, uint32_t v, hipStream_t st, std::string &
 
 sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_var, int32_t k, const int32_t *ids,
                          const float *h, const PointsView &pts, const int64_t *var_off, float scale, int32_t *counts,
-                         float *minutes, int32_t grid_blocks, int32_t grab, uint32_t *flag, Scratch &scr,
+                         float *minutes, const TileLaunch &L, uint32_t *grab, uint32_t *flag, Scratch &scr,
                          Scratch &views_scr, hipStream_t st, std::string &err)
 {
     if (n_var == 0 || pts.n == 0) return SA_OK;
-    grab = std::max(grab, 1);
+    // every variant may end with a tile of its own
+    int64_t tiles;
+    if (!tile_count(pts.n / 64 * 64 + (int64_t)n_var * 64, tiles, err)) return SA_ERR_INVALID_ARG;
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     size_t need = 0;
     auto part = [&](size_t bytes) {
@@ -1283,15 +1290,21 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
     const size_t h_at = part(sizeof(float) * (size_t)n_var * s.n_b);
     const size_t tops_at = part(sizeof(float) * (size_t)s.n_b);
     const size_t tile_at = part(sizeof(int64_t) * (n_var + 1));
-    const size_t counter_at = part(256);
-    if (!grow(scr, need, st)) {
+    // on few tiles, runs in pieces as launch_accrual's, their sums behind the
+    // rest; without room for them, whole runs
+    const int64_t res = resident_blocks(k_batched, L);
+    const bool pieces = tiles < 2 * res * kWaves;
+    const int64_t per_part = (int64_t)pts.n * (int64_t)(sizeof(int32_t) + sizeof(double));
+    const size_t piece_at = need;
+    if (!(pieces && grow(scr, piece_at + (size_t)(std::clamp<int64_t>(kPieceBytes / per_part, 1, 8 * res * kWaves) * per_part) + 256, st)) &&
+        !grow(scr, need, st)) {
         err = "variant scratch allocation failed";
         return SA_ERR_OOM;
     }
+    const int64_t max_parts = std::max<int64_t>(((int64_t)(scr.bytes - piece_at) - 256) / per_part, 1);
     char *base = (char *)scr.ptr;
     float *vh = (float *)(base + h_at), *tops = (float *)(base + tops_at);
     int64_t *tile_off = (int64_t *)(base + tile_at);
-    uint32_t *counter = (uint32_t *)(base + counter_at);
     hipLaunchKernelGGL(k_var_copy, dim3(1024), dim3(256), 0, st, (const float *)s.height, s.n_b, n_var, vh, tops, var_off,
                        tile_off);
     const int64_t edits = (int64_t)n_var * k;
@@ -1300,19 +1313,31 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
                            (const int32_t *)s.rank, s.n_b, vh, (int32_t *)tops, flag);
     SA_CHECK_LAUNCH("variant set-up");
     const PointArgs P = point_args(pts, s);
-    const int blocks = grid_blocks > 0 ? grid_blocks : 2048;
     // segment ranges whose views fit the per-launch budget; outputs accumulate
     // across the launches
     const int64_t per = seg_views_cap(s, p, views_scr, st);
-    for (int64_t j0 = 0; j0 < std::max(p.n_segs, 1); j0 += per) {
+    for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views = nullptr;
-        sa_status rc = build_seg_views(s, p, tops, (int)j0, j1, views_scr, {nullptr, counter, 2}, st, views, err);
+        sa_status rc = build_seg_views(s, p, tops, (int)j0, j1, views_scr, {nullptr, grab, 8 * kGrabStride}, st, views, err);
         if (rc != SA_OK) return rc;
-        hipLaunchKernelGGL(k_batched, dim3(blocks), dim3(kThreads), 0, st, s.n_b > 0 ? (const Node *)s.nodes : nullptr,
-                           views, s.voff, s.verts, (const float *)vh, s.n_b, p.segs, (int)j0, j1, P, var_off,
-                           (const int64_t *)tile_off, n_var, counter, grab, scale, counts, minutes, flag);
+        const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, pieces ? Split::kRunPieces : Split::kUniqueBins, res, grab,
+                                   max_parts);
+        BinOut O{counts, minutes, nullptr, nullptr, nullptr, 0, 0, scale, 0};
+        if (W.sub > 1) {
+            const size_t cnt_bytes = (size_t)W.n_parts * (size_t)pts.n * sizeof(int32_t);
+            O.pcnt = (int32_t *)(base + piece_at);
+            O.pmin = (double *)(base + piece_at + ((cnt_bytes + 255) & ~(size_t)255));
+        }
+        hipLaunchKernelGGL(k_batched, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st,
+                           s.n_b > 0 ? (const Node *)s.nodes : nullptr, views, s.n_b, s.voff, s.verts, (const float *)vh,
+                           p.segs, (int)j0, j1, W, P, O, var_off, (const int64_t *)tile_off, n_var, flag);
         SA_CHECK_LAUNCH("batched accrual");
+        if (W.sub > 1) {
+            hipLaunchKernelGGL(k_add_pieces, dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W,
+                               (int)j0, j1, (const SegConst *)p.segs, pts.n, O, var_off, n_var);
+            SA_CHECK_LAUNCH("batched piece sums");
+        }
     }
     return SA_OK;
 }
@@ -1467,7 +1492,8 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
         SA_CHECK_LAUNCH("accrual kernel");
         if (W.sub > 1) {
             hipLaunchKernelGGL(k_add_pieces,
-                               dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W, (int)j0, j1, (const SegConst *)p.segs, pts.n, O);
+                               dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W, (int)j0, j1,
+                               (const SegConst *)p.segs, pts.n, O, (const int64_t *)nullptr, 0);
             SA_CHECK_LAUNCH("accrual piece sums");
         }
         rc = run_spill(s, p, views, (int)j0, P, scale, counts, minutes, minutes64, q, st, err);

@@ -1098,9 +1098,10 @@ sa_status sa_accumulate_batched(sa_ctx *ctx, const sa_scene *scene, int32_t n_va
     rc = clear_outputs(ctx, opts->flags, (int64_t)path->d.n_bins * pts->n, counts, minutes);
     if (rc != SA_OK) return rc;
     std::string err;
-    const int32_t grid = opts->grid_blocks > 0 ? opts->grid_blocks : ctx->launch.batched_grid_blocks;
+    sa::TileLaunch L = tile_launch(ctx);
+    L.grid_blocks = opts->grid_blocks > 0 ? opts->grid_blocks : ctx->launch.batched_grid_blocks;
     rc = sa::launch_batched(scene->d, path->d, n_var, ids_per_var, var_ids, var_h, view(pts), var_off, scale,
-                            counts, minutes, grid, ctx->launch.batched_tiles_per_grab, ctx->spill.counters + 2,
+                            counts, minutes, L, ctx->spill.grab, ctx->spill.counters + 2,
                             ctx->scratch_batched, ctx->scratch_seg, ctx->stream, err);
     if (rc != SA_OK) return fail(ctx, rc, "sa_accumulate_batched: " + err);
     return SA_OK;
