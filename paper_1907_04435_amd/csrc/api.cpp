@@ -839,9 +839,18 @@ sa_status path_upload(sa_ctx *ctx, const sa_sunpath_buf *in, double bound_deg, s
             e = hipMemcpy(p->d.sam_slices, sam.data(), sizeof(sa::SamSlice) * sam.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && !segs.empty()) {
-        e = hipMalloc((void **)&p->d.segs, sizeof(sa::SegConst) * segs.size());
-        if (e == hipSuccess)
-            e = hipMemcpy(p->d.segs, segs.data(), sizeof(sa::SegConst) * segs.size(), hipMemcpyHostToDevice);
+        for (sa::SegConst **d : {&p->d.segs, &p->d.segs_by_reach}) {
+            if (e == hipSuccess) e = hipMalloc((void **)d, sizeof(sa::SegConst) * segs.size());
+            if (e == hipSuccess)
+                e = hipMemcpy(*d, segs.data(), sizeof(sa::SegConst) * segs.size(), hipMemcpyHostToDevice);
+            auto reach = [](const sa::SegConst &g) {
+                return std::max(g.ua_x * g.ua_x + g.ua_y * g.ua_y, g.ub_x * g.ub_x + g.ub_y * g.ub_y);
+            };
+            const auto &rs = p->d.seg_runs.start;
+            for (size_t r = 0; r + 1 < rs.size(); ++r)
+                std::stable_sort(segs.begin() + rs[r], segs.begin() + rs[r + 1],
+                                 [&](const sa::SegConst &a, const sa::SegConst &b) { return reach(a) > reach(b); });
+        }
     }
     if (e == hipSuccess && !chunks.empty()) {
         e = hipMalloc((void **)&p->d.chunks, sizeof(sa::FanChunk) * chunks.size());
@@ -900,6 +909,7 @@ void sa_path_destroy(sa_path *path)
     (void)hipFree(path->d.samples);
     (void)hipFree(path->d.sam_slices);
     (void)hipFree(path->d.segs);
+    (void)hipFree(path->d.segs_by_reach);
     (void)hipFree(path->d.chunks);
     (void)hipFree(path->d.chunk_dirs);
     (void)hipFree(path->d.chunk_sums);

@@ -268,7 +268,7 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views;
-        rc = build_seg_views(s, p, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
+        rc = build_seg_views(s, p.segs, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
         if (rc != SA_OK) return rc;
         SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);

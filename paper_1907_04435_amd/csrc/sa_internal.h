@@ -216,6 +216,7 @@ struct DevicePath {
     SampleConst *samples = nullptr;  // [n_samples]
     SamSlice *sam_slices = nullptr;  // [n_samples] raster slices (unmerged paths)
     SegConst *segs = nullptr;        // [n_segs]
+    SegConst *segs_by_reach = nullptr;  // [n_segs] each bin run's by the sun's height, lowest first (contributions)
     int32_t words = 0;               // ceil(n_samples / 32)
     std::vector<int32_t> day_seg_off;  // host: first segment of each day, [n_days + 1]
     std::vector<int32_t> seg_bin;      // host: output bin of each segment
@@ -340,7 +341,7 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
 // seg_views_cap: segments whose views a launch takes: the per-launch budget,
 // less where scr cannot be grown to it (a fixed scr, or one under stream
 // capture: its size; 0 if not even one fits).
-sa_status build_seg_views(const DeviceScene &s, const DevicePath &p, const float *tops, int j0, int j1, Scratch &scr,
+sa_status build_seg_views(const DeviceScene &s, const SegConst *segs, const float *tops, int j0, int j1, Scratch &scr,
                           const LaunchState &state, hipStream_t st, ViewEntry *&views, std::string &err);
 int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, hipStream_t st);
 // Gross shadow by raster shadow accrual maps (Sec. 4) into counts/minutes

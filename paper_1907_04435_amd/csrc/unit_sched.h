@@ -46,6 +46,18 @@ constexpr int kGrabStride = 32;                  // words between the eight coun
 // 680 and 699.)
 constexpr int64_t kFewUnits = 8;
 
+// Units per resident wave where a launch may cut its runs: one for every
+// kChunkItems or kPieceItems items a wave has, between the bounds.  A unit has
+// its set-up (its points, the roof test, of pieces a row of sums), and the last
+// ones end one by one.  At 3, 4, 6, 8 and 16 units the accrual form on 200,000
+// points (11 items a wave) takes 417, 440, 468, 470 and 515 us, on 400,000
+// points (72 items) 739, 700, 703, 732 and 853; contributions of 300,000 points
+// (29 items) 954, 827, 838, 874 and 943; at 4, 8, 16 and 24 forward and adjoint
+// at 1-minute knots (280 and 370 items) 8.99, 7.50, 6.94 and 6.84 ms; at 8 and 24
+// the sampled form on 1M points (300 chunks) 4.06 and 3.90 ms.
+constexpr int64_t kChunkItems = 5, kPieceItems = 12;
+constexpr int64_t kLeastChunks = 4, kLeastPieces = 3, kMostUnits = 24;
+
 struct Sched {
     const int32_t *part_start;  // first item of each bin run of the launch (clipped to it), or null
     uint32_t *grab;             // eight counters, kGrabStride words apart, zero at launch; null: a
@@ -61,8 +73,8 @@ namespace dev {
 struct Unit {
     uint32_t tile;
     uint32_t part;
-    int a, b;  // the unit's items a, a + step, ... below b
-    int step;  // 1 but for strided parts
+    int a, b;        // the unit's items a, a + step, ... below b
+    int step;        // 1 but for strided parts
 };
 
 // The next unit of the launch whose Sched is parked at s_W, for items
@@ -147,7 +159,7 @@ static int64_t resident_blocks(Kern kern, const TileLaunch &L)
 
 // The units of a persistent launch over items [a0, a1) (segments or
 // instants, whose bin runs are R) for `tiles` 64-point tiles; `blocks` is
-// the launch size (the chunk mode aims at eight units per wave).
+// the launch size.
 static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, Split split, int64_t blocks,
                                uint32_t *grab, int64_t max_parts = 1)
 {
@@ -159,7 +171,8 @@ static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, 
     const int64_t single = (blocks / 8) * kSchedWaves / std::max<int64_t>((tiles + 7) / 8, 1);
     if (split == Split::kChunks) {
         const int64_t items = a1 - a0;
-        const int64_t want = std::max<int64_t>(1, (8 * waves + tiles - 1) / tiles);
+        const int64_t units = std::clamp(tiles * items / (waves * kChunkItems), kLeastChunks, kMostUnits);
+        const int64_t want = std::max<int64_t>(1, (units * waves + tiles - 1) / tiles);
         int64_t parts = std::min(items, want);
         if (single >= 1 && tiles * items <= kFewUnits * waves) {
             parts = std::min(items, single);
@@ -185,11 +198,11 @@ static inline Sched plan_units(const BinRuns &R, int a0, int a1, int64_t tiles, 
     const int64_t runs = r1 - r0 + 1;
     W.n_parts = (uint32_t)runs;
     if (split == Split::kRunPieces) {
-        // pieces per run: eight units per resident wave, no piece shorter
-        // than one item, no more parts than the caller can hold
+        // no piece shorter than one item, no more parts than the caller can hold
         int shortest = a1 - a0;
         for (int r = r0; r <= r1; ++r) shortest = std::min(shortest, std::min(rs[r + 1], a1) - std::max(rs[r], a0));
-        const int64_t want = (8 * waves + tiles * runs - 1) / (tiles * runs);
+        const int64_t units = std::clamp(tiles * (a1 - a0) / (waves * kPieceItems), kLeastPieces, kMostUnits);
+        const int64_t want = (units * waves + tiles * runs - 1) / (tiles * runs);
         int64_t sub = std::min<int64_t>(std::min<int64_t>(want, shortest), std::max<int64_t>(1, max_parts / runs));
         if (single >= runs && tiles * (a1 - a0) <= kFewUnits * waves) {
             sub = std::min(sub, single / runs);
