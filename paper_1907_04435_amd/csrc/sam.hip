@@ -99,10 +99,12 @@ __device__ __forceinline__ void affine_range(const float (&c)[4], float x0, floa
 
 // Items of a wave's group: (slice, prism) pairs whose boxes are tested a lane
 // each before the pairs left are built one by one.  Groups take prisms that
-// lie n_b / 16 apart in hierarchy order, so neighbours (which the points see
+// lie n_b / per apart in hierarchy order, so neighbours (which the points see
 // together) spread over the waves; larger groups leave too few waves when
-// every prism is seen (a slice of 20,000 prisms has 1,250 groups).
-constexpr int kGroup = 16;
+// every prism is seen, as smaller ones do where there are few (30 slices of
+// 300 prisms make 570 groups of 16: 500,000 points among them took 5.0 ms).
+constexpr int kMostGroup = 16;
+constexpr int64_t kLeastGroups = 16384;
 
 // One wave per group, then per (slice, prism) of it whose shadow may fall on
 // texels that points read: texels outside the box of all the points'
@@ -143,21 +145,40 @@ __device__ __forceinline__ float lane_value(float v, int l)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-__global__ __launch_bounds__(kThreads) void k_sam_build(const float4 *__restrict__ verts,
-                                                        const int32_t *__restrict__ voff,
-                                                        const float *__restrict__ height, int n_b, SamGrid g,
-                                                        const SamSlice *__restrict__ slices, int K,
-                                                        const float4 *__restrict__ pbox,
-                                                        const float *__restrict__ bounds,
-                                                        uint32_t *__restrict__ map, uint32_t stamp)
+struct SamBuild {
+    const float4 *verts;
+    const int32_t *voff;
+    const float *height;
+    const float4 *pbox;
+    const float *bounds;
+    const SamSlice *slices;
+    uint32_t *map;
+    int32_t n_b, K;
+    int32_t per;  // prisms per group
+    uint32_t stamp;
+    int32_t blocks;  // 0: nothing to build
+    SamGrid g;
+};
+
+__device__ __forceinline__ void sam_build(const SamBuild &A, int block)
 {
+    const float4 *__restrict__ verts = A.verts;
+    const int32_t *__restrict__ voff = A.voff;
+    const float *__restrict__ height = A.height;
+    const float4 *__restrict__ pbox = A.pbox;
+    const float *__restrict__ bounds = A.bounds;
+    const SamSlice *__restrict__ slices = A.slices;
+    uint32_t *__restrict__ map = A.map;
+    const int n_b = A.n_b, K = A.K;
+    const uint32_t stamp = A.stamp;
+    const SamGrid &g = A.g;
     const int lane = tid() & 63;
     const int lx = lane & 7, ly = lane >> 3;
     const uint32_t tag = stamp << 24;
     const int64_t T = (int64_t)g.nu * g.nv;
-    const int groups = (n_b + kGroup - 1) / kGroup;  // per slice
-    const int64_t nw = (int64_t)n_wg() * kWavesPerBlock;
-    const int64_t w0 = (int64_t)wg_id() * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid() >> 6);
+    const int per = A.per, groups = (n_b + per - 1) / per;  // per slice
+    const int64_t nw = (int64_t)A.blocks * kWavesPerBlock;
+    const int64_t w0 = (int64_t)block * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid() >> 6);
     for (int64_t it = w0; it < (int64_t)K * groups; it += nw) {
         const int k = (int)(it / groups);
         const int first = (int)(it - (int64_t)k * groups);
@@ -182,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void k_sam_build(const float4 *__restrict
         rj1 = fmaxf(fminf(floorf(rj1), (float)(g.nv - 1)), -1.f);
         bool meets = false;
         const int mine = first + lane * groups;
-        if (lane < kGroup && mine < n_b) {
+        if (lane < per && mine < n_b) {
             const float4 q = pbox[mine];
             float bu0, bu1, bv0, bv1;
             affine_range(cu, q.x - g.ox, q.y - g.oy, -g.oz, q.z - g.ox, q.w - g.oy, height[mine] - g.oz, bu0, bu1);
@@ -340,16 +361,35 @@ __global__ __launch_bounds__(kThreads) void k_sam_build(const float4 *__restrict
 // One thread per point: its shadow on each slice, the stored depth there
 // (if written for this segment) against its own depth plus the bias; the
 // segment's counts and minutes added to the point's bin.
-__global__ __launch_bounds__(kThreads) void k_sam_query(const float *__restrict__ px, const float *__restrict__ py,
-                                                        const float *__restrict__ pz, int64_t n, SamGrid g,
-                                                        const SamSlice *__restrict__ slices, int K,
-                                                        const uint32_t *__restrict__ map, uint32_t stamp,
-                                                        int bin, float scale,
-                                                        int32_t *__restrict__ counts, float *__restrict__ minutes)
+struct SamQuery {
+    const float *px, *py, *pz;
+    const SamSlice *slices;
+    const uint32_t *map;
+    int32_t *counts;
+    float *minutes;
+    int64_t n;
+    float scale;
+    int32_t K, bin;
+    uint32_t stamp;
+    int32_t blocks;  // 0: nothing to ask
+    SamGrid g;
+};
+
+__device__ __forceinline__ void sam_query(const SamQuery &A, int block)
 {
+    const float *__restrict__ px = A.px, *__restrict__ py = A.py, *__restrict__ pz = A.pz;
+    const SamSlice *__restrict__ slices = A.slices;
+    const uint32_t *__restrict__ map = A.map;
+    int32_t *__restrict__ counts = A.counts;
+    float *__restrict__ minutes = A.minutes;
+    const int64_t n = A.n;
+    const float scale = A.scale;
+    const int K = A.K, bin = A.bin;
+    const uint32_t stamp = A.stamp;
+    const SamGrid &g = A.g;
     const int64_t T = (int64_t)g.nu * g.nv;
-    const int64_t stride = (int64_t)n_wg() * wg_size();
-    for (int64_t i = (int64_t)wg_id() * wg_size() + tid(); i < n; i += stride) {
+    const int64_t stride = (int64_t)A.blocks * kThreads;
+    for (int64_t i = (int64_t)block * kThreads + tid(); i < n; i += stride) {
         const float rx = px[i] - g.ox, ry = py[i] - g.oy, rz = pz[i] - g.oz;
         const float ra = rx * g.ax + ry * g.ay + rz * g.az - g.c;
         int cnt = 0;
@@ -372,6 +412,23 @@ __global__ __launch_bounds__(kThreads) void k_sam_query(const float *__restrict_
         if (counts) counts[(int64_t)bin * n + i] += cnt;
         if (minutes) minutes[(int64_t)bin * n + i] += mins * scale;
     }
+}
+
+// One segment's map is built while the one before is asked, in one launch with
+// the blocks of both in even mixture: the build computes (60 % of VALU issue),
+// the query waits for its map words, and on few points or prisms neither fills
+// the device.  One after the other: 60,000 points among 300 prisms at 1.5 m 3.26
+// -> 1.54 ms (with groups as large as they may be), among 5,000 2.98 -> 2.22, 5,000
+// points 1.66 -> 1.03; 1M points among 20,000 at 2 m, which fill it, 4.90 -> 5.01.
+// At 5 waves per SIMD (84 VGPRs) that is 5.38, at 7 and 8 (spilling) 5.23 and 5.60.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_sam_step(SamBuild B, SamQuery Q)
+{
+    const uint32_t total = (uint32_t)(B.blocks + Q.blocks), b = (uint32_t)wg_id();
+    const uint32_t q0 = (uint32_t)((uint64_t)b * Q.blocks / total), q1 = (uint32_t)((uint64_t)(b + 1) * Q.blocks / total);
+    if (q1 > q0)
+        sam_query(Q, (int)q0);
+    else
+        sam_build(B, (int)(b - q0));
 }
 
 // Plane and grid of one segment, FP64 (the float32 copy is relative to o):
@@ -490,31 +547,42 @@ sa_status launch_sam(const DeviceScene &s, const DevicePath &p, const PointsView
         most = std::max(most, (int64_t)grids[j].nu * grids[j].nv * sh.ns);
     }
     // the points' bounds and their shares lie behind the map
+    // two maps, one built while the other is asked; where both cannot be had, one
     const size_t map_bytes = ((size_t)most * sizeof(uint32_t) + 255) & ~(size_t)255;
     const size_t bound_bytes = 6 * (kBoundBlocks + 1) * sizeof(float);
-    const size_t need = map_bytes + bound_bytes;
+    const size_t one = map_bytes + bound_bytes, need = one + map_bytes;
     auto clear_all = [&]() {
         const int64_t words = (int64_t)((scr.bytes - bound_bytes) / sizeof(uint32_t));
         hipLaunchKernelGGL(k_sam_clear, dim3((unsigned)std::min<int64_t>((words + kThreads - 1) / kThreads, 65536)),
                            dim3(kThreads), 0, st, (uint32_t *)scr.ptr, words);
         stamp = 0;
     };
-    if (scr.bytes < need) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (scr.bytes < need && hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+    if (scr.bytes < one || (scr.bytes < need && cs == hipStreamCaptureStatusNone)) {
         // the previous contents may still be read by queued kernels
         (void)hipStreamSynchronize(st);
         (void)hipFree(scr.ptr);
         scr.ptr = nullptr;
         scr.bytes = 0;
-        if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-            (void)hipGetLastError();
+        for (const size_t bytes : {need, one}) {
+            if (scr.ptr) break;
+            if (hipMalloc(&scr.ptr, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                scr.ptr = nullptr;
+            } else {
+                scr.bytes = bytes;
+            }
+        }
+        if (!scr.ptr) {
             err = "raster map allocation failed";
             return SA_ERR_OOM;
         }
-        scr.bytes = need;
         clear_all();
         SA_CHECK_LAUNCH("raster map clear");
     }
-    uint32_t *map = (uint32_t *)scr.ptr;
+    const bool two = scr.bytes >= need;
+    uint32_t *maps[2] = {(uint32_t *)scr.ptr, (uint32_t *)((char *)scr.ptr + (two ? map_bytes : 0))};
     float *bounds = (float *)((char *)scr.ptr + scr.bytes - bound_bytes);
     const unsigned bblocks = (unsigned)std::min<int64_t>((pts.n + kThreads - 1) / kThreads, kBoundBlocks);
     hipLaunchKernelGGL(k_sam_bounds, dim3(bblocks), dim3(kThreads), 0, st, pts.x, pts.y, pts.z, pts.n, bounds + 6);
@@ -522,27 +590,43 @@ sa_status launch_sam(const DeviceScene &s, const DevicePath &p, const PointsView
                        bounds);
     SA_CHECK_LAUNCH("raster point bounds");
     const unsigned qblocks = (unsigned)std::min<int64_t>((pts.n + kThreads - 1) / kThreads, 16384);
+    SamBuild B{};
+    SamQuery Q{};
+    auto step = [&]() {
+        if (B.blocks + Q.blocks > 0)
+            hipLaunchKernelGGL(k_sam_step, dim3((unsigned)(B.blocks + Q.blocks)), dim3(kThreads), 0, st, B, Q);
+        B.blocks = Q.blocks = 0;
+    };
+    int turn = 0;
     for (size_t j = 0; j < p.seg_host.size(); ++j) {
         const SamSegHost &sh = p.seg_host[j];
         if (sh.ns == 0) continue;
         const SamGrid &g = grids[j];
         const SamSlice *sl = p.sam_slices + sh.first;
         if (stamp >= 255u) {
+            step();  // the last map is asked before it is cleared
             clear_all();
             SA_CHECK_LAUNCH("raster map clear");
         }
         ++stamp;
-        const int64_t items = (int64_t)sh.ns * ((s.n_b + kGroup - 1) / kGroup);
-        hipLaunchKernelGGL(k_sam_build,
-                           dim3((unsigned)std::min<int64_t>((items + kWavesPerBlock - 1) / kWavesPerBlock, 32768)),
-                           dim3(kThreads), 0, st, (const float4 *)s.verts, (const int32_t *)s.voff,
-                           (const float *)s.height, s.n_b, g, sl, sh.ns, (const float4 *)s.pbox, (const float *)bounds, map,
-                           stamp);
-        SA_CHECK_LAUNCH("raster map build");
-        hipLaunchKernelGGL(k_sam_query, dim3(qblocks), dim3(kThreads), 0, st, pts.x, pts.y, pts.z, pts.n, g, sl,
-                           sh.ns, (const uint32_t *)map, stamp, sh.bin, scale, counts, minutes);
-        SA_CHECK_LAUNCH("raster map query");
+        int per = kMostGroup;
+        while (per > 1 && (int64_t)sh.ns * ((s.n_b + per - 1) / per) < kLeastGroups) per /= 2;
+        const int64_t items = (int64_t)sh.ns * ((s.n_b + per - 1) / per);
+        uint32_t *map = maps[turn ^= 1];
+        B = SamBuild{s.verts, s.voff, s.height, s.pbox, bounds, sl, map, s.n_b, sh.ns, per, stamp,
+                     (int32_t)std::min<int64_t>((items + kWavesPerBlock - 1) / kWavesPerBlock, 32768), g};
+        if (!two && Q.blocks > 0) {  // the one map is asked before it is built again
+            const SamBuild next = B;
+            B.blocks = 0;
+            step();
+            B = next;
+        }
+        step();
+        SA_CHECK_LAUNCH("raster map");
+        Q = SamQuery{pts.x, pts.y, pts.z, sl, map, counts, minutes, pts.n, scale, sh.ns, sh.bin, stamp, (int32_t)qblocks, g};
     }
+    step();
+    SA_CHECK_LAUNCH("raster map query");
     return SA_OK;
 }
 
