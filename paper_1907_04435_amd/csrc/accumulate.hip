@@ -545,48 +545,21 @@ __device__ __forceinline__ void accrue_segment(const SegSrc &src, cfloat4 *verts
 
 __global__ void k_clear_state(LaunchState L) { clear_state(L, tid()); }
 
-// Roof-covered: inside a footprint (other than the point's own building)
-// and not above that roof -- shadowed from every direction.  Without kTops
-// the boxes' tops are not looked at (hierarchies whose heights are not those
-// of `height`: the footprints alone decide what is tested).
-template <bool kTops = true>
-__device__ __forceinline__ bool roof_covered(cNode *nodes, StackEntry *stack, cfloat4 *verts, cfloat *height,
-                                             const LanePoint &q, bool valid)
-{
-    if (nodes == nullptr) return false;
-    uint64_t covm = 0;
-    auto bt = [&](float x0, float y0, float x1, float y1, float z1) {
-        return q.px >= x0 && q.px <= x1 && q.py >= y0 && q.py <= y1 && (!kTops || q.pz <= z1);
-    };
-    auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
-        const bool t = lane_in(want) && prim != q.own && q.pz <= ld(height + prim) &&
-                       in_footprint(verts, voff, m, q.px, q.py);
-        const uint64_t tm = ballot(t);
-        covm |= tm;
-        return tm;
-    };
-    auto key = [&](float, float, float, float, float) { return 0.f; };
-    Work none{0, 0, 0, 0, 0, 0, 0};
-    packet_traverse<false>(nodes, stack, ballot(valid), bt, leaf, key, none);
-    return lane_in(covm);
-}
-
 // kOcc waves per SIMD, a launch choice (6, 7 or 8; the tuner measures
 // them).  At 8 the kernel fits in 64 VGPRs (the compiler would settle for
 // fewer waves otherwise), which hides more of the scalar-load and
 // compare-chain latency of the traversal loop.
 template <bool kCount, int kOcc>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))) void k_accrual(
-    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
+    RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, SpillArgs S,
     uint64_t *work)
 {
     Work wk{0, 0, 0, 0, 0, 0, 0};
-    cNode *nodes = (cNode *)nodes_g;
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ int s_B[sizeof(RoofBoxes) / 4];
     // the outputs are needed only when a bin ends, the schedule once per
     // unit: parked in LDS so their pointers hold no scalar registers
     // through the traversal loop
@@ -599,9 +572,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
         lds_park((lds_int *)s_S, S);
         lds_park((lds_int *)s_W, W);
         lds_park((lds_int *)s_P, P);
+        lds_park((lds_int *)s_B, B);
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
     __shared__ TileFan s_tile[kWaves];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
@@ -614,7 +587,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(nodes_g ? nodes : nullptr, stack, verts, height, q, valid);
+        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
 
         int cnt = 0;
         double mins = 0.0;  // per-lane FP64: long spans sum thousands of segment measures
@@ -731,15 +704,14 @@ __device__ __forceinline__ void runs_update(const Union4 &U, float w0, float w1,
 // waves per SIMD (the compiler fits the kernel in 72 VGPRs) measured 4 %
 // faster than the six its natural allocation allows.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_accrual_runs(
-    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
+    RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, float *longest,
     uint32_t *overflow)
 {
-    cNode *nodes = (cNode *)nodes_g;
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ int s_B[sizeof(RoofBoxes) / 4];
     // outputs (and where to flag overflow), schedule and points parked in
     // LDS: needed once per unit or at a bin's end, they hold no scalar
     // registers through the traversal
@@ -752,11 +724,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         lds_park((lds_int *)s_O, O);
         lds_park((lds_int *)s_W, W);
         lds_park((lds_int *)s_P, P);
+        lds_park((lds_int *)s_B, B);
         s_longest = longest;
         s_overflow = overflow;
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
     __shared__ TileFan s_tile[kWaves];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
@@ -769,7 +741,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(nodes_g ? nodes : nullptr, stack, verts, height, q, valid);
+        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         const int ja = uniform(un.a), jb = uniform(un.b);
 
         int cnt = 0;
@@ -1075,13 +1047,13 @@ __global__ void k_var_heights(int64_t n, int k, const int32_t *__restrict__ ids,
 // 1.70; 40 of 60,000 points on 3,000 prisms 1.05, in pieces 0.25; 5 of 300,000
 // on 400 prisms 1.51 and 0.67.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(
-    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
+    RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *vh_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O,
     const int64_t *__restrict__ var_off, const int64_t *__restrict__ tile_off, int V, uint32_t *flag)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ int s_B[sizeof(RoofBoxes) / 4];
     __shared__ int s_O[sizeof(BinOut) / 4];
     __shared__ int s_W[sizeof(Sched) / 4];
     __shared__ int s_P[sizeof(PointArgs) / 4];
@@ -1090,9 +1062,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         lds_park((lds_int *)s_O, O);
         lds_park((lds_int *)s_W, W);
         lds_park((lds_int *)s_P, P);
+        lds_park((lds_int *)s_B, B);
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
     Work none{0, 0, 0, 0, 0, 0, 0};
@@ -1115,7 +1087,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const int64_t i = var_off[v] + (t - tile_off[v]) * 64 + lane;
         const bool valid = i < var_off[v + 1];
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered<false>((cNode *)nodes_g, stack, verts, height, q, valid);
+        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         int cnt = 0;
         double mins = 0.0;
         int bin = jb > ja ? ld(segs + ja).bin : 0;
@@ -1203,6 +1175,8 @@ static bool grow(Scratch &scr, size_t need, hipStream_t st)
     scr.bytes = need;
     return true;
 }
+
+static RoofBoxes roof_boxes(const DeviceScene &s) { return RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}; }
 
 static PointArgs point_args(const PointsView &pts, const DeviceScene &s)
 {
@@ -1330,7 +1304,7 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
             O.pmin = (double *)(base + piece_at + ((cnt_bytes + 255) & ~(size_t)255));
         }
         hipLaunchKernelGGL(k_batched, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st,
-                           s.n_b > 0 ? (const Node *)s.nodes : nullptr, views, s.n_b, s.voff, s.verts, (const float *)vh,
+                           roof_boxes(s), views, s.n_b, s.voff, s.verts, (const float *)vh,
                            p.segs, (int)j0, j1, W, P, O, var_off, (const int64_t *)tile_off, n_var, flag);
         SA_CHECK_LAUNCH("batched accrual");
         if (W.sub > 1) {
@@ -1404,7 +1378,6 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     if (pts.n == 0) return SA_OK;
     int64_t tiles;
     if (!tile_count(pts.n, tiles, err)) return SA_ERR_INVALID_ARG;
-    const Node *nodes = s.n_b > 0 ? s.nodes : nullptr;
     const PointArgs P = point_args(pts, s);
     // Long spans run as several launches over consecutive segment ranges,
     // each about kChunkWork point-segments and covering at most
@@ -1439,7 +1412,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             const int64_t res = resident_blocks(k_accrual_runs, L);
             const Sched W = plan_units(p.seg_runs, j0, j1, tiles, Split::kUniqueBins, res, q.grab);
             hipLaunchKernelGGL(k_accrual_runs, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
-                               st, nodes, views, s.n_b, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
+                               st, roof_boxes(s), views, s.n_b, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
                                bin_out(p, j0, store, counts, minutes, minutes64, scale), longest, q.counters + 2);
             SA_CHECK_LAUNCH("accrual kernel (continuous shadow)");
             d0 = d1;
@@ -1487,7 +1460,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             O.pcnt = (int32_t *)piece_scr.ptr;
             O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, nodes, views, s.n_b,
+        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, roof_boxes(s), views, s.n_b,
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
         SA_CHECK_LAUNCH("accrual kernel");
         if (W.sub > 1) {

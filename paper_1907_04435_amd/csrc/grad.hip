@@ -105,27 +105,6 @@ __device__ __forceinline__ void scatter_grad(const UnionG &U, bool ok, float wsc
     }
 }
 
-__device__ __forceinline__ bool roof_covered_g(cNode *nodes, StackEntry *stack, cfloat4 *verts, cfloat *height,
-                                               const LanePoint &q, bool valid)
-{
-    if (nodes == nullptr) return false;
-    uint64_t covm = 0;
-    auto bt = [&](float x0, float y0, float x1, float y1, float z1) {
-        return q.px >= x0 && q.px <= x1 && q.py >= y0 && q.py <= y1 && q.pz <= z1;
-    };
-    auto leaf = [&](int prim, int voff, int m, uint64_t want) -> uint64_t {
-        const bool t = lane_in(want) && prim != q.own && q.pz <= ld(height + prim) &&
-                       in_footprint(verts, voff, m, q.px, q.py);
-        const uint64_t tm = ballot(t);
-        covm |= tm;
-        return tm;
-    };
-    auto key = [&](float, float, float, float, float) { return 0.f; };
-    Work none{0, 0, 0, 0, 0, 0, 0};
-    packet_traverse<false>(nodes, stack, ballot(valid), bt, leaf, key, none);
-    return lane_in(covm);
-}
-
 // Six waves per SIMD: at seven (72 VGPRs) the interval sets with their owners
 // spill 87 registers, at five there are too few waves (forward and adjoint on
 // 200k points, 1-minute knots: 10.77, 10.15 and 10.69 ms at 7, 6 and 5).
@@ -133,14 +112,13 @@ __device__ __forceinline__ bool roof_covered_g(cNode *nodes, StackEntry *stack, 
 // keep every wave busy on small point sets (the gradient sums are atomic, so
 // any split adds up the same).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_grad(
-    const Node *nodes_g, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
+    RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, GradArgs G, SpillArgs S)
 {
-    cNode *nodes = nodes_g ? (cNode *)nodes_g : nullptr;
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
     cSeg *segs = (cSeg *)segs_g;
-    __shared__ StackEntry s_stack[kWaves][kStackDepth];
+    __shared__ int s_B[sizeof(RoofBoxes) / 4];
     __shared__ int s_W[sizeof(Sched) / 4];
     __shared__ int s_P[sizeof(PointArgs) / 4];
     __shared__ int s_G[sizeof(GradArgs) / 4];
@@ -148,11 +126,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     if (tid() == 0) {
         lds_park((lds_int *)s_W, W);
         lds_park((lds_int *)s_P, P);
+        lds_park((lds_int *)s_B, B);
         lds_park((lds_int *)s_G, G);
         lds_park((lds_int *)s_S, S);
     }
     __syncthreads();
-    StackEntry *stack = s_stack[tid() >> 6];
     __shared__ TileFan s_tile[kWaves];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
@@ -164,7 +142,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < Pd.n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered_g(nodes, stack, verts, height, q, valid);
+        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         int bin = -1;
         float w = 0.f;
         for (int j = ja; j < jb; j += step) {
@@ -272,7 +250,7 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
         if (rc != SA_OK) return rc;
         SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
-        hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, s.nodes, views,
+        hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}, views,
                            s.n_b, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
         hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, (int)j0, s.voff,
                            s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, (const uint32_t *)q.counters,

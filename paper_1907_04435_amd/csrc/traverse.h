@@ -1320,5 +1320,86 @@ __device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *
     }
 }
 
+// Footprint boxes of the prisms and of the views' groups (DeviceScene), for
+// the roof test; n_b = 0: an empty scene.
+struct RoofBoxes {
+    const float4 *pbox, *gbox;
+    const int32_t *vorder;
+    int32_t n_b, pad;
+};
+
+// Roof-covered: inside a footprint (other than the point's own building)
+// and not above that roof -- shadowed from every direction.  As walk_view, a
+// lane takes a box: against the box of the wave's points, all 64 lanes here.
+// Bound by its memory round trips, four where the binary hierarchy took one a
+// level, once a unit: 16,384 points on 64 prisms 40.9 -> 38.4 us, 20,000 on 300
+// 43.5 -> 39.1, 4M on 20,000 7.20 -> 7.00 ms, forward and adjoint at 1-minute
+// knots 6.83 -> 6.67 ms.
+__device__ __forceinline__ bool roof_covered(const RoofBoxes &B, cint *voff, cfloat4 *verts, cfloat *height,
+                                             const LanePoint &q, bool valid)
+{
+    const uint64_t asked = ballot(valid);
+    if (B.n_b == 0 || !asked) return false;
+    float x0 = valid ? q.px : INFINITY, x1 = valid ? q.px : -INFINITY;
+    float y0 = valid ? q.py : INFINITY, y1 = valid ? q.py : -INFINITY;
+    // (each step reads what was written three instructions before)
+#define SA_STEP(ctrl)                          \
+    "v_min_f32_dpp %[x0], %[x0], %[x0] " ctrl  \
+    "v_max_f32_dpp %[x1], %[x1], %[x1] " ctrl  \
+    "v_min_f32_dpp %[y0], %[y0], %[y0] " ctrl  \
+    "v_max_f32_dpp %[y1], %[y1], %[y1] " ctrl
+    asm volatile("s_nop 4\n" SA_STEP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n")
+                     SA_STEP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n")
+                         SA_STEP("row_ror:4 row_mask:0xf bank_mask:0xf\n")
+                             SA_STEP("row_ror:8 row_mask:0xf bank_mask:0xf\n")
+                                 SA_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf\n")
+                                     SA_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf\n") "s_nop 0"
+                 : [x0] "+v"(x0), [x1] "+v"(x1), [y0] "+v"(y0), [y1] "+v"(y1));
+#undef SA_STEP
+    auto last = [](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); };
+    const float X0 = last(x0), X1 = last(x1), Y0 = last(y0), Y1 = last(y1);
+    auto meets = [&](const float4 &b) {
+        return ballot(pad_lo(b.x) <= X1 && pad_hi(b.z) >= X0 && pad_lo(b.y) <= Y1 && pad_hi(b.w) >= Y0);
+    };
+    auto first_of = [](int n) -> uint64_t { return n >= 64 ? ~0ull : (1ull << n) - 1ull; };
+    const ViewShape sh = view_shape(B.n_b);
+    const int lane = (int)(tid() & 63);
+    uint64_t cov = 0;
+    for (int c2 = 0; c2 < sh.n2; c2 += 64) {
+        uint64_t m2 = 1ull;
+        if (sh.n2 > 1) m2 = meets(B.gbox[sh.n1 + min(c2 + lane, sh.n2 - 1)]) & first_of(sh.n2 - c2);
+        for (; m2; m2 &= m2 - 1ull) {
+            const int b1 = (c2 + (int)__builtin_ctzll(m2)) << kSuperBits;
+            uint64_t m1 = 1ull;
+            if (sh.n1 > 1) m1 = meets(B.gbox[min(b1 + lane, sh.n1 - 1)]) & first_of(sh.n1 - b1);
+            while (m1) {
+                // two groups at a time, half a wave each
+                const int ka = (int)__builtin_ctzll(m1);
+                m1 &= m1 - 1ull;
+                const int kb = m1 ? (int)__builtin_ctzll(m1) : ka;
+                const uint64_t both = m1 ? ~0ull : 0xffffffffull;
+                m1 &= m1 - 1ull;
+                const int mine = ((b1 + (lane < 32 ? ka : kb)) << kGroupBits) + (lane & 31);
+                const int prim = B.vorder[min(mine, B.n_b - 1)];
+                const float4 box = B.pbox[prim];
+                uint64_t m0 = meets(box) & both & ballot(mine < B.n_b);
+                for (; m0; m0 &= m0 - 1ull) {
+                    // few points lie in a box that their tile's meets
+                    const int k = (int)__builtin_ctzll(m0);
+                    const int b = __builtin_amdgcn_readlane(prim, k);
+                    auto at = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k)); };
+                    uint64_t want = asked & ~cov & ballot(b != q.own && q.px >= pad_lo(at(box.x)) && q.px <= pad_hi(at(box.z)) &&
+                                                         q.py >= pad_lo(at(box.y)) && q.py <= pad_hi(at(box.w)));
+                    if (!want) continue;
+                    want &= ballot(q.pz <= ld(height + b));
+                    const int v0 = ld(voff + b);
+                    cov |= want & ballot(in_footprint(verts, v0, ld(voff + b + 1) - v0, q.px, q.py));
+                }
+            }
+        }
+    }
+    return lane_in(cov);
+}
+
 }  // namespace dev
 }  // namespace sa
