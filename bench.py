@@ -67,7 +67,7 @@ def committed_traffic(workload, seg):
         return None
     rec = json.load(open(p))
     src = "".join(open(os.path.join(ROOT, "paper_1907_04435_amd", "csrc", f)).read()
-                  for f in ("accumulate.hip", "traverse.h"))
+                  for f in ("accumulate.hip", "traverse.h", "views.h"))
     if hashlib.sha256(src.encode()).hexdigest()[:16] != rec["source_hash"]:
         return None
     return rec["traffic_bytes"]

@@ -19,7 +19,7 @@ using namespace dev;
 constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
 constexpr int kSpillBlocks = 1024;
-constexpr int64_t kChunkWork = 4000000000ll;  // point-segments per accrual launch
+constexpr int64_t kChunkWork = 2000000000ll;  // point-segments per contribution launch
 // Views per launch.  A launch has its set-up, its spilled
 // windows and a last unit that others wait for: a year on 45,000 prisms and
 // 500,000 points takes 236, 219 and 207 ms in launches of 150, 300 and 600
@@ -1380,7 +1380,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     if (!tile_count(pts.n, tiles, err)) return SA_ERR_INVALID_ARG;
     const PointArgs P = point_args(pts, s);
     // Long spans run as several launches over consecutive segment ranges,
-    // each about kChunkWork point-segments and covering at most
+    // each about kSpillWork point-segments and covering at most
     // kViewBytes of views (built just before it);
     // outputs are accumulated, so the split is invisible in the results.
     const int64_t cap = seg_views_cap(s, p, scr, st);
@@ -1389,7 +1389,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
               " bytes) exceed the fixed scratch (" + std::to_string(scr.bytes) + " bytes)";
         return SA_ERR_CAPACITY;
     }
-    int64_t per = std::min(std::max<int64_t>(1, kChunkWork / std::max<int64_t>(pts.n, 1)), std::max<int64_t>(cap, 1));
+    int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(pts.n, 1)), std::max<int64_t>(cap, 1));
     if (seg_per_launch > 0) per = std::min<int64_t>(per, seg_per_launch);
     if (longest) {
         // whole days per launch, so a run never spans two launches (one
@@ -1485,7 +1485,7 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
     const PointArgs P = point_args(pts, s);
     // long spans: several launches over consecutive segment ranges
     const int64_t per =
-        std::min(std::max<int64_t>(1, kChunkWork / 2 / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
+        std::min(std::max<int64_t>(1, kChunkWork / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views;

@@ -73,7 +73,6 @@ struct sa_path {
 
 namespace {
 
-constexpr int32_t kSpillCapacity = 1 << 20;
 
 sa_status fail(sa_ctx *ctx, sa_status rc, const std::string &msg)
 {
@@ -179,8 +178,8 @@ sa_status sa_create(int32_t device, void *hip_stream, sa_ctx **out)
     if (!c) return SA_ERR_OOM;
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
-    c->spill.capacity = kSpillCapacity;
-    if (hipMalloc((void **)&c->spill.entries, sizeof(int4) * kSpillCapacity) != hipSuccess ||
+    c->spill.capacity = sa::kSpillCapacity;
+    if (hipMalloc((void **)&c->spill.entries, sizeof(int4) * sa::kSpillCapacity) != hipSuccess ||
         hipMalloc((void **)&c->spill.counters, sizeof(uint32_t) * kCounterWords) != hipSuccess ||
         hipMemset(c->spill.counters, 0, sizeof(uint32_t) * kCounterWords) != hipSuccess) {
         sa_destroy(c);

@@ -242,7 +242,7 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     const GradArgs G{dl, acc, s.order};
     // segment ranges whose per-segment views fit the budget, each
     // followed by its spill rounds
-    const int64_t per = seg_views_cap(s, p, scr, st);
+    const int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views;

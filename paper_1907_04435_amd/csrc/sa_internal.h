@@ -242,6 +242,12 @@ struct DevicePath {
 
 // Scratch owned by a context (grown on demand, freed with it), or a fixed
 // buffer the library never grows or frees (fixed = true).
+// Point-segments of a launch that queues its spilled windows, and the queue's
+// entries: one in 1e4 spills on the block scenes (one in 120 fills the queue).
+// An entry is 16 bytes.
+constexpr int64_t kSpillWork = 500000000ll;
+constexpr int32_t kSpillCapacity = 1 << 22;
+
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
