@@ -53,7 +53,11 @@ __global__ __launch_bounds__(kViewThreads) void k_views(const int32_t *__restric
     const int b1 = g2 << kSuperBits, b0 = g2 * kSuperPrisms;
     auto key_of = [&](const float4 &q) { return seg_key(q.x, q.y, q.z, q.w, mdx, mdy); };
     auto first_of = [](int n) -> uint64_t { return n >= 64 ? ~0ull : (1ull << n) - 1ull; };
-    const float key1 = key_of(gbox[min(b1 + lane, sh.n1 - 1)]);
+    // a group comes where its near edge does: one that holds the points comes
+    // before those beyond, wherever its middle lies (4,000 points among 15,000
+    // prisms 248 -> 204 us, 4M among 20,000 in a strip 6.82 -> 6.74 ms)
+    auto near_of = [&](const float4 &q) { return (mdx > 0.f ? q.x : q.z) * mdx + (mdy > 0.f ? q.y : q.w) * mdy; };
+    const float key1 = near_of(gbox[min(b1 + lane, sh.n1 - 1)]);
     const uint64_t in1 = first_of(sh.n1 - b1);
     // terms as maxima: the second and fourth negated
     float most[6] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -105,7 +109,7 @@ __global__ __launch_bounds__(kViewThreads) void k_views(const int32_t *__restric
     if (tid() >= 64) return;
     // the first wave: this group of groups' entry among 64 of them
     const int c2 = g2 & ~63;
-    const float key2 = key_of(gbox[sh.n1 + min(c2 + lane, sh.n2 - 1)]);
+    const float key2 = near_of(gbox[sh.n1 + min(c2 + lane, sh.n2 - 1)]);
     const int r2 = near_rank(key2, first_of(sh.n2 - c2), g2 - c2);
     for (unsigned k = 0; k < 6; ++k) {
         float m = -INFINITY;
