@@ -697,7 +697,7 @@ __device__ __forceinline__ void runs_update(const Union4 &U, float w0, float w1,
 
 // The accrual form with the continuous shadow of every point.  Runs must be
 // followed in time order, so a segment whose set needs more than four
-// pieces is not queued for the spill rounds: the lane walks that segment
+// pieces is not queued as a spilled window: the lane walks that segment
 // window by window from its start (halving the window on overflow,
 // doubling it after a success) while the other lanes wait.  A window would
 // have to shrink below theta / 4096 to raise the overflow flag.  Seven

@@ -241,7 +241,7 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     const PointArgs P{pts.n, pts.x, pts.y, pts.z, pts.nx, pts.ny, pts.owner, s.rank, s.n_b};
     const GradArgs G{dl, acc, s.order};
     // segment ranges whose per-segment views fit the budget, each
-    // followed by its spill rounds
+    // followed by its spilled windows
     const int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
