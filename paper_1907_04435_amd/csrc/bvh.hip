@@ -1,7 +1,8 @@
 // Device construction of the building hierarchy: footprint boxes, Morton
 // codes of their centres, an LSD radix sort, the binary radix tree of the
 // sorted codes (Karras, HPG 2012), and a bottom-up refit of the boxes with
-// per-node arrival counters.  Every step runs on the GPU; the host only
+// per-node arrival counters; beside it the views' order (a Hilbert curve,
+// sorted the same way) and their groups' footprint boxes.  Every step runs on the GPU; the host only
 // validates the input and sizes the buffers.
 #include <hip/hip_runtime.h>
 
