@@ -175,14 +175,14 @@ __device__ __forceinline__ uint32_t chunk_back(std::integer_sequence<int, K...>,
     return back;
 }
 
-// Bound by VALU issue: on 1M points of the 20,000-prism scene over three days
-// (2.16e9 rays) the pass takes 5.5 ms against 26.2 ms for the packets, with
-// 4.8e7 node fetches and 3.8e6 leaf visits of 400 live rays each.  Chunks of
-// 32 instants walk less (2.8e7 fetches) but test more rays a leaf (7.4
-// against 7.0 ms, both before the edges were paired).  63 VGPRs; 6, 7 and 8
-// waves per SIMD: 5.8, 5.5 and 5.4 ms there, 161, 173 and 184 us on 20,000
-// points and 400 prisms, where a wave's own latency counts and the scalar
-// registers spilled at 7 and 8 are felt.
+// Bound by VALU issue (94 % of it on the block scene): 1M points of the
+// 20,000-prism scene over three days (2.16e9 rays) take 3.9 ms against 26.2 ms
+// for the packets, with 3.8e6 leaf visits of 400 live rays each.  Over the binary
+// hierarchy it was 5.0 ms (4.8e7 node fetches); there chunks of 32 instants walked
+// less (2.8e7 fetches) but tested more rays a leaf (7.4 against 7.0 ms, both
+// before the edges were paired), and 6, 7 and 8 waves per SIMD took 5.8, 5.5 and
+// 5.4 ms, 161, 173 and 184 us on 20,000 points and 400 prisms, where a wave's own
+// latency counts and the scalar registers spilled at 7 and 8 are felt.
 template <bool kCount>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_sampled_fan(
     const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
