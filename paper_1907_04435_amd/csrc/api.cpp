@@ -1176,7 +1176,6 @@ sa_status sa_region_score(sa_ctx *ctx, const sa_path *path, const float *values,
     if (ctx->scratch_w.bytes < need) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->scratch_w.ptr);
-    (void)hipFree(ctx->scratch_edit.ptr);
         ctx->scratch_w.ptr = nullptr;
         ctx->scratch_w.bytes = 0;
         hipError_t e = hipMalloc(&ctx->scratch_w.ptr, need);

@@ -1,0 +1,137 @@
+// What the library's host code asks of the runtime, without a device: memory
+// that calls share between them, and launches.  One scenario a run, by name;
+// 0 if it holds.
+#include "fake_hip.h"
+
+#include <vector>
+
+#include "shadow_accrual.h"
+
+namespace {
+
+int bad = 0;
+
+#define CHECK(c)                                                            \
+    do {                                                                    \
+        if (!(c)) {                                                         \
+            std::printf("line %d: %s does not hold\n", __LINE__, #c);       \
+            ++bad;                                                          \
+        }                                                                   \
+    } while (0)
+// a call of the library that succeeds
+#define OK(ctx, c)                                                                        \
+    do {                                                                                  \
+        if ((c) != SA_OK) {                                                               \
+            std::printf("line %d: %s: %s\n", __LINE__, #c, sa_last_error(ctx));           \
+            ++bad;                                                                        \
+        }                                                                                 \
+    } while (0)
+
+template <class T>
+T *device(size_t n)
+{
+    void *p = nullptr;
+    (void)hipMalloc(&p, sizeof(T) * (n ? n : 1));
+    return (T *)p;
+}
+
+// n unit squares a hundred metres apart, whose order on the device is their own.
+sa_scene *upload(sa_ctx *ctx, int n)
+{
+    std::vector<int32_t> off;
+    std::vector<float> xy, h(n, 10.f);
+    for (int b = 0; b <= n; ++b) off.push_back(4 * b);
+    for (int b = 0; b < n; ++b)
+        for (const auto &c : {std::pair<float, float>{0, 0}, {1, 0}, {1, 1}, {0, 1}}) {
+            xy.push_back(100.f * (b % 200) + c.first);
+            xy.push_back(100.f * (b / 200) + c.second);
+        }
+    sa_scene *s = nullptr;
+    fake::rt().read = [n](void *d, size_t bytes) {
+        int32_t *w = (int32_t *)d;
+        if (bytes == sizeof(int32_t) * (size_t)n)  // the ranks
+            for (int b = 0; b < n; ++b) w[b] = b;
+        else if (bytes == 64 * (size_t)(n - 1))  // the nodes: a chain, words 10 and 11 the children
+            for (int b = 0; b < n - 1; ++b) {
+                w[16 * b + 10] = ~b;
+                w[16 * b + 11] = b < n - 2 ? b + 1 : ~(n - 1);
+            }
+        else
+            return false;
+        return true;
+    };
+    OK(ctx, sa_scene_upload(ctx, n, off.data(), xy.data(), h.data(), &s));
+    fake::rt().read = nullptr;
+    return s;
+}
+
+// `days` days at the given steps, a bin each, or all in one.
+sa_path *upload_path(sa_ctx *ctx, int days, double step, double seg, bool one_bin = false)
+{
+    const sa_site site{40.7, -74.0, -5.0};
+    const sa_timespan span{2019, 1, 1, days, 480.0, 960.0, step, seg, 0};
+    sa_sunpath_buf b{};
+    CHECK(sa_sunpath(&site, &span, &b) == SA_OK);
+    std::vector<int32_t> so(days + 1), ko(days + 1), bin(days);
+    std::vector<double> t(b.n_samples), d(3 * b.n_samples), w(b.n_samples), kt(b.n_knots), kd(3 * b.n_knots);
+    b.cap_days = days;
+    b.cap_samples = b.n_samples;
+    b.cap_knots = b.n_knots;
+    b.day_sample_off = so.data();
+    b.t_min = t.data();
+    b.dir = d.data();
+    b.weight = w.data();
+    b.day_knot_off = ko.data();
+    b.knot_t = kt.data();
+    b.knot_dir = kd.data();
+    CHECK(sa_sunpath(&site, &span, &b) == SA_OK);
+    b.day_bin = one_bin ? bin.data() : nullptr;
+    sa_path *p = nullptr;
+    OK(ctx, sa_path_upload(ctx, &b, &p));
+    return p;
+}
+
+// Long height edits stage their arrays in memory of their own, whatever a
+// region score does with its weights in between.
+void edit_score()
+{
+    sa_ctx *ctx = nullptr;
+    CHECK(sa_create(0, nullptr, &ctx) == SA_OK);
+    const size_t before = fake::rt().live.size();
+    sa_scene *s = upload(ctx, 100);
+    sa_path *one = upload_path(ctx, 1, 5.0, 30.0), *five = upload_path(ctx, 5, 5.0, 30.0);
+    std::vector<int32_t> ids(80);
+    std::vector<float> h(80, 20.f);
+    for (int k = 0; k < 80; ++k) ids[k] = k;
+    float *v = device<float>(5 * 10);
+    int64_t *off = device<int64_t>(2);
+    double *out = device<double>(1);
+    const double w[5] = {1, 1, 1, 1, 1};
+    OK(ctx, sa_scene_set_heights(ctx, s, 80, ids.data(), h.data()));
+    OK(ctx, sa_region_score(ctx, one, v, 10, w, off, 1, nullptr, out));
+    OK(ctx, sa_scene_set_heights(ctx, s, 80, ids.data(), h.data()));
+    OK(ctx, sa_region_score(ctx, five, v, 10, w, off, 1, nullptr, out));
+    OK(ctx, sa_scene_set_heights(ctx, s, 80, ids.data(), h.data()));
+    sa_path_destroy(one);
+    sa_path_destroy(five);
+    sa_scene_destroy(s);
+    CHECK(fake::rt().live.size() > before);
+    sa_destroy(ctx);
+    CHECK(fake::rt().live.size() == 3);  // the test's own
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}};
+    const auto it = all.find(argc > 1 ? argv[1] : "");
+    if (it == all.end()) {
+        std::printf("no such scenario\n");
+        return 2;
+    }
+    it->second();
+    bad += fake::rt().faults;
+    std::printf("%s: %s\n", it->first.c_str(), bad ? "FAILED" : "holds");
+    return bad ? 1 : 0;
+}
