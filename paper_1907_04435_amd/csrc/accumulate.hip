@@ -1159,21 +1159,14 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
         }                                                                       \
     } while (0)
 
-static bool grow(Scratch &scr, size_t need, hipStream_t st)
+// Parts of n points whose sums the scratch has room for.  Asked for in one
+// size, whatever the call: no call then frees what a graph captured over
+// another holds, and one under capture finds what an eager one left.
+static int64_t piece_parts(Scratch &scr, int64_t n, hipStream_t st)
 {
-    if (scr.bytes >= need) return true;
-    // the previous contents may still be read by queued kernels
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(scr.ptr);
-    scr.ptr = nullptr;
-    scr.bytes = 0;
-    if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-        (void)hipGetLastError();
-        scr.ptr = nullptr;
-        return false;
-    }
-    scr.bytes = need;
-    return true;
+    (void)reserve(scr, (size_t)kPieceBytes + 256, st);
+    const int64_t per_part = n * (int64_t)(sizeof(int32_t) + sizeof(double));
+    return std::max<int64_t>(0, (int64_t)scr.bytes - 256) / per_part;
 }
 
 static RoofBoxes roof_boxes(const DeviceScene &s) { return RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}; }
@@ -1248,7 +1241,7 @@ sa_status fill_u32(void *p, int64_t n, uint32_t v, hipStream_t st, std::string &
 sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_var, int32_t k, const int32_t *ids,
                          const float *h, const PointsView &pts, const int64_t *var_off, float scale, int32_t *counts,
                          float *minutes, const TileLaunch &L, uint32_t *grab, uint32_t *flag, Scratch &scr,
-                         Scratch &views_scr, hipStream_t st, std::string &err)
+                         Scratch &views_scr, Scratch &piece_scr, hipStream_t st, std::string &err)
 {
     if (n_var == 0 || pts.n == 0) return SA_OK;
     // every variant may end with a tile of its own
@@ -1264,18 +1257,14 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
     const size_t h_at = part(sizeof(float) * (size_t)n_var * s.n_b);
     const size_t tops_at = part(sizeof(float) * (size_t)s.n_b);
     const size_t tile_at = part(sizeof(int64_t) * (n_var + 1));
-    // on few tiles, runs in pieces as launch_accrual's, their sums behind the
-    // rest; without room for them, whole runs
-    const int64_t res = resident_blocks(k_batched, L);
-    const bool pieces = tiles < 2 * res * kWaves;
-    const int64_t per_part = (int64_t)pts.n * (int64_t)(sizeof(int32_t) + sizeof(double));
-    const size_t piece_at = need;
-    if (!(pieces && grow(scr, piece_at + (size_t)(std::clamp<int64_t>(kPieceBytes / per_part, 1, kMostUnits * res * kWaves) * per_part) + 256, st)) &&
-        !grow(scr, need, st)) {
-        err = "variant scratch allocation failed";
+    if (!reserve(scr, need, st)) {
+        err = "no room for the variants' heights (under stream capture an eager call of the size comes first)";
         return SA_ERR_OOM;
     }
-    const int64_t max_parts = std::max<int64_t>(((int64_t)(scr.bytes - piece_at) - 256) / per_part, 1);
+    // on few tiles, runs in pieces as launch_accrual's
+    const int64_t res = resident_blocks(k_batched, L);
+    const bool pieces = tiles < 2 * res * kWaves;
+    const int64_t max_parts = pieces ? piece_parts(piece_scr, pts.n, st) : 1;
     char *base = (char *)scr.ptr;
     float *vh = (float *)(base + h_at), *tops = (float *)(base + tops_at);
     int64_t *tile_off = (int64_t *)(base + tile_at);
@@ -1300,8 +1289,8 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
         BinOut O{counts, minutes, nullptr, nullptr, nullptr, 0, 0, scale, 0};
         if (W.sub > 1) {
             const size_t cnt_bytes = (size_t)W.n_parts * (size_t)pts.n * sizeof(int32_t);
-            O.pcnt = (int32_t *)(base + piece_at);
-            O.pmin = (double *)(base + piece_at + ((cnt_bytes + 255) & ~(size_t)255));
+            O.pcnt = (int32_t *)piece_scr.ptr;
+            O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
         hipLaunchKernelGGL(k_batched, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st,
                            roof_boxes(s), views, s.n_b, s.voff, s.verts, (const float *)vh,
@@ -1323,12 +1312,10 @@ int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, h
     if (s.n_b == 0) return std::max(p.n_segs, 1);
     const int64_t want = std::max<int64_t>(1, std::min<int64_t>(kViewBytes / per_seg, p.n_segs));
     if (scr.bytes >= (size_t)(want * per_seg)) return want;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
-    if (cs != hipStreamCaptureStatusNone) return std::max<int64_t>(1, (int64_t)scr.bytes / per_seg);
+    if (capturing(st)) return std::max<int64_t>(1, (int64_t)scr.bytes / per_seg);
     for (int64_t budget = kViewBytes; budget > kLeastViewBytes; budget /= 2) {
         const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(budget / per_seg, p.n_segs));
-        if (grow(scr, (size_t)(cap * per_seg), st)) return cap;
+        if (reserve(scr, (size_t)(cap * per_seg), st)) return cap;
     }
     return std::max<int64_t>(1, kLeastViewBytes / per_seg);
 }
@@ -1348,8 +1335,8 @@ sa_status build_seg_views(const DeviceScene &s, const SegConst *segs, const floa
               std::to_string(scr.bytes);
         return SA_ERR_CAPACITY;
     }
-    if (!grow(scr, need, st)) {
-        err = "segment view allocation failed";
+    if (!reserve(scr, need, st)) {
+        err = "no room for the segment views (under stream capture an eager call of the size comes first)";
         return SA_ERR_OOM;
     }
     views = (ViewEntry *)scr.ptr;
@@ -1425,26 +1412,11 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     const int64_t res = resident_blocks(kern, L);
     // Too few tiles to give every resident wave several (tile, bin) units:
     // each bin's run is then cut into pieces, held as per-piece sums in
-    // piece_scr ([part][n] counts and FP64 minutes) and added up in order
-    // by a second kernel, so the results stay deterministic.  Without room
-    // for the sums (a fixed scratch), whole runs.
+    // piece_scr ([part][n] counts, then, 256-byte aligned, FP64 minutes) and
+    // added up in order by a second kernel, so the results stay deterministic.
+    // Without room for the sums, whole runs.
     const bool pieces = tiles < 2 * res * kWaves;
-    int64_t max_parts = 1;
-    if (pieces) {
-        // counts of every part, then (256-byte aligned) their FP64 minutes
-        const int64_t per_part = (int64_t)pts.n * (int64_t)(sizeof(int32_t) + sizeof(double));
-        if (piece_scr.fixed) {
-            max_parts = std::max<int64_t>(0, (int64_t)piece_scr.bytes - 256) / per_part;
-        } else {
-            max_parts = std::max<int64_t>(1, kPieceBytes / per_part);
-            const size_t need = (size_t)(std::min<int64_t>(max_parts, kMostUnits * res * kWaves) * per_part) + 256;
-            if (!grow(piece_scr, need, st)) {
-                err = "accrual piece sums allocation failed";
-                return SA_ERR_OOM;
-            }
-            max_parts = ((int64_t)piece_scr.bytes - 256) / per_part;
-        }
-    }
+    const int64_t max_parts = pieces ? piece_parts(piece_scr, pts.n, st) : 1;
     for (int64_t j0 = 0; j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views;

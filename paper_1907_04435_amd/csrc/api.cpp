@@ -21,7 +21,7 @@ struct sa_ctx {
     std::string err;
     sa::SpillQueue spill;
     sa::Scratch scratch;          // region sums
-    sa::Scratch scratch_batched;  // per-variant hierarchy copies
+    sa::Scratch scratch_batched;  // variants' heights and tiles
     sa::Scratch scratch_seg;      // per-segment views of the accrual form
     sa::Scratch scratch_sam;      // one segment's raster shadow accrual map
     sa::Scratch scratch_grad;     // FP64 height-gradient accumulator
@@ -968,13 +968,7 @@ static bool accrual_stores(const sa_accum_opts *opts, const sa_path *path)
 // a later larger call may free under a captured graph.
 static bool takes_fans(const sa_ctx *ctx)
 {
-    if (ctx->launch.sampled_instants_per_packet != 0) return false;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return cs == hipStreamCaptureStatusNone;
+    return ctx->launch.sampled_instants_per_packet == 0 && !sa::capturing(ctx->stream);
 }
 
 sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts, const sa_path *path,
@@ -1111,7 +1105,7 @@ sa_status sa_accumulate_batched(sa_ctx *ctx, const sa_scene *scene, int32_t n_va
     L.grid_blocks = opts->grid_blocks > 0 ? opts->grid_blocks : ctx->launch.batched_grid_blocks;
     rc = sa::launch_batched(scene->d, path->d, n_var, ids_per_var, var_ids, var_h, view(pts), var_off, scale,
                             counts, minutes, L, ctx->spill.grab, ctx->spill.counters + 2,
-                            ctx->scratch_batched, ctx->scratch_seg, ctx->stream, err);
+                            ctx->scratch_batched, ctx->scratch_seg, ctx->scratch_piece, ctx->stream, err);
     if (rc != SA_OK) return fail(ctx, rc, "sa_accumulate_batched: " + err);
     return SA_OK;
 }

@@ -240,19 +240,52 @@ struct DevicePath {
     std::vector<double> sample_t, sample_w;
 };
 
-// Scratch owned by a context (grown on demand, freed with it), or a fixed
-// buffer the library never grows or frees (fixed = true).
 // Point-segments of a launch that queues its spilled windows, and the queue's
 // entries: one in 1e4 spills on the block scenes (one in 120 fills the queue).
 // An entry is 16 bytes.
 constexpr int64_t kSpillWork = 500000000ll;
 constexpr int32_t kSpillCapacity = 1 << 22;
 
+// Scratch owned by a context (grown on demand, freed with it), or a fixed
+// buffer the library never grows or frees (fixed = true).
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
     bool fixed = false;
 };
+
+// Is the stream being captured, or may it be (the runtime does not say)?
+inline bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+// Room for `need` bytes in scr: what it holds, where that is enough; else new
+// memory, once the stream's work is done with the old.  Not of a fixed one, nor
+// under stream capture, which neither the wait nor the allocation may be part
+// of: false, and scr is as it was.  False with nothing in scr where the memory
+// cannot be had.
+inline bool reserve(Scratch &scr, size_t need, hipStream_t st)
+{
+    if (scr.bytes >= need) return true;
+    if (scr.fixed || capturing(st)) return false;
+    (void)hipStreamSynchronize(st);
+    (void)hipFree(scr.ptr);
+    scr.ptr = nullptr;
+    scr.bytes = 0;
+    if (hipMalloc(&scr.ptr, need) != hipSuccess) {
+        (void)hipGetLastError();
+        scr.ptr = nullptr;
+        return false;
+    }
+    scr.bytes = need;
+    return true;
+}
 
 // Host-side builders implemented in the .hip sources.
 sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t *voff,
@@ -321,7 +354,7 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
 // each bin is stored by the launch holding its first segment.
 // L: the launch choices (segments per launch, persistent grid size).
 // piece_scr: per-piece sums when the tiles are too few to fill the device
-// (grown on demand unless fixed; a fixed one of 0 bytes keeps whole runs).
+// (whole runs where there is no room for them).
 sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const PointsView &pts,
                          float scale, int32_t *counts, float *minutes, double *minutes64, float *longest,
                          uint64_t *work, bool store, const TileLaunch &L, SpillQueue &q, Scratch &scr,
@@ -362,7 +395,7 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
                          const int32_t *ids, const float *h, const PointsView &pts,
                          const int64_t *var_off, float scale, int32_t *counts, float *minutes,
                          const TileLaunch &L, uint32_t *grab, uint32_t *flag, Scratch &scr, Scratch &views_scr,
-                         hipStream_t st, std::string &err);
+                         Scratch &piece_scr, hipStream_t st, std::string &err);
 // Graph-capturable fill of n 32-bit words.
 sa_status fill_u32(void *p, int64_t n, uint32_t v, hipStream_t st, std::string &err);
 

@@ -357,22 +357,6 @@ __global__ __launch_bounds__(kThreads) void k_sampled_bits(const uint16_t *__res
     bits[o] = begun ? (bits[o] | v) : v;
 }
 
-sa_status grow(Scratch &scr, size_t need, hipStream_t st)
-{
-    if (scr.bytes >= need) return SA_OK;
-    (void)hipStreamSynchronize(st);  // queued kernels may still read it
-    (void)hipFree(scr.ptr);
-    scr.ptr = nullptr;
-    scr.bytes = 0;
-    if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-        (void)hipGetLastError();
-        scr.ptr = nullptr;
-        return SA_ERR_OOM;
-    }
-    scr.bytes = need;
-    return SA_OK;
-}
-
 }  // namespace
 
 #define SA_CHECK_LAUNCH(what)                                                   \
@@ -416,8 +400,8 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     const int64_t ranges = (pts.n + fit - 1) / fit;  // of equal length: no short last one
     const int64_t range = ((pts.n + ranges - 1) / ranges + 63) / 64 * 64;
     // no room: the caller's other kernels need none
-    if (grow(views_scr, (size_t)(most * view), st) != SA_OK) return SA_OK;
-    if (grow(mask_scr, (size_t)(most * range * 2), st) != SA_OK) return SA_OK;
+    if (!reserve(views_scr, (size_t)(most * view), st)) return SA_OK;
+    if (!reserve(mask_scr, (size_t)(most * range * 2), st)) return SA_OK;
     taken = true;
     uint16_t *masks = (uint16_t *)mask_scr.ptr;
     auto kern = work ? k_sampled_fan<true> : k_sampled_fan<false>;

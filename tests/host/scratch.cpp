@@ -120,11 +120,67 @@ void edit_score()
     CHECK(fake::rt().live.size() == 3);  // the test's own
 }
 
+// A call on n points of a context's scene and path.
+struct Calls {
+    sa_ctx *ctx = nullptr;
+    sa_scene *scene = nullptr;
+    sa_path *path = nullptr;
+    static constexpr int kMost = 5000000, kVariants = 4;
+    float *x = device<float>(kMost), *minutes = device<float>(kMost), *var_h = device<float>(kVariants);
+    int32_t *counts = device<int32_t>(kMost), *var_ids = device<int32_t>(kVariants);
+    int64_t *var_off = device<int64_t>(kVariants + 1);
+
+    Calls(int prisms, int days, double seg)
+    {
+        OK(ctx, sa_create(0, nullptr, &ctx));
+        scene = upload(ctx, prisms);
+        path = upload_path(ctx, days, 30.0, seg, true);
+    }
+    ~Calls()
+    {
+        sa_path_destroy(path);
+        sa_scene_destroy(scene);
+        sa_destroy(ctx);
+    }
+    sa_points points(int64_t n) const { return sa_points{n, x, x, x, nullptr, nullptr, nullptr}; }
+    void accrual(int64_t n)
+    {
+        const sa_points p = points(n);
+        const sa_accum_opts o{SA_ACCRUAL, 0, 1.f, 0, nullptr, nullptr, nullptr};
+        OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
+    }
+    void batched(int64_t n)
+    {
+        const sa_points p = points(n);
+        const sa_accum_opts o{SA_ACCRUAL, 0, 1.f, 0, nullptr, nullptr, nullptr};
+        OK(ctx, sa_accumulate_batched(ctx, scene, kVariants, 1, var_ids, var_h, &p, var_off, path, &o, counts, minutes));
+    }
+};
+
+// After an eager call of a size, calls of that size or less can be captured:
+// nothing waits, is allocated or freed; and eager ones leave the memory a graph
+// was captured over.
+void capture()
+{
+    for (const bool batched : {false, true})
+        for (const int64_t first : {(int64_t)100000, (int64_t)Calls::kMost}) {  // in pieces, and too large for them
+            Calls c(100, 2, 30.0);
+            auto call = [&](int64_t n) { batched ? c.batched(n) : c.accrual(n); };
+            call(first);
+            const int frees = fake::rt().frees;
+            fake::rt().capturing = true;
+            for (const int64_t n : {100000, 90000, 64, 1}) call(n);
+            fake::rt().capturing = false;
+            for (const int64_t n : {90000, 1, 100000}) call(n);
+            CHECK(fake::rt().frees == frees);
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}};
+    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) {
         std::printf("no such scenario\n");

@@ -1,5 +1,6 @@
 """The library's host code over a runtime without a device (tests/host):
-memory is freed once and used only while it lives."""
+memory is freed once and used only while it lives, and none is asked for under
+stream capture."""
 import os
 import shutil
 import subprocess
@@ -26,7 +27,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["edit_score"])
+@pytest.mark.parametrize("scenario", ["edit_score", "capture"])
 def test_holds(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     print(r.stdout, r.stderr)
