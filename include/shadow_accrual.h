@@ -422,11 +422,11 @@ typedef struct {
  * edges; prisms outside `box` are missed.  Points: ground-type only (any
  * z; pts->owner, nx and ny must be NULL: walls would shade themselves).
  * Outputs as sa_accumulate (counts int32, minutes float, [n_bins * n],
- * either may be NULL).  The library keeps two segments' maps, or one (4 bytes per
- * texel and slice: a segment stamp and the depth to about 1 / 2^24 of its
- * range) in memory the context owns, grown on first need; calls on one
- * context must not overlap.  Not
- * for direction-graph paths.
+ * either may be NULL).  The library keeps two segments' maps where both
+ * stay within max_texels and can be had, else one (4 bytes per texel and
+ * slice: a segment stamp and the depth to about 1 / 2^24 of its range) in
+ * memory the context owns, grown on first need; calls on one context must
+ * not overlap.  Not for direction-graph paths.
  * Errors: INVALID_ARG, CAPACITY (a map above max_texels), OOM, DEVICE. */
 sa_status sa_sam_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts,
                             const sa_path *path, const sa_sam_opts *opts, int32_t *counts,

@@ -1164,7 +1164,7 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
 // another holds, and one under capture finds what an eager one left.
 static int64_t piece_parts(Scratch &scr, int64_t n, hipStream_t st)
 {
-    (void)reserve(scr, (size_t)kPieceBytes + 256, st);
+    (void)reserve_wish(scr, (size_t)kPieceBytes + 256, st);
     const int64_t per_part = n * (int64_t)(sizeof(int32_t) + sizeof(double));
     return std::max<int64_t>(0, (int64_t)scr.bytes - 256) / per_part;
 }
@@ -1310,14 +1310,11 @@ int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, h
     const int64_t per_seg = std::max<int64_t>(view_bytes(s.n_b), 1);
     if (scr.fixed) return (int64_t)scr.bytes / per_seg;
     if (s.n_b == 0) return std::max(p.n_segs, 1);
-    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(kViewBytes / per_seg, p.n_segs));
-    if (scr.bytes >= (size_t)(want * per_seg)) return want;
-    if (capturing(st)) return std::max<int64_t>(1, (int64_t)scr.bytes / per_seg);
-    for (int64_t budget = kViewBytes; budget > kLeastViewBytes; budget /= 2) {
-        const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(budget / per_seg, p.n_segs));
-        if (reserve(scr, (size_t)(cap * per_seg), st)) return cap;
-    }
-    return std::max<int64_t>(1, kLeastViewBytes / per_seg);
+    auto fit = [&](int64_t budget) { return std::max<int64_t>(1, std::min<int64_t>(budget / per_seg, p.n_segs)); };
+    for (int64_t budget = kViewBytes; budget > kLeastViewBytes; budget /= 2)
+        if (reserve_wish(scr, (size_t)(fit(budget) * per_seg), st)) return fit(budget);
+    const int64_t held = (int64_t)scr.bytes / per_seg;
+    return std::max<int64_t>(held, capturing(st) ? 1 : fit(kLeastViewBytes));
 }
 
 sa_status build_seg_views(const DeviceScene &s, const SegConst *segs, const float *tops, int j0, int j1, Scratch &scr,

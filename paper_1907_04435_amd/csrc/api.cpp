@@ -23,7 +23,7 @@ struct sa_ctx {
     sa::Scratch scratch;          // region sums
     sa::Scratch scratch_batched;  // variants' heights and tiles
     sa::Scratch scratch_seg;      // per-segment views of the accrual form
-    sa::Scratch scratch_sam;      // one segment's raster shadow accrual map
+    sa::Scratch scratch_sam;      // one or two segments' raster shadow accrual maps
     sa::Scratch scratch_grad;     // FP64 height-gradient accumulator
     sa::Scratch scratch_w;        // per-bin weights of a region score
     sa::Scratch scratch_edit;     // staging of long height edits

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -252,6 +253,8 @@ struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
     bool fixed = false;
+    uint32_t made = 0;           // allocations so far: a change means new contents
+    size_t refused = SIZE_MAX;   // the least size that could not be had
 };
 
 // Is the stream being captured, or may it be (the runtime does not say)?
@@ -265,6 +268,14 @@ inline bool capturing(hipStream_t st)
     return cs != hipStreamCaptureStatusNone;
 }
 
+inline void release(Scratch &scr, hipStream_t st)
+{
+    (void)hipStreamSynchronize(st);  // queued kernels may still read it
+    (void)hipFree(scr.ptr);
+    scr.ptr = nullptr;
+    scr.bytes = 0;
+}
+
 // Room for `need` bytes in scr: what it holds, where that is enough; else new
 // memory, once the stream's work is done with the old.  Not of a fixed one, nor
 // under stream capture, which neither the wait nor the allocation may be part
@@ -274,18 +285,23 @@ inline bool reserve(Scratch &scr, size_t need, hipStream_t st)
 {
     if (scr.bytes >= need) return true;
     if (scr.fixed || capturing(st)) return false;
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(scr.ptr);
-    scr.ptr = nullptr;
-    scr.bytes = 0;
+    release(scr, st);
     if (hipMalloc(&scr.ptr, need) != hipSuccess) {
         (void)hipGetLastError();
         scr.ptr = nullptr;
+        scr.refused = std::min(scr.refused, need);
         return false;
     }
     scr.bytes = need;
+    ++scr.made;
+    if (need >= scr.refused) scr.refused = SIZE_MAX;
     return true;
 }
+
+// The same for a size the caller can do without: one that was refused (or a
+// larger one) is not asked for again, and what scr holds stays.
+inline bool hopeless(const Scratch &scr, size_t need) { return need > scr.bytes && need >= scr.refused; }
+inline bool reserve_wish(Scratch &scr, size_t need, hipStream_t st) { return !hopeless(scr, need) && reserve(scr, need, st); }
 
 // Host-side builders implemented in the .hip sources.
 sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t *voff,
@@ -343,8 +359,9 @@ sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const Points
                          std::string &err);
 // The sampled form by fans of instants, with views and mask words in
 // views_scr and mask_scr (grown as needed, with the stream synchronised
-// first).  taken = false, with nothing enqueued, where they cannot be had:
-// launch_sampled gives the same results without scratch.  store: outputs need
+// first).  taken = false, with nothing enqueued, where they cannot be had (a
+// size refused once is not asked for again): launch_sampled gives the same
+// results without scratch.  store: outputs need
 // no clearing (no SA_FLAG_ADD and p.chunk_bins_all).
 sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const PointsView &pts, float scale,
                              int32_t *counts, float *minutes, uint32_t *bits, float *longest, uint64_t *work, bool store,
@@ -385,8 +402,8 @@ sa_status build_seg_views(const DeviceScene &s, const SegConst *segs, const floa
 int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, hipStream_t st);
 // Gross shadow by raster shadow accrual maps (Sec. 4) into counts/minutes
 // [n_bins * n] (already cleared): per segment a map of slices x nu x nv
-// 64-bit words (stamp, depth) in scr (grown as needed; max_texels caps one
-// segment's map); stamp: the last segment stamp written into scr, kept by
+// 32-bit words (stamp, depth) in scr (grown as needed; max_texels caps one
+// segment's map, and both where two fit); stamp: the last segment stamp written into scr, kept by
 // the caller with scr.
 sa_status launch_sam(const DeviceScene &s, const DevicePath &p, const PointsView &pts, double texel,
                      double bias, const double box[6], int64_t max_texels, float scale, int32_t *counts,

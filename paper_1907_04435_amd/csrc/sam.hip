@@ -547,7 +547,8 @@ sa_status launch_sam(const DeviceScene &s, const DevicePath &p, const PointsView
         most = std::max(most, (int64_t)grids[j].nu * grids[j].nv * sh.ns);
     }
     // the points' bounds and their shares lie behind the map
-    // two maps, one built while the other is asked; where both cannot be had, one
+    // two maps, one built while the other is asked; one where both cannot be had
+    // or would pass the cap
     const size_t map_bytes = ((size_t)most * sizeof(uint32_t) + 255) & ~(size_t)255;
     const size_t bound_bytes = 6 * (kBoundBlocks + 1) * sizeof(float);
     const size_t one = map_bytes + bound_bytes, need = one + map_bytes;
@@ -557,27 +558,12 @@ sa_status launch_sam(const DeviceScene &s, const DevicePath &p, const PointsView
                            dim3(kThreads), 0, st, (uint32_t *)scr.ptr, words);
         stamp = 0;
     };
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (scr.bytes < need && hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
-    if (scr.bytes < one || (scr.bytes < need && cs == hipStreamCaptureStatusNone)) {
-        // the previous contents may still be read by queued kernels
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(scr.ptr);
-        scr.ptr = nullptr;
-        scr.bytes = 0;
-        for (const size_t bytes : {need, one}) {
-            if (scr.ptr) break;
-            if (hipMalloc(&scr.ptr, bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                scr.ptr = nullptr;
-            } else {
-                scr.bytes = bytes;
-            }
-        }
-        if (!scr.ptr) {
-            err = "raster map allocation failed";
-            return SA_ERR_OOM;
-        }
+    const uint32_t made = scr.made;
+    if (!(most <= max_texels / 2 && reserve_wish(scr, need, st)) && !reserve(scr, one, st)) {
+        err = "no room for a raster map (under stream capture an eager call of the size comes first)";
+        return SA_ERR_OOM;
+    }
+    if (scr.made != made) {
         clear_all();
         SA_CHECK_LAUNCH("raster map clear");
     }

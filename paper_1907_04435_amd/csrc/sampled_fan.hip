@@ -400,8 +400,12 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     const int64_t ranges = (pts.n + fit - 1) / fit;  // of equal length: no short last one
     const int64_t range = ((pts.n + ranges - 1) / ranges + 63) / 64 * 64;
     // no room: the caller's other kernels need none
-    if (!reserve(views_scr, (size_t)(most * view), st)) return SA_OK;
-    if (!reserve(mask_scr, (size_t)(most * range * 2), st)) return SA_OK;
+    const size_t view_need = (size_t)(most * view), mask_need = (size_t)(most * range * 2);
+    if (hopeless(views_scr, view_need) || !reserve_wish(mask_scr, mask_need, st)) return SA_OK;
+    if (!reserve(views_scr, view_need, st)) {
+        release(mask_scr, st);
+        return SA_OK;
+    }
     taken = true;
     uint16_t *masks = (uint16_t *)mask_scr.ptr;
     auto kern = work ? k_sampled_fan<true> : k_sampled_fan<false>;

@@ -22,6 +22,7 @@ struct Runtime {
     std::map<const void *, std::string> names;     // kernels by their host stub
     std::map<std::string, int> launches;           // by (mangled) name
     size_t limit = SIZE_MAX;                       // largest allocation granted
+    size_t largest = 0;                            // and asked for
     int mallocs = 0, frees = 0, refused = 0, syncs = 0, faults = 0;
     bool capturing = false;                        // every stream
     std::function<bool(void *, size_t)> read;      // fills a copy to the host in the kernels' place, if it knows it
@@ -105,6 +106,7 @@ hipError_t hipMalloc(void **p, size_t n)
     fake::Runtime &r = fake::rt();
     *p = nullptr;
     if (r.capturing) fake::fault("allocation under capture", nullptr);
+    r.largest = n > r.largest ? n : r.largest;
     if (n > r.limit) {
         ++r.refused;
         return hipErrorOutOfMemory;

@@ -149,6 +149,18 @@ struct Calls {
         const sa_accum_opts o{SA_ACCRUAL, 0, 1.f, 0, nullptr, nullptr, nullptr};
         OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
     }
+    void sampled(int64_t n)
+    {
+        const sa_points p = points(n);
+        const sa_accum_opts o{SA_SAMPLED, 0, 1.f, 0, nullptr, nullptr, nullptr};
+        OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
+    }
+    void raster(int64_t n)
+    {
+        const sa_points p = points(n);
+        const sa_sam_opts o{2.f, 0.1f, {0, 0, 0, 2000, 2000, 20}, 0, 1.f, 0};
+        OK(ctx, sa_sam_accumulate(ctx, scene, &p, path, &o, counts, minutes));
+    }
     void batched(int64_t n)
     {
         const sa_points p = points(n);
@@ -176,11 +188,59 @@ void capture()
         }
 }
 
+// Where the memory a call would like cannot be had, the first call finds that
+// out and every later one takes what is there: no wait, no allocation tried, no
+// buffer given up.
+void short_of_memory()
+{
+    fake::Runtime &r = fake::rt();
+    const size_t kMiB = 1 << 20;
+    auto settled = [&](auto call) {
+        call();
+        const int refused = r.refused, mallocs = r.mallocs, frees = r.frees, syncs = r.syncs;
+        CHECK(refused > 0);
+        call();
+        call();
+        CHECK(r.refused == refused && r.mallocs == mallocs && r.frees == frees && r.syncs == syncs);
+        r.refused = 0;
+        r.limit = SIZE_MAX;
+    };
+    for (const size_t limit : {600 * kMiB, 300 * kMiB}) {  // the views: half the wish, or the least
+        Calls c(20000, 20, 5.0);
+        r.limit = limit;
+        settled([&]() { c.accrual(1000000); });
+    }
+    {  // and the sums of pieces beside them
+        Calls c(20000, 20, 5.0);
+        r.limit = 100 * kMiB;
+        Calls few(100, 2, 30.0);
+        settled([&]() { few.accrual(1000); });
+    }
+    for (const bool masks : {false, true}) {  // the sampled form's views, or its masks
+        Calls c(masks ? 100 : 20000, masks ? 3 : 20, 5.0);
+        r.limit = 4 * kMiB;
+        const int packets = fake::launches("k_sampled_q"), fans = fake::launches("k_sampled_fan");
+        settled([&]() { c.sampled(1000000); });
+        CHECK(fake::launches("k_sampled_q") == packets + 3 && fake::launches("k_sampled_fan") == fans);
+        c.sampled(1);  // a size not refused
+        CHECK(fake::launches("k_sampled_fan") > fans);
+    }
+    {  // the second raster map
+        Calls a(100, 1, 30.0), b(100, 1, 30.0);
+        r.largest = 0;
+        a.raster(1000);
+        r.limit = r.largest - 1;
+        const int clears = fake::launches("k_sam_clear");
+        settled([&]() { b.raster(1000); });
+        CHECK(fake::launches("k_sam_clear") == clears + 1);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}};
+    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}, {"short_of_memory", short_of_memory}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) {
         std::printf("no such scenario\n");

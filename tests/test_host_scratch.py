@@ -1,6 +1,6 @@
 """The library's host code over a runtime without a device (tests/host):
 memory is freed once and used only while it lives, and none is asked for under
-stream capture."""
+stream capture, nor twice where it was refused."""
 import os
 import shutil
 import subprocess
@@ -27,7 +27,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["edit_score", "capture"])
+@pytest.mark.parametrize("scenario", ["edit_score", "capture", "short_of_memory"])
 def test_holds(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     print(r.stdout, r.stderr)
