@@ -620,8 +620,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
             } else if (!ov) {
                 measure(U, gm, 0.f, gm.theta, true, mins, cnt);
             }
-            if (ballot(valid && ov))
-                spill_push(lds_uniform<SpillArgs>((lds_int *)s_S), valid && ov, i, j, 0.f, gm.theta);
+            const uint64_t over = ballot(valid && ov);
+            if (over) spill_push(lds_uniform<SpillArgs>((lds_int *)s_S), over, (int)i, j);
         }
         const BinOut Oe = lds_uniform<BinOut>((lds_int *)s_O);
         if (Oe.pcnt) {
@@ -820,11 +820,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
 // The lanes' measures are summed across the wave and added with one atomic
 // per output.  One launch: as three rounds over two queues, with their
 // clears, it was seven (4 us each and the gaps where nothing is queued).
-__global__ __launch_bounds__(kThreads) void k_spill(const ViewEntry *views_g, int n_b, int j0, const int32_t *voff_g,
-                                                    const float4 *verts_g, const float *height_g,
-                                                    const SegConst *segs_g, PointArgs P, float scale, int32_t *counts,
-                                                    float *minutes, double *minutes64, const int4 *in,
-                                                    const uint32_t *in_count, int32_t cap, uint32_t *overflow)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_spill(
+    const ViewEntry *views_g, int n_b, int j0, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
+    const SegConst *segs_g, PointArgs P, float scale, int32_t *counts, float *minutes, double *minutes64,
+    const int4 *queue, uint32_t *counters, int32_t cap)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
@@ -834,17 +833,17 @@ __global__ __launch_bounds__(kThreads) void k_spill(const ViewEntry *views_g, in
     __shared__ TileFan s_tile[kWaves];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
-    const int64_t total = min((int32_t)*in_count, cap);
-    const int64_t stride = (int64_t)n_wg() * kWaves;
-    for (int64_t e = (int64_t)wg_id() * kWaves + (tid() >> 6); e < total; e += stride) {
-        const int4 en = in[e];
-        const int64_t i = uniform(en.x);
-        const int j = uniform(en.y);
+    uint32_t singles;
+    const int64_t total = spill_items(counters, cap, singles), stride = (int64_t)n_wg() * kWaves;
+    for (int64_t t = (int64_t)wg_id() * kWaves + (tid() >> 6); t < total; t += stride) {
+        int j;
+        const int64_t i = spill_item(queue, singles, t, j);
+        if (i < 0) continue;
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
         const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b, (cint *)voff_g,
                          tile, height};
-        SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
+        SpillWindow win{0.f, g.theta, 0};
         double mins = 0.0;
         int cnt = 0;
         for (int waiting = 0;;) {
@@ -855,7 +854,7 @@ __global__ __launch_bounds__(kThreads) void k_spill(const ViewEntry *views_g, in
             Work none{0, 0, 0, 0, 0, 0, 0};
             accrue_segment<false>(src, verts, g, q, true, w0, w1, U, ov, none);
             if (!ov) measure(U, g, w0, w1, w1 >= g.theta, mins, cnt);
-            if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
+            if (!spill_next(wait, waiting, ov, w0, w1, counters + 2, win)) break;
         }
         for (int o = 32; o > 0; o >>= 1) {
             mins += __shfl_xor(mins, o, 64);
@@ -1223,8 +1222,8 @@ sa_status run_spill(const DeviceScene &s, const DevicePath &p, const ViewEntry *
                     std::string &err)
 {
     hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, j0, s.voff, s.verts,
-                       s.height, p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries, (const uint32_t *)q.counters,
-                       q.capacity, q.counters + 2);
+                       s.height, p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries,
+                       q.counters, q.capacity);
     SA_CHECK_LAUNCH("accrual spill");
     return SA_OK;
 }
@@ -1364,7 +1363,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
     if (!tile_count(pts.n, tiles, err)) return SA_ERR_INVALID_ARG;
     const PointArgs P = point_args(pts, s);
     // Long spans run as several launches over consecutive segment ranges,
-    // each about kSpillWork point-segments and covering at most
+    // each of at most kSpillWork point-segments and covering at most
     // kViewBytes of views (built just before it);
     // outputs are accumulated, so the split is invisible in the results.
     const int64_t cap = seg_views_cap(s, p, scr, st);
@@ -1373,7 +1372,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
               " bytes) exceed the fixed scratch (" + std::to_string(scr.bytes) + " bytes)";
         return SA_ERR_CAPACITY;
     }
-    int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(pts.n, 1)), std::max<int64_t>(cap, 1));
+    int64_t per = std::min(std::max<int64_t>(1, kSpillWork / (64 * tiles)), std::max<int64_t>(cap, 1));
     if (seg_per_launch > 0) per = std::min<int64_t>(per, seg_per_launch);
     if (longest) {
         // whole days per launch, so a run never spans two launches (one
@@ -1420,7 +1419,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
         sa_status rc = build_seg_views(s, p.segs, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride},
                                        st, views, err);
         if (rc != SA_OK) return rc;
-        SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
+        SpillArgs S{q.entries, q.counters, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, pieces ? Split::kRunPieces : Split::kUniqueBins,
                                    res, q.grab, max_parts);
         BinOut O = bin_out(p, (int)j0, store, counts, minutes, minutes64, scale);

@@ -179,7 +179,7 @@ sa_status sa_create(int32_t device, void *hip_stream, sa_ctx **out)
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
     c->spill.capacity = sa::kSpillCapacity;
-    if (hipMalloc((void **)&c->spill.entries, sizeof(int4) * sa::kSpillCapacity) != hipSuccess ||
+    if (hipMalloc((void **)&c->spill.entries, sizeof(int4) * ((size_t)sa::kSpillSingles + sa::kSpillCapacity)) != hipSuccess ||
         hipMalloc((void **)&c->spill.counters, sizeof(uint32_t) * kCounterWords) != hipSuccess ||
         hipMemset(c->spill.counters, 0, sizeof(uint32_t) * kCounterWords) != hipSuccess) {
         sa_destroy(c);

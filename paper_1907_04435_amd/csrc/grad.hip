@@ -158,8 +158,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
             grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, valid && !covered && w != 0.f, 0.f, g.theta,
                          U, ov);
             scatter_grad(U, valid && !covered && !ov && w != 0.f, w * g.wrate, lds_uniform<GradArgs>((lds_int *)s_G));
-            if (ballot(valid && ov))
-                spill_push(lds_uniform<SpillArgs>((lds_int *)s_S), valid && ov, i, j, 0.f, g.theta);
+            const uint64_t over = ballot(valid && ov);
+            if (over) spill_push(lds_uniform<SpillArgs>((lds_int *)s_S), over, (int)i, j);
         }
     }
 }
@@ -170,8 +170,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
 __global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_g, int n_b, int j0,
                                                          const int32_t *voff_g, const float4 *verts_g,
                                                          const float *height_g, const SegConst *segs_g, PointArgs P,
-                                                         GradArgs G, const int4 *in, const uint32_t *in_count,
-                                                         int32_t cap, uint32_t *overflow)
+                                                         GradArgs G, const int4 *queue, uint32_t *counters, int32_t cap)
 {
     cfloat4 *verts = (cfloat4 *)verts_g;
     cfloat *height = (cfloat *)height_g;
@@ -181,17 +180,17 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_
     __shared__ TileFan s_tile[kWaves];
     TileFan *tile = &s_tile[tid() >> 6];
     const int lane = tid() & 63;
-    const int64_t total = min((int32_t)*in_count, cap);
-    const int64_t stride = (int64_t)n_wg() * kWaves;
-    for (int64_t e = (int64_t)wg_id() * kWaves + (tid() >> 6); e < total; e += stride) {
-        const int4 en = in[e];
-        const int64_t i = uniform(en.x);
-        const int j = uniform(en.y);
+    uint32_t singles;
+    const int64_t total = spill_items(counters, cap, singles), stride = (int64_t)n_wg() * kWaves;
+    for (int64_t t = (int64_t)wg_id() * kWaves + (tid() >> 6); t < total; t += stride) {
+        int j;
+        const int64_t i = spill_item(queue, singles, t, j);
+        if (i < 0) continue;
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
         const float w = G.dl ? G.dl[(int64_t)g.bin * P.n + i] : 1.f;
         const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr;
-        SpillWindow win{__int_as_float(uniform(en.z)), __int_as_float(uniform(en.w)), 0};
+        SpillWindow win{0.f, g.theta, 0};
         for (int waiting = 0;;) {
             float w0, w1;
             spill_share(win, lane, w0, w1);
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_
             bool ov;
             grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, true, w0, w1, U, ov);
             scatter_grad(U, !ov, w * g.wrate, G);
-            if (!spill_next(wait, waiting, ov, w0, w1, overflow, win)) break;
+            if (!spill_next(wait, waiting, ov, w0, w1, counters + 2, win)) break;
         }
     }
 }
@@ -242,19 +241,18 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     const GradArgs G{dl, acc, s.order};
     // segment ranges whose per-segment views fit the budget, each
     // followed by its spilled windows
-    const int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(pts.n, 1)), seg_views_cap(s, p, scr, st));
+    const int64_t per = std::min(std::max<int64_t>(1, kSpillWork / std::max<int64_t>(64 * tiles, 1)), seg_views_cap(s, p, scr, st));
     for (int64_t j0 = 0; pts.n > 0 && j0 < p.n_segs; j0 += per) {
         const int j1 = (int)std::min<int64_t>(j0 + per, p.n_segs);
         ViewEntry *views;
         rc = build_seg_views(s, p.segs, s.height, (int)j0, j1, scr, {q.counters, q.grab, 8 * kGrabStride}, st, views, err);
         if (rc != SA_OK) return rc;
-        SpillArgs S{q.entries, q.counters, q.counters + 2, q.capacity};
+        SpillArgs S{q.entries, q.counters, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
         hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}, views,
                            s.n_b, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
         hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, (int)j0, s.voff,
-                           s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, (const uint32_t *)q.counters,
-                           q.capacity, q.counters + 2);
+                           s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, q.counters, q.capacity);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
             err = std::string("gradient kernels: ") + hipGetErrorString(e);

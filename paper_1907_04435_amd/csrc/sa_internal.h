@@ -241,11 +241,13 @@ struct DevicePath {
     std::vector<double> sample_t, sample_w;
 };
 
-// Point-segments of a launch that queues its spilled windows, and the queue's
-// entries: one in 1e4 spills on the block scenes (one in 120 fills the queue).
-// An entry is 16 bytes.
-constexpr int64_t kSpillWork = 500000000ll;
-constexpr int32_t kSpillCapacity = 1 << 22;
+// The queue of spilled point-segments: entries (first point, segment, points
+// from that one on as 64 bits) of one point first, then of a tile's, of which a
+// launch of kSpillWork point-segments cannot need more.  One in 1e4 point-segments spills
+// on the block scenes, one in 77 among thin towers.
+constexpr uint32_t kSpillSingles = 1u << 20;
+constexpr int32_t kSpillCapacity = 1 << 23;
+constexpr int64_t kSpillWork = 64ll * kSpillCapacity;
 
 // Scratch owned by a context (grown on demand, freed with it), or a fixed
 // buffer the library never grows or frees (fixed = true).
@@ -327,15 +329,15 @@ struct PointsView {
 };
 
 struct SpillQueue {
-    int4 *entries = nullptr;       // (point, segment, w0 bits, w1 bits)
-    uint32_t *counters = nullptr;  // [0] queue length, [2] overflow flag
+    int4 *entries = nullptr;       // [kSpillSingles + capacity]
+    uint32_t *counters = nullptr;  // [0], [1] entries of one point and of a tile's, [2] overflow flag
     uint32_t *grab = nullptr;      // the accrual launch's work counters (eight, 128 B apart)
     int32_t capacity = 0;
 };
 
 // Device words a launch finds at zero (either may be null); n_counters <= 256.
 struct LaunchState {
-    uint32_t *queue_length;
+    uint32_t *queue_lengths;  // two
     uint32_t *counters;
     int32_t n_counters;
 };

@@ -930,20 +930,51 @@ __device__ __forceinline__ T lds_uniform(const lds_int *w)
 }
 
 struct SpillArgs {
-    int4 *out;          // queue to push to
-    uint32_t *counter;  // its length
-    uint32_t *overflow;
-    int32_t cap;
+    int4 *out;           // the queue: its one-lane entries, then the whole ones (kSpillSingles)
+    uint32_t *counters;  // their numbers, the overflow flag
+    int32_t cap;         // whole entries
 };
 
-__device__ __forceinline__ void spill_push(const SpillArgs &S, bool want, int64_t i, int j, float w0, float w1)
+// Queues the lanes of a wave (point i each, 64 of one tile) whose sets over
+// segment j are left to the spill launch, in entries of a point each while there
+// is room for them, else in one: so a launch of kSpillWork cannot fill the queue.
+// (Entries of a point alone, 4M of them for 5e8 point-segments, refused a city
+// of thin towers that left one window in 77.)
+__device__ __forceinline__ void spill_push(const SpillArgs &S, uint64_t lanes, int i, int j)
 {
-    if (!want) return;
-    const uint32_t slot = atomicAdd(S.counter, 1u);
-    if ((int32_t)slot < S.cap)
-        S.out[slot] = make_int4((int)i, j, __float_as_int(w0), __float_as_int(w1));
+    const uint32_t n = (uint32_t)__builtin_popcountll(lanes);
+    uint32_t base = 0;
+    if ((tid() & 63) == 0) base = atomicAdd(S.counters, n);
+    base = (uint32_t)uniform((int)base);
+    const bool fits = base <= kSpillSingles - n;
+    const uint32_t at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
+    // where they don't fit: empty ones to the end
+    if (lane_in(lanes) && at < kSpillSingles) S.out[at] = make_int4(i, j, fits ? 1 : 0, 0);
+    if (fits || (tid() & 63) != 0) return;
+    const uint32_t slot = atomicAdd(S.counters + 1, 1u);
+    if (slot < (uint32_t)S.cap)
+        S.out[kSpillSingles + slot] = make_int4(i, j, (int)(uint32_t)lanes, (int)(uint32_t)(lanes >> 32));
     else
-        atomicOr(S.overflow, 1u);
+        atomicOr(S.counters + 2, 1u);
+}
+
+// The items of a spill launch, a wave each: entries of a point (`singles` of
+// them), then the 64 places of the others.
+__device__ __forceinline__ int64_t spill_items(const uint32_t *counters, int32_t cap, uint32_t &singles)
+{
+    singles = min(counters[0], kSpillSingles);
+    return (int64_t)singles + 64 * (int64_t)min(counters[1], (uint32_t)cap);
+}
+
+// Item t's segment; returns its point, or less than 0 where the place is empty.
+__device__ __forceinline__ int spill_item(const int4 *queue, uint32_t singles, int64_t t, int &j)
+{
+    const bool single = t < singles;
+    const uint32_t u = (uint32_t)(t - singles);
+    const int4 e = queue[single ? (uint32_t)t : kSpillSingles + (u >> 6)];
+    j = uniform(e.y);
+    const int first = uniform(e.x), at = single ? 0 : uniform((int)(u & 63u));
+    return (uniform64((uint32_t)e.z, (uint32_t)e.w) >> at) & 1ull ? first + at : -1;
 }
 
 // Per-lane fan/box test of one segment: the fan of directions from p below
@@ -963,7 +994,7 @@ __device__ __forceinline__ void spill_push(const SpillArgs &S, bool want, int64_
 // counters at zero, cleared by the kernel before it (thread t < 256 of it).
 __device__ __forceinline__ void clear_state(const LaunchState &L, int64_t t)
 {
-    if (L.queue_length && t == 0) *L.queue_length = 0u;
+    if (L.queue_lengths && t < 2) L.queue_lengths[t] = 0u;
     if (t < L.n_counters) L.counters[t] = 0u;
 }
 
