@@ -211,10 +211,9 @@ void short_of_memory()
         settled([&]() { c.accrual(1000000); });
     }
     {  // and the sums of pieces beside them
-        Calls c(20000, 20, 5.0);
+        Calls c(100, 2, 30.0);
         r.limit = 100 * kMiB;
-        Calls few(100, 2, 30.0);
-        settled([&]() { few.accrual(1000); });
+        settled([&]() { c.accrual(1000); });
     }
     for (const bool masks : {false, true}) {  // the sampled form's views, or its masks
         Calls c(masks ? 100 : 20000, masks ? 3 : 20, 5.0);
