@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 
 #include "sa_internal.h"
 #include "traverse.h"
@@ -68,7 +69,10 @@ __global__ __launch_bounds__(kViewThreads) void k_views(const int32_t *__restric
         const int prim = vorder[min(j, n_b - 1)];
         const float4 q = pbox[prim];
         ViewEntry v;
-        seg_child(f, pad_lo(q.x), pad_lo(q.y), pad_hi(q.z), pad_hi(q.w), pad_hi(tops[prim]), in, v.c);
+        // (one variant's infinite height, or a padding past the largest float, must
+        // not lose the prism to all of them: infinity times a reach of zero)
+        const float top = fminf(pad_hi(tops[prim]), FLT_MAX);
+        seg_child(f, pad_lo(q.x), pad_lo(q.y), pad_hi(q.z), pad_hi(q.w), top, in, v.c);
         // its place among its group's: how many are nearer
         const float key = key_of(q);
         const int left = n_b - at;  // of the wave's
