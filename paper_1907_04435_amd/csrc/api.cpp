@@ -445,6 +445,14 @@ sa_status sa_sunpath(const sa_site *site, const sa_timespan *span, sa_sunpath_bu
 
 namespace {
 
+// A direction's component for the views' order: whatever the caller's sun is
+// (only its height is checked), finite and at most one, so that no place in a
+// view is computed from a NaN.
+float order_component(double v)
+{
+    return std::isfinite(v) ? (float)std::max(-1.0, std::min(1.0, v)) : 0.f;
+}
+
 // The great-circle geometry of a segment from knot direction a (at ta) to
 // b (at tb), both unit vectors above the horizon: plane basis, angle, the
 // lift of horizontal offsets into the plane (times |nz|), the fan's offsets
@@ -485,8 +493,8 @@ bool seg_geometry(const double *a, const double *b, double ta, double tb, sa::Se
     g.ub_y = (float)(b[1] / b[2]);
     g.rate = (float)((tb - ta) / theta);
     g.wrate = g.rate;
-    g.mdx = (float)(a[0] + e2[0] * 0.5 * theta);
-    g.mdy = (float)(a[1] + e2[1] * 0.5 * theta);
+    g.mdx = order_component(a[0] + e2[0] * 0.5 * theta);
+    g.mdy = order_component(a[1] + e2[1] * 0.5 * theta);
     return true;
 }
 
@@ -621,8 +629,8 @@ void fan_chunks(const std::vector<sa::SampleConst> &samples, std::vector<sa::Fan
             ch.f[7] = (float)-left[0];
         }
         const sa::SampleConst &mid = samples[(k0 + k1) / 2];
-        ch.mdx = mid.dx;
-        ch.mdy = mid.dy;
+        ch.mdx = order_component(mid.dx);
+        ch.mdy = order_component(mid.dy);
         ch.first = (int32_t)k0;
         ch.n = (int32_t)(k1 - k0);
         sa::ChunkSum cs{ch.first, ch.n | ((a.tag & sa::kDayStart) ? sa::kSumDayStart : 0) | sa::kSumEven,

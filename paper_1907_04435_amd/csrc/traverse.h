@@ -1077,11 +1077,13 @@ __device__ __forceinline__ float box_reach(float x0, float y0, float x1, float y
     return fmaf(y0, fminf(ny, 0.f), fmaf(y1, fmaxf(ny, 0.f), fmaf(x0, fminf(nx, 0.f), x1 * fmaxf(nx, 0.f))));
 }
 
-// Visit order of two child boxes in a segment: nearer along the
-// horizontal direction of the mid-segment sun first.
+// Visit order of the prisms of a segment's view: nearer along the horizontal
+// direction of the mid-segment sun first.  Half sums: finite, as (mdx, mdy) is
+// and neither above one, for every finite box, so the key is never a NaN and
+// each prism has a place of its own.
 __device__ __forceinline__ float seg_key(float x0, float y0, float x1, float y1, float mdx, float mdy)
 {
-    return fmaf(x0 + x1, mdx, (y0 + y1) * mdy);
+    return fmaf(fmaf(0.5f, x0, 0.5f * x1), mdx, fmaf(0.5f, y0, 0.5f * y1) * mdy);
 }
 
 // ---- the fan test on a segment's view of the scene ----

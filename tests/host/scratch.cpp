@@ -3,6 +3,7 @@
 // 0 if it holds.
 #include "fake_hip.h"
 
+#include <cmath>
 #include <vector>
 
 #include "shadow_accrual.h"
@@ -235,11 +236,52 @@ void short_of_memory()
     }
 }
 
+// Only the sun's height is checked at upload: whatever its horizontal part, the
+// directions that order the views' entries are finite and at most one, or two
+// entries could be given one place and another's be left as it was.
+void sun_without_direction()
+{
+    sa_ctx *ctx = nullptr;
+    OK(ctx, sa_create(0, nullptr, &ctx));
+    for (const double x : {(double)NAN, (double)INFINITY, -1e300, 1e39, 3.0}) {
+        int32_t so[2] = {0, 1}, ko[2] = {0, 2};
+        double t[1] = {0}, w[1] = {1}, kt[2] = {0, 2};
+        double d[3] = {x, x, 0.5}, kd[6] = {x, 0.2, 0.5, 0.3, 0.3, 0.6};
+        sa_sunpath_buf b{};
+        b.n_days = 1;
+        b.n_samples = 1;
+        b.n_knots = std::isnan(x) ? 0 : 2;  // coincident directions are refused, and a NaN makes them so
+        ko[1] = b.n_knots;
+        b.day_sample_off = so;
+        b.day_knot_off = ko;
+        b.t_min = t;
+        b.dir = d;
+        b.weight = w;
+        b.knot_t = kt;
+        b.knot_dir = kd;
+        const auto before = fake::rt().live;
+        sa_path *p = nullptr;
+        OK(ctx, sa_path_upload(ctx, &b, &p));
+        int seen = 0;
+        for (const auto &a : fake::rt().live) {
+            // a chunk of instants: a line, the direction at words 8 and 9; a segment: two, at 30 and 31
+            if (before.count(a.first) || (a.second != 64 && a.second != 128)) continue;
+            const float *f = (const float *)a.first + (a.second == 64 ? 8 : 30);
+            CHECK(std::fabs(f[0]) <= 1.f && std::fabs(f[1]) <= 1.f);
+            ++seen;
+        }
+        CHECK(seen >= (b.n_knots ? 3 : 1));  // (two copies of the segment)
+        sa_path_destroy(p);
+    }
+    sa_destroy(ctx);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
-    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}, {"short_of_memory", short_of_memory}};
+    const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}, {"short_of_memory", short_of_memory},
+                                                       {"sun_without_direction", sun_without_direction}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) {
         std::printf("no such scenario\n");

@@ -1,6 +1,7 @@
 """The library's host code over a runtime without a device (tests/host):
 memory is freed once and used only while it lives, and none is asked for under
-stream capture, nor twice where it was refused."""
+stream capture, nor twice where it was refused; what goes to the
+device is finite where kernels take places from it."""
 import os
 import shutil
 import subprocess
@@ -27,7 +28,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["edit_score", "capture", "short_of_memory"])
+@pytest.mark.parametrize("scenario", ["edit_score", "capture", "short_of_memory", "sun_without_direction"])
 def test_holds(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     print(r.stdout, r.stderr)
