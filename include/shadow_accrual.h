@@ -322,8 +322,9 @@ typedef struct {
  * synchronised, kept until sa_destroy.  Under stream capture make one
  * eager call of the same (or a larger) size first.  The sampled form keeps
  * the same views per 16 instants and a 16-bit mask per point and 16
- * instants, at most 256 MiB each per launch; it needs neither, nor
- * an eager call, under stream capture.
+ * instants, at most 256 MiB each per launch (with opts->longest no less
+ * than a day's views, and a day's masks of 64 points); it needs neither,
+ * nor an eager call, under stream capture.
  * Errors: INVALID_ARG, CAPACITY (reported by sa_sync if the accrual spill
  * queue overflows), OOM, DEVICE. */
 sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts,

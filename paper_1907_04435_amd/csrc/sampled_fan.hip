@@ -378,10 +378,13 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
         taken = true;
         return SA_OK;
     }
-    // chunks per launch: their views fit the budget; whole days where runs
-    // of shadow must not be cut
+    // chunks per launch: their views fit the budget, and so do the words of as
+    // many points as fill the device; whole days where runs of shadow must not
+    // be cut
     const int64_t view = s.n_b > 0 ? view_bytes(s.n_b) : 0;
-    const int64_t per = std::max<int64_t>(1, view > 0 ? kViewBytes / view : p.n_chunks);
+    const int64_t least = std::min<int64_t>((pts.n + 63) / 64 * 64, 1 << 14);
+    int64_t per = kMaskBytes / (2 * least);
+    if (view > 0) per = std::max<int64_t>(1, std::min(per, kViewBytes / view));
     std::vector<int> cut{0};
     for (int c = 1; c < p.n_chunks; ++c) {
         const bool may = !longest || p.chunk_day_start[c];
@@ -396,7 +399,7 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     int64_t most = 0;
     for (size_t k = 0; k + 1 < cut.size(); ++k) most = std::max<int64_t>(most, cut[k + 1] - cut[k]);
     // points per launch: their words fit the budget
-    const int64_t fit = std::max<int64_t>(kMaskBytes / (most * 2), 1 << 14);
+    const int64_t fit = std::max<int64_t>(kMaskBytes / (most * 2) / 64 * 64, 64);
     const int64_t ranges = (pts.n + fit - 1) / fit;  // of equal length: no short last one
     const int64_t range = ((pts.n + ranges - 1) / ranges + 63) / 64 * 64;
     // no room: the caller's other kernels need none

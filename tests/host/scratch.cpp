@@ -131,11 +131,11 @@ struct Calls {
     int32_t *counts = device<int32_t>(kMost), *var_ids = device<int32_t>(kVariants);
     int64_t *var_off = device<int64_t>(kVariants + 1);
 
-    Calls(int prisms, int days, double seg)
+    Calls(int prisms, int days, double seg, double step = 30.0)
     {
         OK(ctx, sa_create(0, nullptr, &ctx));
         scene = upload(ctx, prisms);
-        path = upload_path(ctx, days, 30.0, seg, true);
+        path = upload_path(ctx, days, step, seg, true);
     }
     ~Calls()
     {
@@ -150,10 +150,10 @@ struct Calls {
         const sa_accum_opts o{SA_ACCRUAL, 0, 1.f, 0, nullptr, nullptr, nullptr};
         OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
     }
-    void sampled(int64_t n)
+    void sampled(int64_t n, float *longest = nullptr)
     {
         const sa_points p = points(n);
-        const sa_accum_opts o{SA_SAMPLED, 0, 1.f, 0, nullptr, nullptr, nullptr};
+        const sa_accum_opts o{SA_SAMPLED, 0, 1.f, 0, nullptr, longest, nullptr};
         OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
     }
     void raster(int64_t n)
@@ -236,6 +236,22 @@ void short_of_memory()
     }
 }
 
+// The sampled form's views and masks stay within 256 MiB each, however many
+// instants a path has and however few prisms a scene.
+void fan_masks()
+{
+    for (const double step : {1.0, 0.1}) {
+        Calls c(20, step < 1.0 ? 40 : 365, 60.0, step);
+        for (const int64_t n : {(int64_t)1, (int64_t)20000, (int64_t)Calls::kMost})
+            for (const bool longest : {false, true}) {
+                fake::rt().largest = 0;
+                c.sampled(n, longest ? c.minutes : nullptr);
+                CHECK(fake::rt().largest <= 256u << 20);
+            }
+    }
+    CHECK(fake::launches("k_sampled_fan") > 0 && fake::launches("k_sampled_q") == 0);
+}
+
 // Only the sun's height is checked at upload: whatever its horizontal part, the
 // directions that order the views' entries are finite and at most one, or two
 // entries could be given one place and another's be left as it was.
@@ -281,7 +297,8 @@ void sun_without_direction()
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}, {"short_of_memory", short_of_memory},
-                                                       {"sun_without_direction", sun_without_direction}};
+                                                       {"sun_without_direction", sun_without_direction},
+                                                       {"fan_masks", fan_masks}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) {
         std::printf("no such scenario\n");
