@@ -640,16 +640,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
 // Adds the pieces of every run of a launch, in piece order, into the run's
 // bin: the launch's first run is stored or added to as O says for the
 // launch's first bin, the others as for its later bins.
-// One point and run (the y index) per thread.  A round trip to rows that other
+// One point and run (r0 + the y index) per thread.  A round trip to rows that other
 // XCDs have just written takes 2 us, so 24 rows are asked for at once, the
 // run's bin beside them (16,384 points, 20 rows: 9.3 -> 4.7 us).
 constexpr int kRowsInFlight = 24;
 
-__global__ __launch_bounds__(64) void k_add_pieces(Sched W, int j0, int j1, const SegConst *__restrict__ segs, int64_t n,
+__global__ __launch_bounds__(64) void k_add_pieces(Sched W, int r0, int j0, const SegConst *__restrict__ segs, int64_t n,
                                                    BinOut O, const int64_t *__restrict__ var_off, int V)
 {
     const int sub = W.sub > 1 ? W.sub : 1;
-    const int r = wg_id_y();
+    const int r = r0 + wg_id_y();
     const int64_t i = (int64_t)wg_id() * 64 + tid();
     if (i >= n) return;
     if (var_off && (i < var_off[0] || i >= var_off[V])) return;  // no variant's point
@@ -1168,6 +1168,17 @@ static int64_t piece_parts(Scratch &scr, int64_t n, hipStream_t st)
     return std::max<int64_t>(0, (int64_t)scr.bytes - 256) / per_part;
 }
 
+// k_add_pieces over a launch's runs, as many at a time as a grid has rows.
+static void add_pieces(const Sched &W, int j0, const DevicePath &p, int64_t n, const BinOut &O, const int64_t *var_off,
+                       int n_var, hipStream_t st)
+{
+    constexpr int kRows = 32768;
+    const int runs = (int)W.n_parts / W.sub;
+    for (int r0 = 0; r0 < runs; r0 += kRows)
+        hipLaunchKernelGGL(k_add_pieces, dim3((unsigned)((n + 63) / 64), (unsigned)std::min(kRows, runs - r0)), dim3(64), 0,
+                           st, W, r0, j0, (const SegConst *)p.segs, n, O, var_off, n_var);
+}
+
 static RoofBoxes roof_boxes(const DeviceScene &s) { return RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}; }
 
 static PointArgs point_args(const PointsView &pts, const DeviceScene &s)
@@ -1296,8 +1307,7 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
                            p.segs, (int)j0, j1, W, P, O, var_off, (const int64_t *)tile_off, n_var, flag);
         SA_CHECK_LAUNCH("batched accrual");
         if (W.sub > 1) {
-            hipLaunchKernelGGL(k_add_pieces, dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W,
-                               (int)j0, j1, (const SegConst *)p.segs, pts.n, O, var_off, n_var);
+            add_pieces(W, (int)j0, p, pts.n, O, var_off, n_var, st);
             SA_CHECK_LAUNCH("batched piece sums");
         }
     }
@@ -1432,9 +1442,7 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
                            s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, O, S, work);
         SA_CHECK_LAUNCH("accrual kernel");
         if (W.sub > 1) {
-            hipLaunchKernelGGL(k_add_pieces,
-                               dim3((unsigned)((pts.n + 63) / 64), W.n_parts / W.sub), dim3(64), 0, st, W, (int)j0, j1,
-                               (const SegConst *)p.segs, pts.n, O, (const int64_t *)nullptr, 0);
+            add_pieces(W, (int)j0, p, pts.n, O, nullptr, 0, st);
             SA_CHECK_LAUNCH("accrual piece sums");
         }
         rc = run_spill(s, p, views, (int)j0, P, scale, counts, minutes, minutes64, q, st, err);

@@ -131,11 +131,11 @@ struct Calls {
     int32_t *counts = device<int32_t>(kMost), *var_ids = device<int32_t>(kVariants);
     int64_t *var_off = device<int64_t>(kVariants + 1);
 
-    Calls(int prisms, int days, double seg, double step = 30.0)
+    Calls(int prisms, int days, double seg, double step = 30.0, bool one_bin = true)
     {
         OK(ctx, sa_create(0, nullptr, &ctx));
         scene = upload(ctx, prisms);
-        path = upload_path(ctx, days, step, seg, true);
+        path = upload_path(ctx, days, step, seg, one_bin);
     }
     ~Calls()
     {
@@ -252,6 +252,15 @@ void fan_masks()
     CHECK(fake::launches("k_sampled_fan") > 0 && fake::launches("k_sampled_q") == 0);
 }
 
+// More bins in a launch than a grid has rows: 192 years, a bin a day, in pieces.
+void many_bins()
+{
+    Calls c(2, 70000, 30.0, 480.0, false);
+    const int sums = fake::launches("k_add_pieces");
+    c.accrual(1);
+    CHECK(fake::launches("k_add_pieces") >= sums + 3);
+}
+
 // Only the sun's height is checked at upload: whatever its horizontal part, the
 // directions that order the views' entries are finite and at most one, or two
 // entries could be given one place and another's be left as it was.
@@ -298,7 +307,7 @@ int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> all = {{"edit_score", edit_score}, {"capture", capture}, {"short_of_memory", short_of_memory},
                                                        {"sun_without_direction", sun_without_direction},
-                                                       {"fan_masks", fan_masks}};
+                                                       {"fan_masks", fan_masks}, {"many_bins", many_bins}};
     const auto it = all.find(argc > 1 ? argv[1] : "");
     if (it == all.end()) {
         std::printf("no such scenario\n");

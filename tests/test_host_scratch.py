@@ -28,7 +28,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["edit_score", "capture", "short_of_memory", "sun_without_direction", "fan_masks"])
+@pytest.mark.parametrize("scenario", ["edit_score", "capture", "short_of_memory", "sun_without_direction", "fan_masks", "many_bins"])
 def test_holds(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     print(r.stdout, r.stderr)
