@@ -1,8 +1,7 @@
 """Autotuner: measures launch choices on the GPU and caches the best.
 
 * ``accrual_segments_per_launch``: how many path segments one accrual
-  launch covers (the per-segment hierarchy views it reads are its working
-  set), timed on the block scene's 4M points over three days.
+  launch covers (the per-segment views it reads are its working set), timed on the block scene's 4M points over three days.
 * ``tile_grid_blocks``: blocks of the persistent per-tile launches (0: as
   many as the device holds at once), timed on the same accrual launch.
 * ``accrual_waves_per_simd``: the accrual kernel's occupancy variant (6, 7
@@ -11,10 +10,9 @@
   or by packets of 1, 2, 4, 8 or 16 consecutive instants of 64 down to 4
   points, timed on the sampled form over the block scene's 4M points and
   three days.
-* ``batched_grid_blocks`` x ``batched_tiles_per_grab``: size of the
-  persistent (variant, tile) launch of sa_accumulate_batched and how many
-  64-point tiles a wave takes per atomic, timed on a 32-variant slice of
-  the batched scenario workload.
+* ``batched_grid_blocks``: blocks of the persistent launch of
+  sa_accumulate_batched (0: as many as the device holds at once), timed on
+  a 32-variant slice of the batched scenario workload.
 * ``seg_min``: knot spacing of the accrual form -- the fastest spacing
   whose error per point and day against the continuous duration stays
   within both bars: mean |error| <= ``error_bar`` minutes and at most
@@ -43,8 +41,8 @@ import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CACHE = os.path.join(HERE, "tuning.json")
-LAUNCH_KEYS = ("accrual_segments_per_launch", "batched_grid_blocks", "batched_tiles_per_grab", "tile_grid_blocks",
-               "accrual_waves_per_simd", "sampled_instants_per_packet")
+LAUNCH_KEYS = ("accrual_segments_per_launch", "batched_grid_blocks", "tile_grid_blocks", "accrual_waves_per_simd",
+               "sampled_instants_per_packet")
 
 
 def _time(torch, stream, fn, reps=3):
@@ -155,15 +153,13 @@ def tune_batched(sa, torch, ctx, log):
     off = torch.from_numpy(w.extra["var_off"].astype(np.int64)).cuda()
     mins = torch.empty((path.n_bins, dp.n), dtype=torch.float32, device="cuda")
     res = {}
-    for gb in (1024, 2048, 4096, 8192):
-        for grab in (1, 2, 4, 8):
-            ctx.set_launch(batched_grid_blocks=gb, batched_tiles_per_grab=grab)
-            res[(gb, grab)] = _time(torch, ctx.stream,
-                                    lambda: sa.sa_accumulate_batched(ctx, sc, ids, hh, dp, off, path, None, mins))
-            log(f"batched grid {gb}, {grab} tiles per grab: {res[(gb, grab)]:.2f} ms")
+    for gb in (0, 1024, 1536, 2048, 3072, 4096, 8192):
+        ctx.set_launch(batched_grid_blocks=gb)
+        res[gb] = _time(torch, ctx.stream,
+                        lambda: sa.sa_accumulate_batched(ctx, sc, ids, hh, dp, off, path, None, mins))
+        log(f"batched, persistent grid {gb or 'device-resident'} blocks: {res[gb]:.2f} ms")
     ctx.set_launch()
-    best = pick(res, (2048, 1))
-    return best, {f"{k[0]}x{k[1]}": v for k, v in res.items()}
+    return pick(res, 0), {str(k): v for k, v in res.items()}
 
 
 def tune_seg(sa, torch, ctx, log, error_bar, tail_bar):
@@ -203,11 +199,11 @@ def main():
     t0 = time.time()
     (per, tgb, occ), ares = tune_accrual(sa, torch, ctx, log)
     inst, sres = tune_sampled(sa, torch, ctx, log)
-    (gb, grab), bres = tune_batched(sa, torch, ctx, log)
+    gb, bres = tune_batched(sa, torch, ctx, log)
     L, lres = tune_seg(sa, torch, ctx, log, args.error_bar, args.tail_bar)
     out = {"arch": arch, "accrual_segments_per_launch": per, "tile_grid_blocks": tgb,
            "accrual_waves_per_simd": occ, "sampled_instants_per_packet": inst, "batched_grid_blocks": gb,
-           "batched_tiles_per_grab": grab, "seg_min": L, "error_bar": args.error_bar, "tail_bar": args.tail_bar,
+           "seg_min": L, "error_bar": args.error_bar, "tail_bar": args.tail_bar,
            "accrual_sweep_ms": ares, "sampled_sweep_ms": sres, "batched_sweep_ms": bres, "seg_sweep": lres, "seconds": time.time() - t0}
     with open(CACHE, "w") as f:
         json.dump(out, f, indent=1)
