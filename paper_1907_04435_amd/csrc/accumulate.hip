@@ -500,7 +500,7 @@ struct SegSrc {
 // The occluded set of every active lane's point over its window of segment g:
 // back-face term, then the walk of the view (which takes the whole wave).  On
 // return `ov` marks lanes whose set needed more than four pieces.
-template <bool kCount>
+template <bool kCount, bool kBlocks>
 __device__ __forceinline__ void accrue_segment(const SegSrc &src, cfloat4 *verts, const SegConst &g, const LanePoint &q,
                                                bool active, float w0, float w1, Union4 &U, bool &ov, Work &wk)
 {
@@ -539,7 +539,7 @@ __device__ __forceinline__ void accrue_segment(const SegSrc &src, cfloat4 *verts
         return over | (hit & ballot(U.n == 1 && U.lo[0] <= w0 && U.hi[0] >= w1));
     };
     const SegFan ft(g, q.px, q.py, q.pz);
-    walk_view<kCount>(src.view, src.n_b, src.voff, src.tile, ballot(live), ft, leaf, wk);
+    walk_view<kCount, kBlocks>(src.view, src.n_b, src.voff, src.tile, ballot(live), ft, leaf, wk);
     ov = lane_in(ovm);
 }
 
@@ -549,7 +549,7 @@ __global__ void k_clear_state(LaunchState L) { clear_state(L, tid()); }
 // them).  At 8 the kernel fits in 64 VGPRs (the compiler would settle for
 // fewer waves otherwise), which hides more of the scalar-load and
 // compare-chain latency of the traversal loop.
-template <bool kCount, int kOcc>
+template <bool kCount, int kOcc, bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))) void k_accrual(
     RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, SpillArgs S,
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
+        const bool covered = roof_covered<kBlocks>(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
 
         int cnt = 0;
         double mins = 0.0;  // per-lane FP64: long spans sum thousands of segment measures
@@ -606,9 +606,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kOcc))
             }
             Union4 U;
             bool ov;
-            const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b, (cint *)voff_g,
+            const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr, n_b, (cint *)voff_g,
                              tile, height};
-            accrue_segment<kCount>(src, verts, g, q, valid && !covered, 0.f, g.theta, U, ov, wk);
+            accrue_segment<kCount, kBlocks>(src, verts, g, q, valid && !covered, 0.f, g.theta, U, ov, wk);
             if constexpr (kCount) {
                 wk.units += valid ? 1u : 0u;
                 wk.spills += (valid && ov) ? 1u : 0u;
@@ -703,6 +703,7 @@ __device__ __forceinline__ void runs_update(const Union4 &U, float w0, float w1,
 // have to shrink below theta / 4096 to raise the overflow flag.  Seven
 // waves per SIMD (the compiler fits the kernel in 72 VGPRs) measured 4 %
 // faster than the six its natural allocation allows.
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_accrual_runs(
     RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O, float *longest,
@@ -741,7 +742,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
+        const bool covered = roof_covered<kBlocks>(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         const int ja = uniform(un.a), jb = uniform(un.b);
 
         int cnt = 0;
@@ -785,9 +786,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 const float w1 = fminf(w0 + s, g.theta);
                 Union4 U;
                 bool ov;
-                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b,
+                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr, n_b,
                                  (cint *)voff_g, tile, height};
-                accrue_segment<false>(src, verts, g, q, pending, w0, w1, U, ov, none);
+                accrue_segment<false, kBlocks>(src, verts, g, q, pending, w0, w1, U, ov, none);
                 if (pending) {
                     if (ov) {
                         if (s < g.theta * (1.0f / 4096.0f)) {
@@ -820,6 +821,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
 // The lanes' measures are summed across the wave and added with one atomic
 // per output.  One launch: as three rounds over two queues, with their
 // clears, it was seven (4 us each and the gaps where nothing is queued).
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_spill(
     const ViewEntry *views_g, int n_b, int j0, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
     const SegConst *segs_g, PointArgs P, float scale, int32_t *counts, float *minutes, double *minutes64,
@@ -841,7 +843,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
         if (i < 0) continue;
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
-        const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b, (cint *)voff_g,
+        const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr, n_b, (cint *)voff_g,
                          tile, height};
         SpillWindow win{0.f, g.theta, 0};
         double mins = 0.0;
@@ -852,7 +854,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
             Union4 U;
             bool ov;
             Work none{0, 0, 0, 0, 0, 0, 0};
-            accrue_segment<false>(src, verts, g, q, true, w0, w1, U, ov, none);
+            accrue_segment<false, kBlocks>(src, verts, g, q, true, w0, w1, U, ov, none);
             if (!ov) measure(U, g, w0, w1, w1 >= g.theta, mins, cnt);
             if (!spill_next(wait, waiting, ov, w0, w1, counters + 2, win)) break;
         }
@@ -877,6 +879,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
 // the wave and added with one FP64 atomic; a back-facing wall counts for
 // the point's own building.  Eight waves per SIMD (56 VGPRs): 17.5 ms on
 // the block scene against 19.4 at the compiler's seven.
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_contrib(const ViewEntry *views_g, int n_b, const int32_t *voff_g,
                                                       const float4 *verts_g, const float *height_g,
                                                       const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P,
@@ -974,7 +977,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
                 }
                 return 0;  // no lane retires: every building counts
             };
-            walk_view<false>(views_g + (int64_t)(j - j0) * view_shape(n_b).all, n_b, (cint *)voff_g, tile, ballot(active),
+            walk_view<false, kBlocks>(views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all, n_b, (cint *)voff_g, tile, ballot(active),
                              ft, leaf, none);
         }
         flush_held();
@@ -1045,6 +1048,7 @@ __global__ void k_var_heights(int64_t n, int k, const int32_t *__restrict__ ids,
 // variants of 1M points on 20,000 prisms took 2.37 ms, in (tile, bin) units
 // 1.70; 40 of 60,000 points on 3,000 prisms 1.05, in pieces 0.25; 5 of 300,000
 // on 400 prisms 1.51 and 0.67.
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_batched(
     RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *vh_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, BinOut O,
@@ -1086,7 +1090,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
         const int64_t i = var_off[v] + (t - tile_off[v]) * 64 + lane;
         const bool valid = i < var_off[v + 1];
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
+        const bool covered = roof_covered<kBlocks>(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         int cnt = 0;
         double mins = 0.0;
         int bin = jb > ja ? ld(segs + ja).bin : 0;
@@ -1108,9 +1112,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 const float w1 = fminf(w0 + s, g.theta);
                 Union4 U;
                 bool ov;
-                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr, n_b,
+                const SegSrc src{views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr, n_b,
                                  (cint *)voff_g, tile, height};
-                accrue_segment<false>(src, verts, g, q, pending, w0, w1, U, ov, none);
+                accrue_segment<false, kBlocks>(src, verts, g, q, pending, w0, w1, U, ov, none);
                 if (pending) {
                     if (ov) {
                         if (s < g.theta * (1.0f / 4096.0f)) {
@@ -1232,7 +1236,7 @@ sa_status run_spill(const DeviceScene &s, const DevicePath &p, const ViewEntry *
                     float scale, int32_t *counts, float *minutes, double *minutes64, SpillQueue &q, hipStream_t st,
                     std::string &err)
 {
-    hipLaunchKernelGGL(k_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, j0, s.voff, s.verts,
+    hipLaunchKernelGGL(has_blocks(s.n_b) ? k_spill<true> : k_spill<false>, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, j0, s.voff, s.verts,
                        s.height, p.segs, P, scale, counts, minutes, minutes64, (const int4 *)q.entries,
                        q.counters, q.capacity);
     SA_CHECK_LAUNCH("accrual spill");
@@ -1272,7 +1276,8 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
         return SA_ERR_OOM;
     }
     // on few tiles, runs in pieces as launch_accrual's
-    const int64_t res = resident_blocks(k_batched, L);
+    const auto kern = has_blocks(s.n_b) ? k_batched<true> : k_batched<false>;
+    const int64_t res = resident_blocks(kern, L);
     const bool pieces = tiles < 2 * res * kWaves;
     const int64_t max_parts = pieces ? piece_parts(piece_scr, pts.n, st) : 1;
     char *base = (char *)scr.ptr;
@@ -1302,7 +1307,7 @@ sa_status launch_batched(const DeviceScene &s, const DevicePath &p, int32_t n_va
             O.pcnt = (int32_t *)piece_scr.ptr;
             O.pmin = (double *)((char *)piece_scr.ptr + ((cnt_bytes + 255) & ~(size_t)255));
         }
-        hipLaunchKernelGGL(k_batched, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st,
                            roof_boxes(s), views, s.n_b, s.voff, s.verts, (const float *)vh,
                            p.segs, (int)j0, j1, W, P, O, var_off, (const int64_t *)tile_off, n_var, flag);
         SA_CHECK_LAUNCH("batched accrual");
@@ -1402,9 +1407,10 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
             ViewEntry *views;
             sa_status rc = build_seg_views(s, p.segs, s.height, j0, j1, scr, {nullptr, q.grab, 8 * kGrabStride}, st, views, err);
             if (rc != SA_OK) return rc;
-            const int64_t res = resident_blocks(k_accrual_runs, L);
+            const auto kern = has_blocks(s.n_b) ? k_accrual_runs<true> : k_accrual_runs<false>;
+            const int64_t res = resident_blocks(kern, L);
             const Sched W = plan_units(p.seg_runs, j0, j1, tiles, Split::kUniqueBins, res, q.grab);
-            hipLaunchKernelGGL(k_accrual_runs, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
+            hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0,
                                st, roof_boxes(s), views, s.n_b, s.voff, s.verts, s.height, p.segs, j0, j1, W, P,
                                bin_out(p, j0, store, counts, minutes, minutes64, scale), longest, q.counters + 2);
             SA_CHECK_LAUNCH("accrual kernel (continuous shadow)");
@@ -1412,9 +1418,11 @@ sa_status launch_accrual(const DeviceScene &s, const DevicePath &p, const Points
         }
         return SA_OK;
     }
-    auto kern = work ? k_accrual<true, 8> : k_accrual<false, 8>;
-    if (L.waves_per_simd == 6) kern = work ? k_accrual<true, 6> : k_accrual<false, 6>;
-    if (L.waves_per_simd == 7) kern = work ? k_accrual<true, 7> : k_accrual<false, 7>;
+    // (scenes of several blocks at eight waves per SIMD alone)
+    auto kern = work ? k_accrual<true, 8, false> : k_accrual<false, 8, false>;
+    if (L.waves_per_simd == 6) kern = work ? k_accrual<true, 6, false> : k_accrual<false, 6, false>;
+    if (L.waves_per_simd == 7) kern = work ? k_accrual<true, 7, false> : k_accrual<false, 7, false>;
+    if (has_blocks(s.n_b)) kern = work ? k_accrual<true, 8, true> : k_accrual<false, 8, true>;
     const int64_t res = resident_blocks(kern, L);
     // Too few tiles to give every resident wave several (tile, bin) units:
     // each bin's run is then cut into pieces, held as per-piece sums in
@@ -1475,10 +1483,11 @@ sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const P
         // prisms, 475 -> 409 on 15,000; 250,000 on 15,000: 1.82 -> 1.61 ms).  The
         // accrual form retires soonest under the lowest sun and gains nothing
         // from this order (60,000 points on 300 prisms: 133 -> 162 us).
-        const int64_t res = resident_blocks(k_contrib, L);
+        const auto kern = has_blocks(s.n_b) ? k_contrib<true> : k_contrib<false>;
+        const int64_t res = resident_blocks(kern, L);
         const Split split = tiles < 2 * res * kWaves ? Split::kChunks : Split::kBinRuns;
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, split, res, grab);
-        hipLaunchKernelGGL(k_contrib, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, views,
+        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, views,
                            s.n_b, s.voff, s.verts, s.height, p.segs_by_reach, (int)j0, j1, W, P, weight,
                            (const int32_t *)s.order, contrib);
         SA_CHECK_LAUNCH("contribution kernel");

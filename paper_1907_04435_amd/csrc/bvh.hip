@@ -469,6 +469,21 @@ __global__ __launch_bounds__(64) void k_group_boxes(int n_b, const int32_t *__re
     if (tid() == 0) gbox[g] = q;
 }
 
+// And of their blocks (after them), from the groups of groups'.
+__global__ __launch_bounds__(64) void k_block_boxes(int n_b, float4 *__restrict__ gbox)
+{
+    const ViewShape sh = view_shape(n_b);
+    const int g = wg_id();
+    float4 q = gbox[sh.n1 + min((g << kBlockBits) + (int)tid(), sh.n2 - 1)];
+    for (int o = 1; o < 64; o <<= 1) {
+        q.x = fminf(q.x, __shfl_xor(q.x, o, 64));
+        q.y = fminf(q.y, __shfl_xor(q.y, o, 64));
+        q.z = fmaxf(q.z, __shfl_xor(q.z, o, 64));
+        q.w = fmaxf(q.w, __shfl_xor(q.w, o, 64));
+    }
+    if (tid() == 0) gbox[sh.n1 + sh.n2 + g] = q;
+}
+
 // A single prism: one node whose right child is absent.
 __global__ void k_single(const int32_t *__restrict__ voff, Node *nodes, int32_t *parent)
 {
@@ -633,7 +648,7 @@ sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t
     SA_TRY(dalloc(s.pbox, n_b, err));
     const ViewShape groups = view_shape(n_b);
     SA_TRY(dalloc(s.vorder, n_b, err));
-    SA_TRY(dalloc(s.gbox, (size_t)groups.n1 + groups.n2, err));
+    SA_TRY(dalloc(s.gbox, (size_t)groups.n1 + groups.n2 + groups.n3, err));
     SA_TRY(dalloc(s.leaf_depth, n_b, err));
 #undef SA_TRY
     auto fail = [&](hipError_t e, const char *what) -> sa_status {
@@ -689,6 +704,7 @@ sa_status scene_build(DeviceScene &s, hipStream_t st, int32_t n_b, const int32_t
         return fail(e, "view order copy");
     hipLaunchKernelGGL(k_group_boxes, dim3(groups.n1 + groups.n2), dim3(64), 0, st, n_b,
                        (const int32_t *)s.vorder, (const float4 *)s.pbox, s.gbox);
+    if (groups.n3 > 1) hipLaunchKernelGGL(k_block_boxes, dim3(groups.n3), dim3(64), 0, st, n_b, s.gbox);
     if ((e = hipGetLastError())) return fail(e, "hierarchy kernels");
     rc = scene_refit(s, st, err);
     if (rc != SA_OK) {

@@ -35,6 +35,7 @@ struct GradArgs {
     const int32_t *order;  // hierarchy position -> original id
 };
 
+template <bool kBlocks>
 __device__ __forceinline__ void grad_segment(const ViewEntry *view, int n_b, cint *voff, TileFan *tile, cfloat4 *verts, cfloat *height,
                                              const SegConst &g, const LanePoint &q, bool active,
                                              float w0, float w1, UnionG &U, bool &ov)
@@ -67,7 +68,7 @@ __device__ __forceinline__ void grad_segment(const ViewEntry *view, int n_b, cin
     };
     const SegFan ft(g, q.px, q.py, q.pz);
     Work none{0, 0, 0, 0, 0, 0, 0};
-    walk_view<false>(view, n_b, voff, tile, ballot(live), ft, leaf, none);
+    walk_view<false, kBlocks>(view, n_b, voff, tile, ballot(live), ft, leaf, none);
     ov = lane_in(ovm);
 }
 
@@ -111,6 +112,7 @@ __device__ __forceinline__ void scatter_grad(const UnionG &U, bool ok, float wsc
 // Persistent: its units are (tile, every n-th segment), enough of them to
 // keep every wave busy on small point sets (the gradient sums are atomic, so
 // any split adds up the same).
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_grad(
     RoofBoxes B, const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g,
     const float *height_g, const SegConst *segs_g, int j0, int j1, Sched W, PointArgs P, GradArgs G, SpillArgs S)
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
         const int64_t i = (int64_t)un.tile * 64 + lane;
         const bool valid = i < Pd.n;
         const LanePoint q = load_point(Pd, i, valid);
-        const bool covered = roof_covered(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
+        const bool covered = roof_covered<kBlocks>(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
         int bin = -1;
         float w = 0.f;
         for (int j = ja; j < jb; j += step) {
@@ -154,8 +156,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
             }
             UnionG U;
             bool ov;
-            const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr;
-            grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, valid && !covered && w != 0.f, 0.f, g.theta,
+            const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr;
+            grad_segment<kBlocks>(view, n_b, (cint *)voff_g, tile, verts, height, g, q, valid && !covered && w != 0.f, 0.f, g.theta,
                          U, ov);
             scatter_grad(U, valid && !covered && !ov && w != 0.f, w * g.wrate, lds_uniform<GradArgs>((lds_int *)s_G));
             const uint64_t over = ballot(valid && ov);
@@ -167,6 +169,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
 // The adjoint's spilled point-segments: as the accrual form's, one wave each,
 // every lane one 64th of the window, sub-windows split again.  Ends clamped to
 // a sub-window do not move with a height, so splitting adds no gradient terms.
+template <bool kBlocks>
 __global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_g, int n_b, int j0,
                                                          const int32_t *voff_g, const float4 *verts_g,
                                                          const float *height_g, const SegConst *segs_g, PointArgs P,
@@ -189,14 +192,14 @@ __global__ __launch_bounds__(kThreads) void k_grad_spill(const ViewEntry *views_
         const LanePoint q = load_point(P, i, true);
         const SegConst g = ld(segs + j);
         const float w = G.dl ? G.dl[(int64_t)g.bin * P.n + i] : 1.f;
-        const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape(n_b).all : nullptr;
+        const ViewEntry *view = views_g ? views_g + (int64_t)(j - j0) * view_shape<kBlocks>(n_b).all : nullptr;
         SpillWindow win{0.f, g.theta, 0};
         for (int waiting = 0;;) {
             float w0, w1;
             spill_share(win, lane, w0, w1);
             UnionG U;
             bool ov;
-            grad_segment(view, n_b, (cint *)voff_g, tile, verts, height, g, q, true, w0, w1, U, ov);
+            grad_segment<kBlocks>(view, n_b, (cint *)voff_g, tile, verts, height, g, q, true, w0, w1, U, ov);
             scatter_grad(U, !ov, w * g.wrate, G);
             if (!spill_next(wait, waiting, ov, w0, w1, counters + 2, win)) break;
         }
@@ -236,7 +239,8 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
     if (rc != SA_OK) return rc;
     int64_t tiles;
     if (!tile_count(pts.n, tiles, err)) return SA_ERR_INVALID_ARG;
-    const int64_t res = resident_blocks(k_grad, L);
+    const auto kern = has_blocks(s.n_b) ? k_grad<true> : k_grad<false>;
+    const int64_t res = resident_blocks(kern, L);
     const PointArgs P{pts.n, pts.x, pts.y, pts.z, pts.nx, pts.ny, pts.owner, s.rank, s.n_b};
     const GradArgs G{dl, acc, s.order};
     // segment ranges whose per-segment views fit the budget, each
@@ -249,9 +253,9 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
         if (rc != SA_OK) return rc;
         SpillArgs S{q.entries, q.counters, q.capacity};
         const Sched W = plan_units(p.seg_runs, (int)j0, j1, tiles, Split::kChunks, res, q.grab);
-        hipLaunchKernelGGL(k_grad, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}, views,
+        hipLaunchKernelGGL(kern, dim3((unsigned)unit_blocks(res, W)), dim3(kThreads), 0, st, RoofBoxes{s.pbox, s.gbox, s.vorder, s.n_b, 0}, views,
                            s.n_b, s.voff, s.verts, s.height, p.segs, (int)j0, j1, W, P, G, S);
-        hipLaunchKernelGGL(k_grad_spill, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, (int)j0, s.voff,
+        hipLaunchKernelGGL(has_blocks(s.n_b) ? k_grad_spill<true> : k_grad_spill<false>, dim3(kSpillBlocks), dim3(kThreads), 0, st, views, s.n_b, (int)j0, s.voff,
                            s.verts, s.height, p.segs, P, G, (const int4 *)q.entries, q.counters, q.capacity);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {

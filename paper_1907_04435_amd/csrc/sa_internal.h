@@ -87,31 +87,38 @@ static_assert(sizeof(SegConst) == 128, "two lines");
 // them: the box terms of the fan test (the box edges shifted by the fan's
 // per-metre reach: x1 - z1 umnx, x0 - z1 umxx, y1 - z1 umny, y0 - z1 umxy; the
 // two wedge projections), of a group the least strict of its members'.  A
-// fan's view of the scene is the entries of the groups of 64 groups (two or
-// more of them), of the groups of 32 prisms (two or more), and of the prisms,
-// group by group along a Hilbert curve; siblings (up to 64 groups of groups, a
+// fan's view of the scene is the entries of the blocks of 64 groups of groups,
+// of the groups of 64 groups, of the groups of 32 prisms (of each where there
+// are two or more), and of the prisms, group by group along a Hilbert curve;
+// siblings (up to 64 blocks, a block's groups of groups, those' groups, a
 // group's prisms) nearest along the fan's middle direction first.
 struct alignas(32) ViewEntry {
     float c[6];
-    int32_t ref;    // prism (hierarchy position) or group
+    int32_t ref;    // prism (hierarchy position), group, or block
     uint32_t vert;  // prism: first vertex and, above kLeafVertBits, their number (0: see its offsets)
 };
 static_assert(sizeof(ViewEntry) == 32, "two 16-byte loads a lane");
 constexpr int kGroupBits = 5;  // prisms per group
 constexpr int kSuperBits = 6;  // groups per group of groups: as many as a wave has lanes
+constexpr int kBlockBits = 6;  // groups of groups per block: as many again
 constexpr int kLeafVertBits = 27;
 struct ViewShape {
-    int32_t n_b, n1, n2;     // prisms, groups, groups of groups
-    uint32_t at1, at0, all;  // entries before the groups, before the prisms, in all
+    int32_t n_b, n1, n2, n3;      // prisms, groups, groups of groups, blocks
+    uint32_t at2, at1, at0, all;  // entries before the groups of groups, the groups, the prisms, in all
 };
+// (kBlocks = false: of a scene known to have one block, at most 131,072 prisms.)
+template <bool kBlocks = true>
 constexpr ViewShape view_shape(int32_t n_b)
 {
     const int32_t n1 = (int32_t)(((uint32_t)n_b + (1u << kGroupBits) - 1u) >> kGroupBits);
     const int32_t n2 = (n1 + (1 << kSuperBits) - 1) >> kSuperBits;
-    const uint32_t at1 = n2 > 1 ? (uint32_t)n2 : 0u;
+    const int32_t n3 = kBlocks ? (n2 + (1 << kBlockBits) - 1) >> kBlockBits : 1;
+    const uint32_t at2 = n3 > 1 ? (uint32_t)n3 : 0u;
+    const uint32_t at1 = at2 + (n2 > 1 ? (uint32_t)n2 : 0u);
     const uint32_t at0 = at1 + (n1 > 1 ? (uint32_t)n1 : 0u);
-    return {n_b, n1, n2, at1, at0, at0 + (uint32_t)n_b};
+    return {n_b, n1, n2, n3, at2, at1, at0, at0 + (uint32_t)n_b};
 }
+inline bool has_blocks(int32_t n_b) { return view_shape(n_b).n3 > 1; }
 inline int64_t view_bytes(int32_t n_b) { return (int64_t)view_shape(n_b).all * (int64_t)sizeof(ViewEntry); }
 
 // A chunk of the sampled form: up to kFanInstants consecutive instants of one
@@ -160,7 +167,7 @@ struct DeviceScene {
     int32_t *flags = nullptr;    // [n_nodes] refit arrival counters
     float4 *pbox = nullptr;      // [n_b] prism footprint boxes, hierarchy order
     int32_t *vorder = nullptr;   // [n_b] views' order: hierarchy positions along a Hilbert curve
-    float4 *gbox = nullptr;      // [n1 + n2] footprint boxes of the groups and groups of groups (ViewShape)
+    float4 *gbox = nullptr;      // [n1 + n2 + n3] footprint boxes of the groups, groups of groups and blocks (ViewShape)
     int32_t *leaf_depth = nullptr;  // [n_b] nodes above each prism, hierarchy order
 };
 

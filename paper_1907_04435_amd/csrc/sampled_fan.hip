@@ -183,7 +183,7 @@ __device__ __forceinline__ uint32_t chunk_back(std::integer_sequence<int, K...>,
 // before the edges were paired), and 6, 7 and 8 waves per SIMD took 5.8, 5.5 and
 // 5.4 ms, 161, 173 and 184 us on 20,000 points and 400 prisms, where a wave's own
 // latency counts and the scalar registers spilled at 7 and 8 are felt.
-template <bool kCount>
+template <bool kCount, bool kBlocks>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_sampled_fan(
     const ViewEntry *views_g, int n_b, const int32_t *voff_g, const float4 *verts_g, const float *height_g,
     const FanChunk *chunks_g, const FanDirs *dirs_g, int c0, int c1, Sched W, PointArgs P, uint16_t *masks,
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                     return gm & ballot(pend == 0u);
                 };
                 const SegFan ft(fan_geom(ch), q.px, q.py, q.pz);
-                walk_view<kCount>(views_g + (int64_t)(c - c0) * view_shape(n_b).all, n_b, (cint *)voff_g, tile,
+                walk_view<kCount, kBlocks>(views_g + (int64_t)(c - c0) * view_shape<kBlocks>(n_b).all, n_b, (cint *)voff_g, tile,
                                   ballot(pend != 0u), ft, leaf, wk);
             }
             if (valid) s_masks[(int64_t)(c - c0) * n + i] = (uint16_t)(all & ~pend);
@@ -411,7 +411,8 @@ sa_status launch_sampled_fan(const DeviceScene &s, const DevicePath &p, const Po
     }
     taken = true;
     uint16_t *masks = (uint16_t *)mask_scr.ptr;
-    auto kern = work ? k_sampled_fan<true> : k_sampled_fan<false>;
+    auto kern = work ? k_sampled_fan<true, false> : k_sampled_fan<false, false>;
+    if (has_blocks(s.n_b)) kern = work ? k_sampled_fan<true, true> : k_sampled_fan<false, true>;
     const int64_t res = resident_blocks(kern, L);
     const auto &rs = p.chunk_runs.start;
     for (size_t k = 0; k + 1 < cut.size(); ++k) {

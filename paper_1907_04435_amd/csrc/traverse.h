@@ -1276,7 +1276,10 @@ __device__ __forceinline__ void leaf_range(uint32_t word, cint *voff, int prim, 
 // Groups in Morton order instead (whose runs jump, so far groups come before
 // near ones): 10.0 ms, eight times the spilled sets.  The extremes in scalar
 // registers and the shape held across the walk: 0.1 ms more.
-template <bool kCount, class LeafFn>
+// kBlocks: the scene has more than one block of groups of groups.  (Kernels are
+// built for either: the blocks' part costs the others' registers, 2 to 5 % of
+// every call on 5,000 and 20,000 prisms.)
+template <bool kCount, bool kBlocks, class LeafFn>
 __device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *voff, TileFan *tile, uint64_t alive,
                                           const SegFan &ft, LeafFn leaf, Work &w)
 {
@@ -1287,7 +1290,7 @@ __device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *
     auto shape = [&]() {
         int n = n_b;
         asm volatile("" : "+s"(n));
-        return view_shape(n);
+        return view_shape<kBlocks>(n);
     };
     cView *cv = (cView *)view;
     auto test = [&](uint32_t at, int &ref) -> uint64_t {
@@ -1302,13 +1305,26 @@ __device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *
     };
     auto first_of = [](int n) -> uint64_t { return n >= 64 ? ~0ull : (1ull << n) - 1ull; };
     int ref, none;
-    for (int c2 = 0;;) {
+    // the k3-th block, nearest first; its number is read where it is used, and
+    // what is left of its siblings found again after it, for registers' sake
+    auto first_super = [&](const ViewShape &sh, int k3) { return sh.n3 > 1 ? ld(cv + k3).ref << kBlockBits : 0; };
+    for (int k3 = 0;;) {
         ViewShape sh = shape();
+        if (sh.n3 > 1) {
+            const int c3 = k3 & ~63;
+            const uint64_t m3 = test((uint32_t)min(c3 + lane, sh.n3 - 1), none) & first_of(sh.n3 - c3) & (~0ull << (k3 & 63));
+            k3 = c3 + (m3 ? (int)__builtin_ctzll(m3) : 64);
+            if (k3 >= sh.n3) break;
+            if (!m3) continue;
+        }
         uint64_t m2 = 1ull;
-        if (sh.n2 > 1) m2 = test((uint32_t)min(c2 + lane, sh.n2 - 1), none) & first_of(sh.n2 - c2);
+        if (sh.n2 > 1) {
+            const int c2 = first_super(sh, k3);
+            m2 = test(sh.at2 + (uint32_t)min(c2 + lane, sh.n2 - 1), none) & first_of(sh.n2 - c2);
+        }
         while (m2) {
             sh = shape();
-            const int b1 = sh.n2 > 1 ? ld(cv + c2 + (int)__builtin_ctzll(m2)).ref << kSuperBits : 0;
+            const int b1 = sh.n2 > 1 ? ld(cv + sh.at2 + first_super(sh, k3) + (int)__builtin_ctzll(m2)).ref << kSuperBits : 0;
             m2 &= m2 - 1ull;
             uint64_t m1 = 1ull;
             if (sh.n1 > 1) m1 = test(sh.at1 + (uint32_t)min(b1 + lane, sh.n1 - 1), ref) & first_of(sh.n1 - b1);
@@ -1348,8 +1364,11 @@ __device__ __forceinline__ void walk_view(const ViewEntry *view, int n_b, cint *
             }
             m2 = alive ? m2 : 0ull;
         }
-        c2 += 64;
-        if (!alive || c2 >= shape().n2) break;
+        // (a loop for one block too, to the compiler: without it the adjoint's
+        // kernel keeps 41 registers in memory instead of 17, 6.36 -> 6.50 ms)
+        int blocks = shape().n3;
+        if constexpr (!kBlocks) asm volatile("" : "+s"(blocks));
+        if (!alive || ++k3 >= blocks) break;
     }
 }
 
@@ -1368,6 +1387,7 @@ struct RoofBoxes {
 // level, once a unit: 16,384 points on 64 prisms 40.9 -> 38.4 us, 20,000 on 300
 // 43.5 -> 39.1, 4M on 20,000 7.20 -> 7.00 ms, forward and adjoint at 1-minute
 // knots 6.83 -> 6.67 ms.
+template <bool kBlocks>
 __device__ __forceinline__ bool roof_covered(const RoofBoxes &B, cint *voff, cfloat4 *verts, cfloat *height,
                                              const LanePoint &q, bool valid)
 {
@@ -1395,10 +1415,17 @@ __device__ __forceinline__ bool roof_covered(const RoofBoxes &B, cint *voff, cfl
         return ballot(pad_lo(b.x) <= X1 && pad_hi(b.z) >= X0 && pad_lo(b.y) <= Y1 && pad_hi(b.w) >= Y0);
     };
     auto first_of = [](int n) -> uint64_t { return n >= 64 ? ~0ull : (1ull << n) - 1ull; };
-    const ViewShape sh = view_shape(B.n_b);
+    const ViewShape sh = view_shape<kBlocks>(B.n_b);
     const int lane = (int)(tid() & 63);
     uint64_t cov = 0;
     for (int c2 = 0; c2 < sh.n2; c2 += 64) {
+        if (sh.n3 > 1) {
+            // the next block that is met
+            const int k3 = c2 >> kBlockBits, c3 = k3 & ~63;
+            const uint64_t m3 = meets(B.gbox[sh.n1 + sh.n2 + min(c3 + lane, sh.n3 - 1)]) & first_of(sh.n3 - c3) & (~0ull << (k3 & 63));
+            c2 = (c3 + (m3 ? (int)__builtin_ctzll(m3) : 63)) << kBlockBits;
+            if (!m3) continue;
+        }
         uint64_t m2 = 1ull;
         if (sh.n2 > 1) m2 = meets(B.gbox[sh.n1 + min(c2 + lane, sh.n2 - 1)]) & first_of(sh.n2 - c2);
         for (; m2; m2 &= m2 - 1ull) {
