@@ -1175,18 +1175,8 @@ sa_status sa_region_score(sa_ctx *ctx, const sa_path *path, const float *values,
     }
     if (!set_device(ctx)) return fail(ctx, SA_ERR_DEVICE, "hipSetDevice failed");
     const size_t need = sizeof(double) * (size_t)n_bins;
-    if (ctx->scratch_w.bytes < need) {
-        (void)hipStreamSynchronize(ctx->stream);
-        (void)hipFree(ctx->scratch_w.ptr);
-        ctx->scratch_w.ptr = nullptr;
-        ctx->scratch_w.bytes = 0;
-        hipError_t e = hipMalloc(&ctx->scratch_w.ptr, need);
-        if (e != hipSuccess) {
-            ctx->scratch_w.ptr = nullptr;
-            return hip_fail(ctx, e, "sa_region_score: weights");
-        }
-        ctx->scratch_w.bytes = need;
-    }
+    if (!sa::reserve(ctx->scratch_w, need, ctx->stream))
+        return fail(ctx, SA_ERR_OOM, "sa_region_score: no room for the weights");
     // the weights go with the work on the stream (the host vector is gone
     // by the time the copy runs, so copy synchronously first)
     hipError_t e = hipStreamSynchronize(ctx->stream);

@@ -558,13 +558,9 @@ sa_status scene_edit_heights(DeviceScene &s, int32_t n, const int32_t *pos, cons
         return SA_OK;
     }
     const size_t bytes = sizeof(int32_t) * (size_t)n;  // positions, then heights
-    if (scr.bytes < 2 * bytes) {
-        (void)hipStreamSynchronize(st);  // an earlier edit may still read it
-        (void)hipFree(scr.ptr);
-        scr.ptr = nullptr;
-        scr.bytes = 0;
-        SA_HIP(hipMalloc(&scr.ptr, 2 * bytes));
-        scr.bytes = 2 * bytes;
+    if (!reserve(scr, 2 * bytes, st)) {
+        err = "device allocation failed";
+        return SA_ERR_OOM;
     }
     int32_t *dpos = (int32_t *)scr.ptr;
     float *dh = (float *)((char *)scr.ptr + bytes);

@@ -221,18 +221,9 @@ sa_status launch_grad(const DeviceScene &s, const DevicePath &p, const PointsVie
 {
     if (s.n_b == 0) return SA_OK;
     const size_t need = sizeof(double) * (size_t)s.n_b;
-    if (acc_scr.bytes < need) {
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(acc_scr.ptr);
-        acc_scr.ptr = nullptr;
-        acc_scr.bytes = 0;
-        if (hipMalloc(&acc_scr.ptr, need) != hipSuccess) {
-            (void)hipGetLastError();
-            acc_scr.ptr = nullptr;
-            err = "gradient accumulator allocation failed";
-            return SA_ERR_OOM;
-        }
-        acc_scr.bytes = need;
+    if (!reserve(acc_scr, need, st)) {
+        err = "no room for the gradient accumulator (under stream capture an eager call of the size comes first)";
+        return SA_ERR_OOM;
     }
     double *acc = (double *)acc_scr.ptr;
     sa_status rc = fill_u32(acc, 2 * (int64_t)s.n_b, 0u, st, err);

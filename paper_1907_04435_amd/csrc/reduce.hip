@@ -63,16 +63,9 @@ sa_status launch_region_sum(const float *v, int n_bins, int64_t n, const double 
                             std::string &err)
 {
     const size_t need = sizeof(double) * (size_t)n_reg * kBlocksPerRegion;
-    if (scr.bytes < need) {
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(scr.ptr);
-        scr.ptr = nullptr;
-        scr.bytes = 0;
-        if (hipMalloc(&scr.ptr, need) != hipSuccess) {
-            err = "region sum scratch allocation failed";
-            return SA_ERR_OOM;
-        }
-        scr.bytes = need;
+    if (!reserve(scr, need, st)) {
+        err = "no room for the region sums (under stream capture an eager call of the size comes first)";
+        return SA_ERR_OOM;
     }
     double *part = (double *)scr.ptr;
     hipLaunchKernelGGL(k_region_part, dim3(kBlocksPerRegion, n_reg), dim3(kThreads), 0, st, v, n_bins, n, bin_w, off,

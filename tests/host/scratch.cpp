@@ -162,6 +162,15 @@ struct Calls {
         const sa_sam_opts o{2.f, 0.1f, {0, 0, 0, 2000, 2000, 20}, 0, 1.f, 0};
         OK(ctx, sa_sam_accumulate(ctx, scene, &p, path, &o, counts, minutes));
     }
+    void gradient(int64_t n)
+    {
+        const sa_points p = points(n);
+        OK(ctx, sa_grad_heights(ctx, scene, &p, path, nullptr, nullptr, minutes));
+    }
+    void sums(int64_t n)
+    {
+        OK(ctx, sa_region_sum(ctx, minutes, n, var_off, 3, nullptr, (double *)x));
+    }
     void batched(int64_t n)
     {
         const sa_points p = points(n);
@@ -187,6 +196,28 @@ void capture()
             for (const int64_t n : {90000, 1, 100000}) call(n);
             CHECK(fake::rt().frees == frees);
         }
+    // without an eager call first, calls that need memory are refused, and the
+    // capture is as it was
+    Calls c(100, 2, 30.0);
+    const sa_points p = c.points(1000);
+    const sa_accum_opts o{SA_ACCRUAL, 0, 1.f, 0, nullptr, nullptr, nullptr};
+    fake::rt().capturing = true;
+    CHECK(sa_accumulate(c.ctx, c.scene, &p, c.path, &o, c.counts, c.minutes, nullptr) == SA_ERR_OOM);
+    CHECK(sa_accumulate_batched(c.ctx, c.scene, c.kVariants, 1, c.var_ids, c.var_h, &p, c.var_off, c.path, &o, c.counts,
+                                c.minutes) == SA_ERR_OOM);
+    CHECK(sa_grad_heights(c.ctx, c.scene, &p, c.path, nullptr, nullptr, c.minutes) == SA_ERR_OOM);
+    CHECK(sa_region_sum(c.ctx, c.minutes, 1000, c.var_off, 3, nullptr, (double *)c.x) == SA_ERR_OOM);
+    fake::rt().capturing = false;
+    c.accrual(1000);
+    c.batched(1000);
+    c.gradient(1000);
+    c.sums(1000);
+    fake::rt().capturing = true;
+    c.accrual(1000);
+    c.batched(1000);
+    c.gradient(1000);
+    c.sums(1000);
+    fake::rt().capturing = false;
 }
 
 // Where the memory a call would like cannot be had, the first call finds that
