@@ -275,7 +275,8 @@ typedef struct {
      * launch runs an instrumented instantiation that counts, per lane, the
      * work its own traversal needed -- [0] box tests, [1] prism tests,
      * [2] footprint edges visited in prism tests, [3] interval insertions,
-     * [4] box tests (per wave), [5] lanes x units (point-instants or
+     * [4] box tests (per wave; of packets the node fetches, two boxes
+     * each), [5] lanes x units (point-instants or
      * point-segments), [6] spilled windows, [7] leaf visits (per wave).  Slower; for
      * measurement only. */
     uint64_t *work;
@@ -315,12 +316,14 @@ typedef struct {
  * with a spilled point-segment (more than four pieces), whose measures are
  * added with float atomics in no fixed order.
  * The accrual form (here, and in sa_accumulate_batched, sa_grad_heights
- * and sa_building_contribution) keeps a per-segment view of the hierarchy
- * (32 bytes per prism and segment, at most 1 GiB per launch; longer paths
+ * and sa_building_contribution) keeps a per-segment view of the scene
+ * (33 bytes per prism and segment, at most 1 GiB per launch; longer paths
  * run as several launches, the continuous shadow one day at least) in
  * memory the context owns: grown on first need with the stream
- * synchronised, kept until sa_destroy.  Under stream capture make one
- * eager call of the same (or a larger) size first.  The sampled form keeps
+ * synchronised, kept until sa_destroy; a size that could not be had is not
+ * asked for again.  Under stream capture make one eager call of the same
+ * (or a larger) size first: a call that would need memory there is refused
+ * (OOM).  The sampled form keeps
  * the same views per 16 instants and a 16-bit mask per point and 16
  * instants, at most 256 MiB each per launch (with opts->longest no less
  * than a day's views, and a day's masks of 64 points); it needs neither,
@@ -335,7 +338,7 @@ sa_status sa_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points *pts
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): sa_accumulate with the same arguments, outputs and results,
  * except that it allocates nothing.  The accrual form's per-segment
- * views (32 bytes per prism and segment) go to a fixed device
+ * views (33 bytes per prism and segment) go to a fixed device
  * array of SA_NOALLOC_SCRATCH_BYTES that every device the library runs on
  * holds from its first sa_create until the process ends, and the spill
  * queue is the one sa_create made for the context; the sampled form needs

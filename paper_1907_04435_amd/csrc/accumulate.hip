@@ -18,7 +18,7 @@ using namespace dev;
 
 constexpr int kThreads = kSchedThreads;
 constexpr int kWaves = kSchedWaves;
-constexpr int kSpillBlocks = 1536;  // what the device holds of k_spill (1,024: block scene 6.78 ms, so 6.65)
+constexpr int kSpillBlocks = 1536;  // six of k_spill on each of 256 CUs (1,024: block scene 6.78 ms, so 6.65)
 constexpr int64_t kChunkWork = 2000000000ll;  // point-segments per contribution launch
 // Views per launch.  A launch has its set-up, its spilled
 // windows and a last unit that others wait for: a year on 45,000 prisms and

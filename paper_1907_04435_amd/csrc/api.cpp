@@ -97,7 +97,7 @@ bool set_device(sa_ctx *ctx)
 }  // namespace
 
 // Fixed device scratch of sa_accumulate_noalloc, for callers that cannot
-// allocate: the accrual form's per-segment hierarchy views.  Every device
+// allocate: the accrual form's per-segment views.  Every device
 // the library runs on holds its own copy from first use until the process
 // ends.  Host code never uses this name as an address: the device address
 // comes from hipGetSymbolAddress, once per device, in sa_create.

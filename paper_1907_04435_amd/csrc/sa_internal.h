@@ -359,7 +359,8 @@ struct TileLaunch {
     int64_t grid_blocks;
     int32_t n_cu;
     int32_t waves_per_simd;  // the accrual kernel's occupancy variant: 6, 7 or 8 (0: 8)
-    int32_t sampled_instants;  // instants per packet of the sampled form: 1, 2, 4, 8 or 16 (0: 8)
+    int32_t sampled_instants;  // instants per packet of the sampled form: 1, 2, 4, 8 or 16 (0: fans of
+                               // instants; of packets where those cannot be, 8)
 };
 
 sa_status launch_sampled(const DeviceScene &s, const DevicePath &p, const PointsView &pts,
@@ -399,13 +400,12 @@ sa_status measure_valu_peak(int n_cu, float *sink, int64_t sink_floats, hipStrea
 sa_status launch_contribution(const DeviceScene &s, const DevicePath &p, const PointsView &pts,
                               const float *weight, double *contrib, const TileLaunch &L, uint32_t *grab,
                               Scratch &scr, hipStream_t st, std::string &err);
-// Views of segments [j0, j1) into scr (grown as needed, with the stream
-// synchronised first; a fixed scr that is too small is a CAPACITY error), one
-// after the other, and `state` cleared; views = nullptr for an empty scene.
+// Views of segments [j0, j1) into scr (reserved; a fixed scr that is too small
+// is a CAPACITY error), one after the other, and `state` cleared; views = nullptr for an empty scene.
 // `tops`: the prisms' heights the views take (hierarchy order).
 // seg_views_cap: segments whose views a launch takes: the per-launch budget,
-// less where scr cannot be grown to it (a fixed scr, or one under stream
-// capture: its size; 0 if not even one fits).
+// less where scr cannot be grown to it (of a fixed scr what fits, 0 if not even
+// one does; under stream capture what fits, at least one).
 sa_status build_seg_views(const DeviceScene &s, const SegConst *segs, const float *tops, int j0, int j1, Scratch &scr,
                           const LaunchState &state, hipStream_t st, ViewEntry *&views, std::string &err);
 int64_t seg_views_cap(const DeviceScene &s, const DevicePath &p, Scratch &scr, hipStream_t st);

@@ -2,14 +2,14 @@
 //
 // Traversal is wave-coherent: a wave of 64 lanes (64 neighbouring points,
 // one sun instant or one path segment) walks the scene as one packet.
-// Segments and fans of instants go by views of it (walk_view, below); single
-// instants and roof tests by the binary hierarchy.  There the
-// node index is wave-uniform, so a node is fetched once per wave with a
-// scalar load into SGPRs; each lane tests the two child boxes against its
-// own ray or fan; a child is entered when any still-live lane needs it.
-// The traversal stack is wave-uniform too: one 64-entry array per wave in
-// LDS (every lane writes the same entry, pops are broadcast reads), so no
-// per-lane stack and no scratch memory is needed.
+// Segments and fans of instants go by views of it (walk_view, below), roof
+// tests by the boxes of the views' groups (roof_covered), single instants by
+// the binary hierarchy.  There the node index is wave-uniform, so a node is
+// fetched once per wave with a scalar load into SGPRs; each lane tests the two
+// child boxes against its own ray; a child is entered when any still-live lane
+// needs it.  The traversal stack is wave-uniform too: one 64-entry array per
+// wave in LDS (every lane writes the same entry, pops are broadcast reads), so
+// no per-lane stack and no scratch memory is needed.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -977,19 +977,6 @@ __device__ __forceinline__ int spill_item(const int4 *queue, uint32_t singles, i
     return (uniform64((uint32_t)e.z, (uint32_t)e.w) >> at) & 1ull ? first + at : -1;
 }
 
-// Per-lane fan/box test of one segment: the fan of directions from p below
-// height z1 projects on the ground to the triangle p, p + (z1 - pz) ua,
-// p + (z1 - pz) ub (central projection maps the great-circle arc to a
-// segment), so the box test is a 2D separating-axis test against that
-// triangle: its bounding box and the normals of its two edges through p.
-// (The third edge, at the far end, is left out: the bounding box already
-// bounds the far end, and measured over the block scene the edge removes
-// under 1% of the box hits for 23% of the test's arithmetic.)  For an edge
-// with normal n the box point farthest along n is the corner picked by
-// the signs of n, so max n.x over the box is
-//     x1 max(nx,0) + x0 min(nx,0) + y1 max(ny,0) + y0 min(ny,0),
-// a wave-uniform value (the box is the wave's node) compared with the
-// lane's n.p.
 // What a launch's persistent waves start from: an empty spill queue and work
 // counters at zero, cleared by the kernel before it (thread t < 256 of it).
 __device__ __forceinline__ void clear_state(const LaunchState &L, int64_t t)
@@ -1036,6 +1023,19 @@ __device__ __forceinline__ bool spill_next(SpillWindow *wait, int &waiting, bool
     win.level = uniform(next.level);
     return true;
 }
+
+// Per-lane fan/box test of one segment: the fan of directions from p below
+// height z1 projects on the ground to the triangle p, p + (z1 - pz) ua,
+// p + (z1 - pz) ub (central projection maps the great-circle arc to a
+// segment), so the box test is a 2D separating-axis test against that
+// triangle: its bounding box and the normals of its two edges through p.
+// (The third edge, at the far end, is left out: the bounding box already
+// bounds the far end, and measured over the block scene the edge removes
+// under 1% of the box hits for 23% of the test's arithmetic.)  For an edge
+// with normal n the box point farthest along n is the corner picked by
+// the signs of n, so max n.x over the box is
+//     x1 max(nx,0) + x0 min(nx,0) + y1 max(ny,0) + y0 min(ny,0),
+// a wave-uniform value (the box is the wave's) compared with the lane's n.p.
 
 // The fan of a segment seen from the xy plane: over the segment the rays
 // from p sweep the wedge between the horizontal offsets ua (first knot) and
