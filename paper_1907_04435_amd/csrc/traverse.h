@@ -962,8 +962,9 @@ __device__ __forceinline__ void spill_push(const SpillArgs &S, uint64_t lanes, i
 // them), then the 64 places of the others.
 __device__ __forceinline__ int64_t spill_items(const uint32_t *counters, int32_t cap, uint32_t &singles)
 {
-    singles = min(counters[0], kSpillSingles);
-    return (int64_t)singles + 64 * (int64_t)min(counters[1], (uint32_t)cap);
+    const uint2 n = *(const uint2 *)counters;  // (one round trip: all that a launch without entries does)
+    singles = min(n.x, kSpillSingles);
+    return (int64_t)singles + 64 * (int64_t)min(n.y, (uint32_t)cap);
 }
 
 // Item t's segment; returns its point, or less than 0 where the place is empty.
