@@ -427,7 +427,7 @@ typedef struct {
  * z; pts->owner, nx and ny must be NULL: walls would shade themselves).
  * Outputs as sa_accumulate (counts int32, minutes float, [n_bins * n],
  * either may be NULL).  The library keeps two segments' maps where both
- * stay within max_texels and can be had, else one (4 bytes per texel and
+ * can be had and stay within a given max_texels, else one (4 bytes per texel and
  * slice: a segment stamp and the depth to about 1 / 2^24 of its range) in
  * memory the context owns, grown on first need; calls on one context must
  * not overlap.  Not for direction-graph paths.

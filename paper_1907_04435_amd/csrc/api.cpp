@@ -1253,8 +1253,8 @@ sa_status sa_sam_accumulate(sa_ctx *ctx, const sa_scene *scene, const sa_points 
     const float scale = opts->out_scale == 0.f ? 1.f : opts->out_scale;
     const int64_t cap = opts->max_texels > 0 ? opts->max_texels : (int64_t)1 << 31;
     std::string err;
-    rc = sa::launch_sam(scene->d, path->d, view(pts), opts->texel_m, opts->bias_m, box, cap, scale, counts, minutes,
-                        ctx->scratch_sam, ctx->sam_stamp, ctx->stream, err);
+    rc = sa::launch_sam(scene->d, path->d, view(pts), opts->texel_m, opts->bias_m, box, cap, opts->max_texels > 0,
+                        scale, counts, minutes, ctx->scratch_sam, ctx->sam_stamp, ctx->stream, err);
     if (rc != SA_OK) return fail(ctx, rc, err);
     return SA_OK;
 }

@@ -156,10 +156,10 @@ struct Calls {
         const sa_accum_opts o{SA_SAMPLED, 0, 1.f, 0, nullptr, longest, nullptr};
         OK(ctx, sa_accumulate(ctx, scene, &p, path, &o, counts, minutes, nullptr));
     }
-    void raster(int64_t n)
+    void raster(int64_t n, int64_t max_texels = 0)
     {
         const sa_points p = points(n);
-        const sa_sam_opts o{2.f, 0.1f, {0, 0, 0, 2000, 2000, 20}, 0, 1.f, 0};
+        const sa_sam_opts o{2.f, 0.1f, {0, 0, 0, 2000, 2000, 20}, 0, 1.f, max_texels};
         OK(ctx, sa_sam_accumulate(ctx, scene, &p, path, &o, counts, minutes));
     }
     void gradient(int64_t n)
@@ -264,6 +264,15 @@ void short_of_memory()
         const int clears = fake::launches("k_sam_clear");
         settled([&]() { b.raster(1000); });
         CHECK(fake::launches("k_sam_clear") == clears + 1);
+    }
+    {  // which a caller's cap counts too
+        Calls a(100, 1, 30.0), b(100, 1, 30.0);
+        r.largest = 0;
+        a.raster(1000);
+        const size_t two = r.largest;
+        r.largest = 0;
+        b.raster(1000, (int64_t)(two / 4) - 8192);  // (less the points' bounds: one and not quite two)
+        CHECK(r.largest < two * 6 / 10 && r.largest > two * 4 / 10);
     }
 }
 
