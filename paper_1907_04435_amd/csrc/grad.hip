@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     while (next_unit((lds_int *)s_W, j0, j1, kx, un)) {
         const int ja = uniform(un.a), jb = uniform(un.b), step = uniform(un.step);
         const PointArgs Pd = lds_uniform<PointArgs>((lds_int *)s_P);
-        const int64_t i = (int64_t)un.tile * 64 + lane;
+        const uint32_t i = un.tile * 64u + (uint32_t)lane;  // (fewer than 2^31 points)
         const bool valid = i < Pd.n;
         const LanePoint q = load_point(Pd, i, valid);
         const bool covered = roof_covered<kBlocks>(lds_uniform<RoofBoxes>((lds_int *)s_B), (cint *)voff_g, verts, height, q, valid);
